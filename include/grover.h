@@ -77,16 +77,17 @@ typedef enum grover_form {
     GROVER_FORM_AUTO = 0,     /* RESIDENT for n <= 14 with f64/c64/c128 storage and binary64 sums; HELD for
                                  larger complex64 states with binary64 sums while they fit on chip; else FUSED */
     GROVER_FORM_FUSED = 1,    /* one persistent cooperative kernel per grover_iterate call, one grid
-                                 barrier per iteration, update fused with the next iteration's sum */
+                                 barrier per iteration, update fused with the next iteration's sum; with
+                                 binary64 sums a binary64, complex64 or complex128 state of at most 128 MiB on
+                                 256 CUs (and at least 64 KiB) is kept on chip for the whole call */
     GROVER_FORM_RESIDENT = 2, /* one workgroup holds the whole state on chip (n <= 14) */
     GROVER_FORM_TWO_PASS = 3, /* plain form: per iteration an oracle flip, a sum pass and an update pass,
                                  launched from the host (Algorithms 3 and 4 as separate kernels) */
-    GROVER_FORM_HELD = 4      /* complex64 with binary64 sums only: a team of T workgroups (a power of two;
-                                 about 2 16-byte vectors per thread up to 64 workgroups, at most 8 per
-                                 thread in registers while T <= 128, else 16 with 8 in LDS) loads the state once
-                                 per grover_iterate call and keeps it on chip for all k iterations, one team
-                                 barrier each; n <= 23 on 256 CUs (GROVER_E_UNSUPPORTED when the state does
-                                 not fit) */
+    GROVER_FORM_HELD = 4      /* complex64 with binary64 sums only: a team of T workgroups of 512 threads (T a
+                                 power of two; about 4 16-byte vectors per thread up to 64 workgroups, at most
+                                 16 while T <= 128, else 32) loads the state once per grover_iterate call and
+                                 keeps it on chip for all k iterations, one team barrier each; n <= 23 on 256
+                                 CUs (GROVER_E_UNSUPPORTED when the state does not fit) */
 } grover_form;
 
 /* ---------------------------------------------------------------------------------------- config */
@@ -198,10 +199,11 @@ int grover_sync(grover_ctx *ctx);
  * 6 = grid-barrier wait limit in device wall-clock ticks, 7 = workgroups per CU of the fused kernel as the
  * runtime's occupancy calculator reports them (the grid actually used is confirmed on the device), 8 = bytes
  * of the state per pass that the fused kernel streams with ordinary loads and stores, so that the next pass
- * finds them in the memory-side cache (the whole state up to 272 MiB; above that, the leading tiles of each
- * workgroup's share up to 272 MiB in all, the rest with nontemporal accesses; 0 for the other forms).  The
- * environment variable GROVER_FUSED_TEMPORAL, read at grover_init, forces 0 (all nontemporal) or 1 (all
- * ordinary).  Results are identical either way. */
+ * finds them in the memory-side cache, or keeps on chip (the whole state up to 272 MiB; above that, the leading
+ * tiles of each workgroup's share up to 272 MiB in all, the rest with nontemporal accesses; 0 for the other
+ * forms).  The environment variable GROVER_FUSED_TEMPORAL, read at grover_init, makes a state of any size
+ * stream, with all accesses nontemporal (0) or all ordinary (1); the results of the two are identical, and equal
+ * up to the order of the sums to those of a state kept on chip. */
 int grover_query(grover_ctx *ctx, int key, int64_t *value);
 
 /* grover_stream_probe — measurement helper, not a step of the method: the bandwidth ceiling that the fused
@@ -245,7 +247,7 @@ const char *grover_last_error(const grover_ctx *ctx);
  * tight serving loops, harnesses that forbid hipMalloc): k iterations of the proposed method exactly as
  * grover_iterate computes them on a GROVER_FORM_FUSED context with binary64 sums (the same kernel, grid and
  * order of additions, so the same bits), on a state and a marked list the caller holds, with no context.
- * The grid barrier's memory is a fixed array inside the library, 17472 bytes per GPU (barrier slots for a
+ * The grid barrier's memory is a fixed array inside the library, 19456 bytes per GPU (barrier slots for a
  * persistent grid of at most 256 workgroups), held until the process ends; nothing is allocated or freed.
  *   hip_stream  stream to enqueue on (NULL = default); the device is the current one.
  *   state_dev   device, 2^n amplitudes of `dtype` (grover_dtype), 16-byte aligned; updated in place.

@@ -67,8 +67,12 @@ void release(grover_ctx *c)
 
 int check_ctx(const grover_ctx *c) { return c ? GROVER_OK : GROVER_E_INVAL; }
 
-// Bytes of the fused kernel's barrier slots: [2][grid][4] member slots and the [2][4] published sum.
-size_t barrier_slot_bytes(int64_t grid) { return size_t(8 * grid + 8) * sizeof(uint64_t); }
+// Bytes of the barrier slots: the streaming fused kernel's [2][grid][4] member slots and [2][4] published
+// sum, or those of a team that holds the state on chip, whichever are more.
+size_t barrier_slot_bytes(int64_t grid)
+{
+    return std::max<size_t>(size_t(8 * grid + 8), size_t(team_words(uint64_t(grid)))) * sizeof(uint64_t);
+}
 
 // Clear the grid-barrier state (after a wait gave up, the device grid has exited by then; or before the
 // generation tags would wrap).  A failure is reported with the name of the call that failed.
@@ -94,6 +98,29 @@ int quiesce_device(grover_ctx *c, const char *what)
     return GROVER_OK;
 }
 
+// The held form's team must be co-resident (its members wait on each other): its barrier slots are
+// allocated and one team barrier is run under a short wait limit, as the fused form's grid is checked.
+int check_held_team(grover_ctx *c, int clock_khz)
+{
+    const int64_t team = int64_t(c->held_team);
+    GROVER_HIP(c, dev_alloc(&c->partials, barrier_slot_bytes(team)), "barrier allocation");
+    GROVER_HIP(c, hipMemset(c->partials, 0, barrier_slot_bytes(team)), "barrier allocation");
+    c->partials_grid = team;
+    GROVER_HIP(c, dev_alloc(&c->sync, sizeof(GridSync)), "barrier allocation");
+    if (int st = reset_barrier(c, "barrier reset before the team check"))
+        return st;
+    if (int st = quiesce_device(c, "device synchronise before the team check"))
+        return st;
+    const uint64_t probe_ticks = uint64_t(clock_khz > 0 ? clock_khz : 100000) * 250;  // 0.25 s
+    GROVER_HIP(c, launch_held_iterate(c, 0, probe_ticks, true), "held team check");
+    GROVER_HIP(c, hipStreamSynchronize(c->stream), "held team check");
+    GridSync gs;
+    GROVER_HIP(c, hipMemcpy(&gs, c->sync, sizeof(gs), hipMemcpyDeviceToHost), "held team check");
+    if (gs.error)
+        return fail(c, GROVER_E_COOP, "the held form's team is not co-resident on this device");
+    return GROVER_OK;
+}
+
 // Persistent grid of the fused form.  Every workgroup of a launch must be resident at once, or the first
 // grid barrier can never complete.  The runtime's occupancy figure has proved optimistic (MI355X admits
 // fewer workgroups per CU of this kernel than it reports), so the grid is confirmed on the device: the
@@ -106,6 +133,23 @@ int select_persistent_grid(grover_ctx *c, int clock_khz)
     int64_t forced = 0;
     GROVER_HIP(c, fused_configure(c, &per_cu, &block, &forced), "persistent grid configuration");
     c->per_cu_reported = per_cu;
+    if (c->held_team > 0) {  // the state stays on chip: a team instead of the streaming grid
+        const int st = check_held_team(c, clock_khz);
+        if (st == GROVER_OK) {
+            c->grid = int(c->held_team);
+            c->block = 512;
+            return GROVER_OK;
+        }
+        if (st != GROVER_E_COOP)
+            return st;
+        if (int rs = reset_barrier(c, "barrier reset after a failed team check"))
+            return rs;
+        (void)hipFree(c->partials);
+        (void)hipFree(c->sync);
+        c->partials = nullptr;
+        c->sync = nullptr;
+        c->held_team = 0;
+    }
     if (per_cu < 1)
         per_cu = 1;  // the runtime may report 0 workgroups per CU; the device check below decides
     const int64_t max_grid = forced > 0 ? forced : int64_t(per_cu) * c->cu_count;
@@ -139,29 +183,6 @@ int select_persistent_grid(grover_ctx *c, int clock_khz)
             break;
     }
     return fail(c, GROVER_E_COOP, "no persistent grid of the fused kernel is co-resident on this device");
-}
-
-// The held form's team must be co-resident (its members wait on each other): its barrier slots are
-// allocated and one team barrier is run under a short wait limit, as the fused form's grid is checked.
-int check_held_team(grover_ctx *c, int clock_khz)
-{
-    const int64_t team = int64_t(c->held_team);
-    GROVER_HIP(c, dev_alloc(&c->partials, barrier_slot_bytes(team)), "barrier allocation");
-    GROVER_HIP(c, hipMemset(c->partials, 0, barrier_slot_bytes(team)), "barrier allocation");
-    c->partials_grid = team;
-    GROVER_HIP(c, dev_alloc(&c->sync, sizeof(GridSync)), "barrier allocation");
-    if (int st = reset_barrier(c, "barrier reset before the team check"))
-        return st;
-    if (int st = quiesce_device(c, "device synchronise before the team check"))
-        return st;
-    const uint64_t probe_ticks = uint64_t(clock_khz > 0 ? clock_khz : 100000) * 250;  // 0.25 s
-    GROVER_HIP(c, launch_held_iterate(c, 0, probe_ticks, true), "held team check");
-    GROVER_HIP(c, hipStreamSynchronize(c->stream), "held team check");
-    GridSync gs;
-    GROVER_HIP(c, hipMemcpy(&gs, c->sync, sizeof(gs), hipMemcpyDeviceToHost), "held team check");
-    if (gs.error)
-        return fail(c, GROVER_E_COOP, "the held form's team is not co-resident on this device");
-    return GROVER_OK;
 }
 
 int run_iterations(grover_ctx *c, uint64_t k)
@@ -376,7 +397,7 @@ int grover_init(grover_ctx **out, const grover_config *cfg, void *hip_stream, vo
             c->block = kResidentBlock;
         } else if (form == GROVER_FORM_HELD) {
             c->grid = int(c->held_team);
-            c->block = 1024;
+            c->block = 512;
         } else {
             c->grid = twopass_blocks(c);
             c->block = 256;

@@ -252,7 +252,7 @@ int select_grid(grover_batch *b, int clock_khz)
     per_cu = std::min(per_cu, per_cu_held);
     const int max_grid = std::max(1, per_cu) * b->cu_count;
     BATCH_HIP(b, balloc(&b->team_sync, size_t(max_grid) * kBatchMaxPhases * sizeof(GridSync)), "batch allocation");
-    BATCH_HIP(b, balloc(&b->team_partials, size_t(max_grid) * kBatchMaxPhases * 8 * sizeof(uint64_t)),
+    BATCH_HIP(b, balloc(&b->team_partials, size_t(max_grid) * kBatchMaxPhases * kBatchSlotWords * sizeof(uint64_t)),
               "batch allocation");
     // work still running on other (non-blocking) streams could hold CUs and starve the check
     BATCH_HIP(b, hipDeviceSynchronize(), "device synchronise before the grid check");

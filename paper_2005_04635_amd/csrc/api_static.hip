@@ -14,8 +14,14 @@ namespace {
 constexpr int kStaticMaxGrid = 256;    // workgroups of the persistent grid (one per CU, at most this many)
 constexpr int kStaticMaxDevices = 64;  // devices whose scratch address is remembered
 constexpr uint64_t kSyncWords = sizeof(GridSync) / sizeof(uint64_t);
-constexpr uint64_t kSlotWords = 8u * kStaticMaxGrid + 8u;  // tagged slots [2][grid][4] and the sum [2][4]
-constexpr uint64_t kScratchWords = kSyncWords + kSlotWords;  // 2184 words = 17472 bytes
+// the slots of the streaming kernel ([2][grid][4] and the sum [2][4]) or of a team that holds the state on chip
+constexpr uint64_t slot_words(uint64_t grid, uint64_t team)
+{
+    return team > 0 ? team_words(team) : 8u * grid + 8u;
+}
+constexpr uint64_t kSlotWords = slot_words(0, kStaticMaxGrid);
+static_assert(kSlotWords >= slot_words(kStaticMaxGrid, 0) && kSlotWords >= slot_words(0, kFlatTeam), "the largest of all");
+constexpr uint64_t kScratchWords = kSyncWords + kSlotWords;  // 2432 words = 19456 bytes
 
 // The barrier's memory: the GridSync words (error word, ...) first, then the slots.  In host code this name
 // is only a stand-in for the symbol; its device address comes from hipGetSymbolAddress.
@@ -127,7 +133,8 @@ extern "C" int grover_iterate_static(void *hip_stream, void *state_dev, uint32_t
         return fail(GROVER_E_INVAL, "persistent grid beyond the static scratch (at most 256 workgroups)");
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     uint64_t *words = d.ptr;
-    uint64_t nwords = kSyncWords + 8u * uint64_t(grid) + 8u;
+    const uint32_t team = chip_team_size(dtype, GROVER_ACC_F64, N / elems_per_vec(dtype), d.cu_count);
+    uint64_t nwords = kSyncWords + slot_words(uint64_t(grid), team);
     GridSync *sync = reinterpret_cast<GridSync *>(d.ptr);
     void *ca[] = {&words, &nwords};
     hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(&static_clear_kernel), dim3(1), dim3(256), ca, 0,
@@ -153,6 +160,8 @@ extern "C" int grover_iterate_static(void *hip_stream, void *state_dev, uint32_t
         x.m = m;
         x.k = k;
         x.grid = int(grid);
+        x.team = team;
+        x.cu_count = d.cu_count;
         x.slots = d.ptr + kSyncWords;
         x.sync = sync;
         x.timeout_ticks = d.ticks_per_ms * 10000u;  // 10 s per barrier wait

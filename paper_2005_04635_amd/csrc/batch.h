@@ -6,6 +6,7 @@
 namespace grover {
 
 constexpr int kBatchMaxPhases = 12;
+constexpr uint64_t kBatchSlotWords = 16;  // barrier slot words per workgroup of the grid and phase
 constexpr int kBatchRegE = 8;                         // 16-byte vectors a thread holds in registers
 constexpr int kBatchLdsE = 8;                         // ... and in its own slots of LDS (128 KiB per workgroup)
 constexpr int kBatchHoldE = kBatchRegE + kBatchLdsE;  // 16 vectors = 32 complex64 amplitudes per thread
@@ -41,7 +42,7 @@ struct BatchLaunch {
     uint32_t update;             // grover_update of the element update
     unsigned long long *heads;   // one per phase
     GridSync *sync;              // [phase][grid]
-    uint64_t *partials;          // [phase][grid * 8]: team slots [2][T][4]
+    uint64_t *partials;          // [phase][grid * kBatchSlotWords]: the teams' slots, team_words(T) each
     int grid;
     uint64_t timeout_ticks;
     hipStream_t stream;

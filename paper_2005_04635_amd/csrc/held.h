@@ -1,6 +1,6 @@
 // Device code for states held on chip by a team of workgroups for all iterations (the batched kernel's
-// resident phases and the single-state held form): one iteration's update of a thread's held vectors and
-// the handling of the marked amplitudes around it.  Thread tid of a member holds its vectors
+// resident phases): one iteration's update of a thread's held vectors and the handling of the marked
+// amplitudes around it.  Thread tid of a member holds its vectors
 // e * 1024 + tid, e < ne: the first kHeldRegE in registers (x[e]), the others in its own slots of LDS
 // (held[(e - kHeldRegE) * 1024 + tid]; no other thread touches them, so they need no workgroup barrier).
 // Marked bits travel packed, two per vector (bits 2e, 2e + 1 of `mask` for vector e).
@@ -122,21 +122,6 @@ __device__ inline void held_sweep(float4 (&x)[kHeldRegE], float4 *held, unsigned
             if (unsigned(e) < ne)
                 unmarked_update(x[e], mr, mi, acc);
     }
-}
-
-// The sum of a thread's held vectors as they stand (e < ne in order, each vector's two amplitudes as
-// held_sweep adds them), without the signs: correct_marked then makes it the oracle-signed sum.  Adds in
-// exactly the order of an iteration, so a sum computed here from a stored state equals, bit for bit, the
-// one the iteration that stored it produced.
-__device__ inline void held_accumulate(const float4 (&x)[kHeldRegE], const float4 *held, unsigned ne, AccF64 &acc)
-{
-#pragma unroll
-    for (int e = 0; e < kHeldHoldE; ++e)
-        if (unsigned(e) < ne) {
-            const float4 v = e < kHeldRegE ? x[e] : held[(e - kHeldRegE) * kStreamBlock + threadIdx.x];
-            acc.add(double(v.x), double(v.y));
-            acc.add(double(v.z), double(v.w));
-        }
 }
 
 }  // namespace grover

@@ -364,6 +364,61 @@ __device__ inline double wave_total(double x)
 
 __device__ inline float wave_total(float x) { return wave_sum(x); }
 
+// Sums of a pair over a wave in half the instructions of two wave_totals: the pair is folded into one value
+// per lane (one swap of the wave's halves), then each half of 32 lanes is summed by DPP row shifts and one
+// broadcast of a row's last lane into the next row.  A fixed order, so the result is reproducible.
+// fold_pair: lane l < 32 gets a[l] + a[l + 32], lane l >= 32 gets b[l - 32] + b[l].
+__device__ inline double fold_pair(double a, double b)
+{
+    const unsigned long long x = (unsigned long long)__double_as_longlong(a), y = (unsigned long long)__double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap(unsigned(x), unsigned(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(unsigned(x >> 32), unsigned(y >> 32), false, false);
+    const double p = __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0]));
+    const double q = __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+    return p + q;
+}
+
+// row_totals: lane 15 of each row of 16 lanes gets the row's sum (other lanes: partial sums).
+__device__ inline double row_totals(double v)
+{
+    v += dpp_row_shifted<0x111>(v);  // row_shr:1
+    v += dpp_row_shifted<0x112>(v);  // row_shr:2
+    v += dpp_row_shifted<0x114>(v);  // row_shr:4
+    v += dpp_row_shifted<0x118>(v);  // row_shr:8
+    return v;
+}
+
+// half_totals: lane 31 gets the sum of lanes 0 .. 31, lane 63 that of lanes 32 .. 63 (other lanes: partial sums).
+__device__ inline double half_totals(double v)
+{
+    v = row_totals(v);
+    // row_bcast:15 into rows 1 and 3 only (row mask 0xa): lanes 16 .. 31 and 48 .. 63 add the row before's last lane
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, int(b), 0x142, 0xa, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), 0x142, 0xa, 0xf, true);
+    return v + __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
+}
+
+// fold_quad: four values over a wave into one per lane, in the rows of 16 lanes: row 0 gets a's partial sums, row
+// 1 c's, row 2 b's, row 3 d's.
+__device__ inline double fold_quad(double a, double b, double c, double d)
+{
+    const unsigned long long x = (unsigned long long)__double_as_longlong(fold_pair(a, b));
+    const unsigned long long y = (unsigned long long)__double_as_longlong(fold_pair(c, d));
+    const auto lo = __builtin_amdgcn_permlane16_swap(unsigned(x), unsigned(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(unsigned(x >> 32), unsigned(y >> 32), false, false);
+    const double p = __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0]));
+    const double q = __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+    return p + q;
+}
+
+// Number of this block in an order that keeps the blocks of one XCD together (blocks go round the 8 XCDs in
+// launch order), so that a team of consecutive numbers has the shortest way between its members.
+__device__ inline unsigned xcd_major_block()
+{
+    return gridDim.x % 8u == 0u ? (blockIdx.x % 8u) * (gridDim.x / 8u) + blockIdx.x / 8u : blockIdx.x;
+}
+
 // Workgroup sum of (a, b): wave butterflies, then thread 0 adds the per-wave values in wave order.
 // `red` must hold 2 * (blockDim / 64) values.  Result valid in thread 0 only.
 template <class V>
@@ -407,6 +462,19 @@ struct GridSync {
 };
 static_assert(sizeof(GridSync) == 1024, "barrier words on separate lines");
 
+// ------------------------------------------------------------------------------- team barrier memory
+// Teams of more than kFlatTeam workgroups whose size is a multiple of 8 meet in two levels (see team_sum).
+constexpr unsigned kFlatTeam = 128;
+__host__ __device__ constexpr bool team_two_level(uint64_t size) { return size > kFlatTeam && size <= 256 && size % 8 == 0; }
+// Bytes between member slots: 64 (two members to a 128-byte line) up to kFlatTeam, else 32.
+__host__ __device__ constexpr unsigned team_stride(uint64_t size) { return size <= kFlatTeam ? 64u : 32u; }
+constexpr uint64_t kGroupWords = 16;  // a group's sum in a two-level team: a 128-byte line each
+// 64-bit words of a team's slots: two sets of member slots, then two sets of group sums.
+__host__ __device__ constexpr uint64_t team_words(uint64_t size)
+{
+    return 2 * size * team_stride(size) / 8 + (team_two_level(size) ? 2 * 8 * kGroupWords : 0);
+}
+
 // ------------------------------------------------------------------------------------------ context
 }  // namespace grover
 
@@ -428,7 +496,7 @@ struct grover_ctx {
     // fused form
     int grid = 0;
     int block = 0;
-    uint64_t *partials = nullptr;  // fused barrier: slots [2][grid][4] and the published sum [2][4]
+    uint64_t *partials = nullptr;  // barrier slots of the fused grid or of the team that holds the state
     int64_t partials_grid = 0;     // the largest grid those slots were allocated for
     int per_cu_reported = 0;       // workgroups per CU of the fused kernel according to the runtime
     grover::GridSync *sync = nullptr;
@@ -436,7 +504,7 @@ struct grover_ctx {
     const void *fused_check_kernel = nullptr;  // its code-identical twin for the residency check
     uint64_t fused_tile = 0;             // 16-byte vectors per tile of that variant
     uint64_t fused_temporal_bytes = 0;   // bytes per pass streamed with ordinary (not nontemporal) accesses
-    uint32_t held_team = 0;              // held form: workgroups holding the state (one launch of that many)
+    uint32_t held_team = 0;              // held form, or fused form on chip: workgroups holding the state
     uint64_t generation = 0;
     uint64_t timeout_ticks = 0;
     // two-pass form and reductions
@@ -485,6 +553,8 @@ struct FusedExternal {
     uint64_t m;
     uint64_t k;
     int grid;
+    uint32_t team;  // > 0: the on-chip kernel with this team instead of the streaming one on `grid`
+    int cu_count;
     uint64_t *slots;
     GridSync *sync;
     uint64_t timeout_ticks;
@@ -497,8 +567,28 @@ void set_thread_error(const std::string &msg);
 hipError_t launch_resident_iterate(grover_ctx *c, uint64_t k);
 
 // Held form (complex64, binary64 sums): workgroups that hold a state of nvec vectors, 0 when it does not fit
-// a team of at most max_team (a power of two); and the launch (`probe`: one team barrier only).
+// a team of at most max_team (a power of two); the fused form's team on chip (0: the state streams); and the
+// launches (`probe`: one team barrier only).
 uint32_t held_team_size(uint64_t nvec, uint32_t max_team);
+uint32_t chip_team_size(uint32_t dtype, uint32_t accum, uint64_t nvec, int cu_count);
+struct ChipLaunch {
+    void *state;
+    uint32_t dtype;
+    uint32_t update;  // grover_update
+    uint64_t N;
+    const uint64_t *marks;
+    uint64_t m;
+    uint64_t k;
+    uint32_t team;
+    int cu_count;
+    uint64_t *partials;  // team slots: team_words(team), zero or of generations up to gen0
+    GridSync *sync;
+    uint64_t gen0;
+    uint64_t timeout_ticks;
+    bool probe;
+    hipStream_t stream;
+};
+hipError_t launch_chip(const ChipLaunch &L);
 hipError_t launch_held_iterate(grover_ctx *c, uint64_t k, uint64_t timeout_ticks, bool probe = false);
 
 hipError_t launch_twopass_iterate(grover_ctx *c, uint64_t k);

@@ -41,24 +41,6 @@ struct BatchArgs {
     uint64_t timeout_ticks;
 };
 
-// Workgroup sum of (a, b) for every thread with one workgroup barrier: wave totals, then every thread adds
-// the wave values by the same fixed tree (the same bits everywhere).  The wave values alternate between two
-// buffers by `parity`: a buffer is rewritten two calls later, after the next call's barrier, which every
-// thread reaches only after reading it.
-__device__ inline void block_allsum(double &a, double &b, unsigned parity, TeamShared<double> &sh)
-{
-    const unsigned lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    double *red = sh.red[parity & 1u];
-    a = wave_total(a);
-    b = wave_total(b);
-    if (lane == 0) {
-        red[2 * wave] = a;
-        red[2 * wave + 1] = b;
-    }
-    __syncthreads();
-    add_wave_values(red, a, b);
-}
-
 // Sets an error word (the team's, which its members' barrier waits poll, or the workgroup's own), which
 // the host reads after the run and reports as a failure.
 __device__ inline void flag_error(GridSync *word)
@@ -76,14 +58,14 @@ __device__ inline float4 uniform_vec(double amp)
 // One instance streamed by the T workgroups of a team.  Returns false when a barrier gave up.
 template <bool U32>
 __device__ bool run_team_streamed(const BatchArgs &a, const BatchInstance &I, const Team &tm, uint64_t &gen,
-                                  TeamShared<double> &sh, uint32_t *table)
+                                  TeamShared<kStreamBlock> &sh, uint32_t *table)
 {
     const Share<C64> share{a.state + I.state_off, I.nvec, a.marks + I.marks_off, I.m, tm.rank, tm.size};
     const bool use_table = build_mark_table(share, table);
     AccF64 acc0;
     stream_pass<C64, AccF64, kFill>(share, table, use_table, 0.0, 0.0, uniform_vec(I.amp), acc0);
     double sr = acc0.r, si = acc0.i;
-    if (!team_sum<double>(sr, si, tm, ++gen, sh))
+    if (!team_sum<kStreamBlock>(sr, si, tm, ++gen, sh))
         return false;
     const float4 none{};
     for (uint64_t it = 0; it < I.iters; ++it) {
@@ -92,7 +74,7 @@ __device__ bool run_team_streamed(const BatchArgs &a, const BatchInstance &I, co
         stream_pass<C64, AccF64, kUpdate, U32>(share, table, use_table, mr, mi, none, acc);
         sr = acc.r;
         si = acc.i;
-        if (!team_sum<double>(sr, si, tm, ++gen, sh))
+        if (!team_sum<kStreamBlock>(sr, si, tm, ++gen, sh))
             return false;
     }
     return true;
@@ -107,7 +89,7 @@ __device__ bool run_team_streamed(const BatchArgs &a, const BatchInstance &I, co
 // the end.  Returns false when a barrier gave up.
 template <bool U32, class Reduce>
 __device__ bool run_held(const BatchArgs &a, const BatchInstance &I, uint64_t base, uint64_t per, float4 *held,
-                         TeamShared<double> &sh, Reduce reduce)
+                         TeamShared<kStreamBlock> &sh, Reduce reduce)
 {
     float4 *st = a.state + I.state_off + base;
     const uint64_t *marks = a.marks + I.marks_off;
@@ -166,7 +148,7 @@ __device__ bool run_held(const BatchArgs &a, const BatchInstance &I, uint64_t ba
 
 // One instance iterated by one workgroup, its state streamed from memory.
 template <bool U32>
-__device__ void run_single_streamed(const BatchArgs &a, const BatchInstance &I, TeamShared<double> &sh,
+__device__ void run_single_streamed(const BatchArgs &a, const BatchInstance &I, TeamShared<kStreamBlock> &sh,
                                     uint32_t *table)
 {
     const Share<C64> share{a.state + I.state_off, I.nvec, a.marks + I.marks_off, I.m, 0, 1};
@@ -195,21 +177,24 @@ __device__ void run_single_streamed(const BatchArgs &a, const BatchInstance &I, 
 template <bool kStreams, bool U32>
 __global__ __launch_bounds__(kStreamBlock) void batch_kernel(BatchArgs a)
 {
-    __shared__ TeamShared<double> sh;
+    __shared__ TeamShared<kStreamBlock> sh;
     __shared__ uint32_t table[kMarkWords];
     __shared__ uint64_t taken;
     __shared__ float4 held[kLdsE * kStreamBlock];  // on-chip state beyond the registers (128 KiB)
     const uint32_t grid = gridDim.x;
+    const unsigned major = xcd_major_block();
     if (a.probe) {
         const Team tm{a.sync, a.partials, grid, blockIdx.x, a.timeout_ticks};
         double zr = 0.0, zi = 0.0;
-        (void)team_sum<double>(zr, zi, tm, 1u, sh);
+        (void)team_sum<kStreamBlock>(zr, zi, tm, 1u, sh);
         return;
     }
     for (uint32_t p = 0; p < a.nphases; ++p) {
         const uint64_t q0 = a.qoff[p], count = a.qoff[p + 1] - q0;
         const unsigned T = a.team[p];
-        const unsigned teams = grid / T, team_id = blockIdx.x / T;
+        // a team of the whole grid meets in two levels by XCD, which ranks by launch order give (team_sum)
+        const unsigned block = T == grid ? blockIdx.x : major;
+        const unsigned teams = grid / T, team_id = block / T;
         if (count == 0 || team_id >= teams)
             continue;
         if (T == 1) {
@@ -233,12 +218,12 @@ __global__ __launch_bounds__(kStreamBlock) void batch_kernel(BatchArgs a)
                 else if (kStreams)
                     run_single_streamed<U32>(a, I, sh, table);
                 else
-                    flag_error(a.sync + uint64_t(p) * grid + blockIdx.x);
+                    flag_error(a.sync + uint64_t(p) * grid + block);
             }
             continue;
         }
         const Team tm{a.sync + uint64_t(p) * grid + team_id,
-                      a.partials + uint64_t(p) * 8u * grid + uint64_t(team_id) * 8u * T, T, blockIdx.x % T,
+                      a.partials + uint64_t(p) * kBatchSlotWords * grid + uint64_t(team_id) * team_words(T), T, block % T,
                       a.timeout_ticks};
         uint64_t gen = 0;
         for (;;) {
@@ -247,7 +232,7 @@ __global__ __launch_bounds__(kStreamBlock) void batch_kernel(BatchArgs a)
             double zr = 0.0, zi = 0.0;
             if (tm.rank == 0 && threadIdx.x == 0)
                 zr = double(atomicAdd(&a.heads[p], 1ull));
-            if (!team_sum<double>(zr, zi, tm, ++gen, sh))
+            if (!team_sum<kStreamBlock>(zr, zi, tm, ++gen, sh))
                 return;
             const uint64_t qv = uint64_t(zr);  // the same in every lane (a team sum); made scalar below
             const uint64_t q = __builtin_amdgcn_readfirstlane(uint32_t(qv)) |
@@ -259,7 +244,7 @@ __global__ __launch_bounds__(kStreamBlock) void batch_kernel(BatchArgs a)
             if (a.resident[p]) {
                 const uint64_t per = I.nvec / T;
                 ok = run_held<U32>(a, I, uint64_t(tm.rank) * per, per, held, sh,
-                                   [&](double &r, double &i) { return team_sum<double>(r, i, tm, ++gen, sh); });
+                                   [&](double &r, double &i) { return team_sum<kStreamBlock>(r, i, tm, ++gen, sh); });
             } else if (kStreams) {
                 ok = run_team_streamed<U32>(a, I, tm, gen, sh, table);
             } else {
@@ -323,7 +308,7 @@ hipError_t launch_batch(const BatchLaunch &L)
     uint64_t *words = reinterpret_cast<uint64_t *>(L.sync);
     uint64_t nwords = uint64_t(kBatchMaxPhases) * uint64_t(L.grid) * sizeof(GridSync) / sizeof(uint64_t);
     uint64_t *slots = L.partials;
-    uint64_t nslots = uint64_t(kBatchMaxPhases) * uint64_t(L.grid) * 8u;
+    uint64_t nslots = uint64_t(kBatchMaxPhases) * uint64_t(L.grid) * kBatchSlotWords;
     void *ra[] = {&heads, &nheads, &words, &nwords, &slots, &nslots};
     hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(&batch_reset_kernel), dim3(256), dim3(256), ra, 0,
                                    L.stream);

@@ -656,6 +656,10 @@ hipError_t fused_configure(grover_ctx *c, int *per_cu, int *block, int64_t *forc
             budget = state_bytes;  // every access ordinary
     }
     const bool temporal = state_bytes <= budget;
+    // a state that fits on chip does not stream at all, unless the streaming kernel's grid or accesses are forced
+    c->held_team = getenv("GROVER_FUSED_TEMPORAL") || getenv("GROVER_FUSED_GRID")
+                       ? 0u
+                       : chip_team_size(c->dtype, c->accum, c->N / elems_per_vec(c->dtype), c->cu_count);
     const void *k = kernel_for<false>(c->dtype, c->accum, temporal, c->update);
     if (!k)
         return hipErrorInvalidValue;
@@ -693,6 +697,25 @@ uint64_t fused_tiles_of(uint32_t dtype, uint64_t N)
 
 hipError_t launch_fused_external(const FusedExternal &x)
 {
+    if (x.team > 0) {
+        ChipLaunch L;
+        L.state = x.state;
+        L.dtype = x.dtype;
+        L.update = GROVER_UPDATE_F64;
+        L.N = x.N;
+        L.marks = x.marks;
+        L.m = x.m;
+        L.k = x.k;
+        L.team = x.team;
+        L.cu_count = x.cu_count;
+        L.partials = x.slots;
+        L.sync = x.sync;
+        L.gen0 = 0;
+        L.timeout_ticks = x.timeout_ticks;
+        L.probe = false;
+        L.stream = x.stream;
+        return launch_chip(L);
+    }
     const uint64_t state_bytes = x.N * elem_bytes(x.dtype);
     const bool temporal = state_bytes <= kTemporalBytes;
     const void *fn = kernel_for<false>(x.dtype, GROVER_ACC_F64, temporal);
@@ -728,6 +751,8 @@ uint64_t fused_temporal_tiles(const grover_ctx *c)
 
 hipError_t launch_fused_iterate(grover_ctx *c, uint64_t k, uint64_t timeout_ticks, bool check)
 {
+    if (c->held_team > 0)
+        return launch_held_iterate(c, k, timeout_ticks, check);
     FusedArgs a;
     a.state = c->state;
     a.nvec = c->N / elems_per_vec(c->dtype);

@@ -39,154 +39,95 @@ struct C2 {
 __device__ inline C2 cmul(C2 a, C2 b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
 
 struct PhaseShared {
-    double red[kPV * (kStreamBlock / kWave)];
-    double sum[kPV];
+    double red[8 * (kStreamBlock / kWave)];  // wave sums, a row of 16 per value (two groups of four)
+    double sum[8];
     int failed;
 };
 
 struct PhaseTeam {
     PhaseSync *sync;
-    uint64_t *partials;  // [2][size][16]: kPV values as tagged word pairs
+    uint64_t *partials;  // [2][size][16]: kPV values as 16 tagged bytes each
     unsigned size;
     unsigned rank;
     uint64_t timeout_ticks;
 };
 
-// Workgroup sum of v[0 .. kPV): wave butterflies, then thread 0 adds the wave values in wave order.
-__device__ inline void block_sum_n(double (&v)[kPV], PhaseShared &sh)
-{
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
-#pragma unroll
-    for (int q = 0; q < kPV; ++q)
-        v[q] = wave_total(v[q]);
-    if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < kPV; ++q)
-            sh.red[q * (kStreamBlock / kWave) + wave] = v[q];
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int q = 0; q < kPV; ++q) {
-            double s = 0.0;
-            for (int w = 0; w < nw; ++w)
-                s += sh.red[q * (kStreamBlock / kWave) + w];
-            v[q] = s;
-        }
-    }
-    __syncthreads();
-}
-
-// Bounded wait until the first NV values of one member's slot carry generation `tag`, then adds them to w.
-// False when the wait gave up (time limit, or another workgroup gave up).
-template <int NV>
-__device__ inline bool wait_slot_n(const uint64_t *slot, uint32_t tag, const PhaseTeam &tm, double (&w)[kPV])
-{
-    const uint64_t t0 = wall_clock64();
-    uint64_t hi[NV], lo[NV];
-    for (;;) {
-        bool ready = true;
-#pragma unroll
-        for (int q = 0; q < NV; ++q)
-            ready = tagged_ready(slot + 2 * q, tag, hi[q], lo[q]) && ready;
-        if (ready)
-            break;
-        if (__hip_atomic_load(&tm.sync->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
-            return false;
-        if (uint64_t(wall_clock64()) - t0 > tm.timeout_ticks) {
-            __hip_atomic_store(&tm.sync->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return false;
-        }
-        __builtin_amdgcn_s_sleep(1);
-    }
-#pragma unroll
-    for (int q = 0; q < NV; ++q)
-        w[q] += tagged_value(hi[q], lo[q]);
-    return true;
-}
-
 // Team-wide sum of v[0 .. NV) (the other entries are left as they are), an all-gather as in the batched
-// kernels' barrier: every member publishes its partials in its slot of the generation's parity as tagged
-// words (two per value, each carrying the generation; see put_tagged); in every member the slots are
-// awaited in parallel, one member per thread, until all of a member's words carry this generation, and the
-// partials are added by a fixed tree, so all members compute identical sums.  Slots are double-buffered by
-// parity (a slot is rewritten two generations later, after every member has read it).  Every thread gets
-// the sums; false when the wait gave up.  Each value costs two more words to publish and to poll, so
-// callers pass only the values the next step needs.  A member's partial: wave totals, then lane q of wave 0
-// adds value q's 16 wave values by a tree and publishes it (the values in parallel).  For T <= 256 the
-// gather is done by wave 0 alone (lane l adds members l, l + 64, ... in order) and the lanes' sums are added
-// by wave totals (the same bits in every lane and member), so the barrier costs two workgroup barriers;
-// LDS words are written again only after the first barrier of the next call, which every thread reaches
-// after reading them.
+// kernels' barrier (team_sum): every member publishes its partials in its slot of the generation's parity, 16
+// tagged bytes per value; in every member wave 0 awaits the members' values and adds them in a fixed order, so
+// all members compute identical sums.  Slots are double-buffered by parity (a slot is rewritten two generations
+// later, after every member has read it).  Every thread gets the sums; false when the wait gave up.
+//
+// The values travel four at a time through a wave's rows of 16 lanes: a wave's four sums take one fold and four
+// row shifts together, the workgroup's 16 wave values of a value lie in one row, and a row gathers one value of
+// the members, 16 at a time and four of those together.  LDS words are written again only after the first
+// workgroup barrier of the next call, which every thread reaches after reading them.
 template <int NV = kPV>
 __device__ bool team_sum_n(double (&v)[kPV], const PhaseTeam &tm, uint64_t gen, PhaseShared &sh)
 {
-    static_assert(NV >= 1 && NV <= kPV, "values per barrier");
+    static_assert(NV >= 1 && NV <= kPV && kPV <= 8, "values per barrier");
+    constexpr int kGroups = (NV + 3) / 4;
     constexpr unsigned kW = kStreamBlock / kWave;
+    static_assert(kW == 16, "a row per value");
     const uint32_t tag = uint32_t(gen);
-    uint64_t *slots = tm.partials + uint64_t(gen & 1u) * tm.size * 16u;
     const unsigned lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const unsigned row = lane / 16u, in_row = lane % 16u;
+    // the value of a row within its group of four (fold_quad's order)
+    const unsigned of_row = (row & 1u) * 2u + (row >> 1);
 #pragma unroll
-    for (int q = 0; q < NV; ++q)
-        v[q] = wave_total(v[q]);
-    if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < NV; ++q)
-            sh.red[q * kW + wave] = v[q];
+    for (int g = 0; g < kGroups; ++g) {
+        auto val = [&](int q) { return 4 * g + q < NV ? v[4 * g + q < kPV ? 4 * g + q : 0] : 0.0; };
+        const double t = row_totals(fold_quad(val(0), val(1), val(2), val(3)));
+        if (in_row == 15u)
+            sh.red[(4u * g + of_row) * kW + wave] = t;
     }
     __syncthreads();
-    if (wave == 0 && lane < unsigned(NV)) {
-        double r[kW];
+    if (wave == 0) {
+        const auto slots = buffer_rsrc(tm.partials + uint64_t(gen & 1u) * tm.size * 16u, tm.size * 128u);
+        bool ok = true;
 #pragma unroll
-        for (unsigned w = 0; w < kW; ++w)
-            r[w] = sh.red[lane * kW + w];
-#pragma unroll
-        for (unsigned h = 1; h < kW; h *= 2)
-#pragma unroll
-            for (unsigned w = 0; w < kW; w += 2 * h)
-                r[w] += r[w + h];
-        put_tagged(slots + uint64_t(tm.rank) * 16u + 2 * lane, r[0], tag);
-    }
-    if (tm.size <= 4u * kWave) {
-        if (wave == 0) {
-            double w[kPV] = {};
-            bool ok = true;
-            for (unsigned r = lane; r < tm.size && ok; r += kWave)  // members lane, lane + 64, ... in order
-                ok = wait_slot_n<NV>(slots + uint64_t(r) * 16u, tag, tm, w);
-#pragma unroll
-            for (int q = 0; q < NV; ++q)
-                w[q] = wave_total(w[q]);
-            const bool failed = __any(!ok);
-            if (lane == 0) {
-#pragma unroll
-                for (int q = 0; q < NV; ++q)
-                    sh.sum[q] = w[q];
-                sh.failed = failed;
-            }
+        for (int g = 0; g < kGroups; ++g) {
+            const unsigned q = 4u * g + of_row;
+            const double t = row_totals(sh.red[q * kW + in_row]);
+            if (in_row == 15u && q < unsigned(NV))
+                put_value(slots, tm.rank * 128u + q * 16u, t, tag);
         }
-        __syncthreads();
 #pragma unroll
-        for (int q = 0; q < NV; ++q)
-            v[q] = sh.sum[q];
-        return sh.failed == 0;
-    }
-    double w[kPV] = {};
-    bool ok = true;
-    for (unsigned r = threadIdx.x; r < tm.size && ok; r += kStreamBlock)
-        ok = wait_slot_n<NV>(slots + uint64_t(r) * 16u, tag, tm, w);
-    const bool failed = __syncthreads_or(!ok) != 0;
-    block_sum_n(w, sh);
-    if (threadIdx.x == 0) {
+        for (int g = 0; g < kGroups; ++g) {
+            const unsigned q = 4u * g + of_row;
+            double w = 0.0;
+            for (unsigned m = in_row; m < tm.size && ok; m += 64u) {
+                // members m, m + 16, m + 32, m + 48: a team's size is mostly a power of two
+                double x[4] = {0.0, 0.0, 0.0, 0.0};
+                if (q < unsigned(NV)) {
+                    if (m + 48u < tm.size) {
+                        ok = wait_values<4>(slots, m * 128u + q * 16u, 16u * 128u, tag, &tm.sync->error, tm.timeout_ticks, x);
+                    } else {
 #pragma unroll
-        for (int q = 0; q < NV; ++q)
-            sh.sum[q] = w[q];
+                        for (unsigned i = 0; i < 3u; ++i) {
+                            double y[1] = {0.0};
+                            if (ok && m + 16u * i < tm.size)
+                                ok = wait_values<1>(slots, (m + 16u * i) * 128u + q * 16u, 0u, tag, &tm.sync->error,
+                                                    tm.timeout_ticks, y);
+                            x[i] = y[0];
+                        }
+                    }
+                }
+                w += (x[0] + x[1]) + (x[2] + x[3]);
+            }
+            w = row_totals(w);
+            if (in_row == 15u && q < unsigned(NV))
+                sh.sum[q] = w;
+        }
+        const bool failed = __any(!ok);
+        if (lane == 0)
+            sh.failed = failed;
     }
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < NV; ++q)
         v[q] = sh.sum[q];
-    __syncthreads();  // sh.sum is rewritten by the next call before its first barrier on this path
-    return !failed;
+    return sh.failed == 0;
 }
 
 struct PhaseArgs {
@@ -321,10 +262,10 @@ __global__ __launch_bounds__(kStreamBlock) void phase_forward_kernel(PhaseArgs a
 {
     __shared__ PhaseShared sh;
     __shared__ uint32_t table[kMarkWords];
-    const unsigned T = a.team_size, teams = gridDim.x / T, team_id = blockIdx.x / T;
+    const unsigned T = a.team_size, teams = gridDim.x / T, team_id = xcd_major_block() / T;
     if (team_id >= teams)
         return;
-    const PhaseTeam tm{a.sync + team_id, a.partials + uint64_t(team_id) * 32u * T, T, blockIdx.x % T,
+    const PhaseTeam tm{a.sync + team_id, a.partials + uint64_t(team_id) * 32u * T, T, xcd_major_block() % T,
                        a.timeout_ticks};
     uint64_t gen = 0;
     if (a.probe) {
@@ -475,10 +416,10 @@ __global__ __launch_bounds__(kStreamBlock) void phase_adjoint_kernel(PhaseArgs a
 {
     __shared__ PhaseShared sh;
     __shared__ uint32_t table[kMarkWords];
-    const unsigned T = a.team_size, teams = gridDim.x / T, team_id = blockIdx.x / T;
+    const unsigned T = a.team_size, teams = gridDim.x / T, team_id = xcd_major_block() / T;
     if (team_id >= teams)
         return;
-    const PhaseTeam tm{a.sync + team_id, a.partials + uint64_t(team_id) * 32u * T, T, blockIdx.x % T,
+    const PhaseTeam tm{a.sync + team_id, a.partials + uint64_t(team_id) * 32u * T, T, xcd_major_block() % T,
                        a.timeout_ticks};
     uint64_t gen = 0;
     if (a.probe) {
@@ -654,10 +595,10 @@ __global__ __launch_bounds__(kStreamBlock) void phase_forward_held_kernel(PhaseA
     __shared__ PhaseShared sh;
     __shared__ float4 held[kHeldLds * kStreamBlock];
     __shared__ TrigTable trig;
-    const unsigned T = a.team_size, teams = gridDim.x / T, team_id = blockIdx.x / T;
+    const unsigned T = a.team_size, teams = gridDim.x / T, team_id = xcd_major_block() / T;
     if (team_id >= teams)
         return;
-    const PhaseTeam tm{a.sync + team_id, a.partials + uint64_t(team_id) * 32u * T, T, blockIdx.x % T,
+    const PhaseTeam tm{a.sync + team_id, a.partials + uint64_t(team_id) * 32u * T, T, xcd_major_block() % T,
                        a.timeout_ticks};
     uint64_t gen = 0;
     if (a.probe) {
@@ -812,10 +753,10 @@ __global__ __launch_bounds__(kStreamBlock) void phase_adjoint_held_kernel(PhaseA
     __shared__ PhaseShared sh;
     __shared__ float4 held[kHeldLds * kStreamBlock];  // the adjoint state
     __shared__ TrigTable trig;
-    const unsigned T = a.team_size, teams = gridDim.x / T, team_id = blockIdx.x / T;
+    const unsigned T = a.team_size, teams = gridDim.x / T, team_id = xcd_major_block() / T;
     if (team_id >= teams)
         return;
-    const PhaseTeam tm{a.sync + team_id, a.partials + uint64_t(team_id) * 32u * T, T, blockIdx.x % T,
+    const PhaseTeam tm{a.sync + team_id, a.partials + uint64_t(team_id) * 32u * T, T, xcd_major_block() % T,
                        a.timeout_ticks};
     uint64_t gen = 0;
     if (a.probe) {

@@ -1,4 +1,4 @@
-// Device code shared by the batched and the phase kernels: the team barrier that also reduces the
+// Device code shared by the held, batched and phase kernels: the team barrier that also reduces the
 // iteration's sum, the marked-tile table, and one streaming pass of a team's share of a state.  A "team"
 // is T workgroups of one launch (rank 0 .. T-1) that iterate one state together.  The single-state fused
 // kernel keeps its own copy of the same pass and barrier specialised to the whole grid: written against
@@ -16,39 +16,16 @@ constexpr int kStreamTile = kStreamBlock * kStreamUnroll;
 constexpr int kMarkWords = 1024;    // LDS bitmap of a workgroup's tiles that hold marked amplitudes
 constexpr int kTileMarks = 8;       // marks of one tile held in registers
 
-template <class V>
+// LDS of a workgroup's part in a team barrier (B threads).
+template <int B>
 struct TeamShared {
-    V red[2][2 * (kStreamBlock / kWave)];  // per-wave partials, double-buffered (see block_allsum)
-    V sum[2];
+    double red[2][2 * (B / kWave)];  // wave sums of re, then of im; block_allsum alternates the two sets
+    double sum[2];
     int failed;
 };
 
-// The 16 wave values of a 1024-thread workgroup, (re, im) interleaved in red[0 .. 32), added as a balanced
-// tree (four levels of dependent additions instead of fifteen).
-template <class V>
-__device__ inline void add_wave_values(const V *red, V &sr, V &si)
-{
-    V r[kStreamBlock / kWave], i[kStreamBlock / kWave];
-#pragma unroll
-    for (unsigned w = 0; w < kStreamBlock / kWave; ++w) {
-        r[w] = red[2 * w];
-        i[w] = red[2 * w + 1];
-    }
-#pragma unroll
-    for (unsigned h = 1; h < kStreamBlock / kWave; h *= 2) {
-#pragma unroll
-        for (unsigned w = 0; w < kStreamBlock / kWave; w += 2 * h) {
-            r[w] += r[w + h];
-            i[w] += i[w + h];
-        }
-    }
-    sr = r[0];
-    si = i[0];
-}
-
-// Where a team's barrier lives: its error word (GridSync), its member slots [2][T][4] (the member's partial
-// sum as tagged words, see put_tagged; double-buffered by the generation's parity), the number of
-// workgroups T, this workgroup's rank, and the wait limit.
+// Where a team's barrier lives: its error word (GridSync), its member slots (team_words() 64-bit words: two
+// sets by the generation's parity), the number of workgroups T, this workgroup's rank, and the wait limit.
 struct Team {
     GridSync *sync;
     uint64_t *partials;
@@ -57,194 +34,197 @@ struct Team {
     uint64_t timeout_ticks;
 };
 
-__device__ inline uint64_t load_bits(const uint64_t *p)
+// A binary64 value travels as 16 bytes {tag, high, tag, low}: two self-validating 64-bit words, each carrying
+// 32 bits of the value and the barrier generation (mod 2^32).  A reader that sees the current tag in both has
+// both halves of this generation's value, and no memory fence (which on this GPU writes back or invalidates a
+// whole L2) is needed to order the value against a separate flag.  Slots are zeroed before a launch and
+// generations start at 1.  Device-scope (sc1) 16-byte buffer accesses; the loads are volatile.
+constexpr int kBufDevice = 16;                            // sc1
+constexpr int kBufDeviceVolatile = 16 | int(0x80000000);  // sc1, and never hoisted or merged by the compiler
+
+__device__ inline void put_value(__amdgpu_buffer_rsrc_t slots, uint32_t off, double x, uint32_t tag)
 {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    u32x4 w;
+    w.x = tag;
+    w.y = unsigned(b >> 32);
+    w.z = tag;
+    w.w = unsigned(b);
+    __builtin_amdgcn_raw_buffer_store_b128(w, slots, off, 0, kBufDevice);
 }
 
-__device__ inline void store_bits(uint64_t *p, double x)
-{
-    __hip_atomic_store(p, (uint64_t)__double_as_longlong(x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// A binary64 value published as two self-validating 64-bit words: each carries 32 bits of the value in its
-// high half and the barrier generation (mod 2^32) in its low half.  Each word is stored and loaded as one
-// atomic access, so a reader that sees the current tag in both words has both halves of this generation's
-// value, and no memory fence (which on this GPU writes back or invalidates a whole L2) is needed to order
-// the value against a separate flag.  Slots are zeroed before a launch and generations start at 1.
-__device__ inline void put_tagged(uint64_t *w, double x, uint32_t tag)
-{
-    const uint64_t b = (uint64_t)__double_as_longlong(x);
-    __hip_atomic_store(w, (b & 0xFFFFFFFF00000000ull) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(w + 1, (b << 32) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ inline bool tagged_ready(const uint64_t *w, uint32_t tag, uint64_t &hi, uint64_t &lo)
-{
-    hi = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    lo = __hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return uint32_t(hi) == tag && uint32_t(lo) == tag;
-}
-
-__device__ inline double tagged_value(uint64_t hi, uint64_t lo)
-{
-    return __longlong_as_double((long long)((hi & 0xFFFFFFFF00000000ull) | (lo >> 32)));
-}
-
-// Bounded wait for the two values (tagged words w[0..3]) of generation `tag`, giving up when the team's
-// error word is set or the wall-clock limit passes (then setting the error word).
-__device__ inline bool wait_pair(const uint64_t *w, uint32_t tag, const Team &tm, double &a, double &b)
+// Bounded wait for NV values of generation `tag`, value q at byte offset off + q * stride: the loads of a
+// round are issued together.  Gives up when the error word is set or the wall-clock limit passes (then
+// setting the error word); both are looked at in the first and every 16th unsuccessful round only.
+template <int NV>
+__device__ inline bool wait_values(__amdgpu_buffer_rsrc_t slots, uint32_t off, uint32_t stride, uint32_t tag,
+                                   uint32_t *error, uint64_t timeout_ticks, double (&x)[NV])
 {
     const uint64_t t0 = wall_clock64();
-    uint64_t h0, l0, h1, l1;
-    for (;;) {
-        const bool ra = tagged_ready(w, tag, h0, l0);
-        const bool rb = tagged_ready(w + 2, tag, h1, l1);
-        if (ra && rb)
+    u32x4 w[NV];
+    for (unsigned round = 0;; ++round) {
+        bool ready = true;
+#pragma unroll
+        for (int q = 0; q < NV; ++q)
+            w[q] = __builtin_amdgcn_raw_buffer_load_b128(slots, off + uint32_t(q) * stride, 0, kBufDeviceVolatile);
+#pragma unroll
+        for (int q = 0; q < NV; ++q)
+            ready = ready && w[q].x == tag && w[q].z == tag;
+        if (ready)
             break;
-        if (__hip_atomic_load(&tm.sync->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
-            return false;
-        if (uint64_t(wall_clock64()) - t0 > tm.timeout_ticks) {
-            __hip_atomic_store(&tm.sync->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return false;
+        if ((round & 15u) == 0u) {
+            if (__hip_atomic_load(error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
+                return false;
+            if (uint64_t(wall_clock64()) - t0 > timeout_ticks) {
+                __hip_atomic_store(error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return false;
+            }
         }
-        __builtin_amdgcn_s_sleep(1);
     }
-    a = tagged_value(h0, l0);
-    b = tagged_value(h1, l1);
+#pragma unroll
+    for (int q = 0; q < NV; ++q)
+        x[q] = __longlong_as_double((long long)(((unsigned long long)w[q].y << 32) | w[q].w));
     return true;
 }
 
-// Bounded wait for the value pairs of up to four slots w + 4 kWave i (i < cnt, slot i of a lane that gathers
-// members lane + kWave i), polled together so that the wait ends one memory round trip after the last of
-// them is published instead of one round trip per slot; same limits as wait_pair.
-__device__ inline bool wait_pairs4(const uint64_t *w, unsigned cnt, uint32_t tag, const Team &tm, double (&a)[4],
-                                   double (&b)[4])
+// Adds the wave values that `red` holds (re of waves 0 .. W-1, then im): lane W - 1 gets the sum of re, lane
+// 2 W - 1 that of im.  Called by one whole wave.
+template <int B>
+__device__ inline double add_wave_values(const double *red)
 {
-    const uint64_t t0 = wall_clock64();
-    const unsigned all = (1u << cnt) - 1u;
-    unsigned done = 0u;  // bit i: slot i read
-    for (;;) {
-#pragma unroll
-        for (unsigned i = 0; i < 4u; ++i) {
-            if (i < cnt && ((done >> i) & 1u) == 0u) {
-                const uint64_t *slot = w + uint64_t(i) * kWave * 4u;
-                uint64_t h0, l0, h1, l1;
-                const bool ra = tagged_ready(slot, tag, h0, l0);
-                const bool rb = tagged_ready(slot + 2, tag, h1, l1);
-                if (ra && rb) {
-                    a[i] = tagged_value(h0, l0);
-                    b[i] = tagged_value(h1, l1);
-                    done |= 1u << i;
-                }
-            }
-        }
-        if (done == all)
-            return true;
-        if (__hip_atomic_load(&tm.sync->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
-            return false;
-        if (uint64_t(wall_clock64()) - t0 > tm.timeout_ticks) {
-            __hip_atomic_store(&tm.sync->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return false;
-        }
-        __builtin_amdgcn_s_sleep(1);
-    }
+    constexpr unsigned W = B / kWave;
+    const unsigned lane = threadIdx.x % kWave;
+    double p = lane < 2 * W ? red[lane] : 0.0;
+    if (W > 1)
+        p += dpp_row_shifted<0x111>(p);
+    if (W > 2)
+        p += dpp_row_shifted<0x112>(p);
+    if (W > 4)
+        p += dpp_row_shifted<0x114>(p);
+    if (W > 8)
+        p += dpp_row_shifted<0x118>(p);
+    return p;
+}
+
+// Each wave's sums of (re, im) into red.
+template <int B>
+__device__ inline void put_wave_values(double xr, double xi, double *red)
+{
+    const unsigned lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const double v = half_totals(fold_pair(xr, xi));
+    if (lane == 31)
+        red[wave] = v;
+    if (lane == 63)
+        red[B / kWave + wave] = v;
+}
+
+// Workgroup sum of (a, b) for every thread with one workgroup barrier: wave sums, then every wave adds the
+// wave values by the same fixed tree (the same bits everywhere).  The wave values alternate between two sets
+// by `parity`: a set is rewritten two calls later, after the next call's barrier, which every thread reaches
+// only after reading it.
+template <int B>
+__device__ inline void block_allsum(double &a, double &b, unsigned parity, TeamShared<B> &sh)
+{
+    double *red = sh.red[parity & 1u];
+    put_wave_values<B>(a, b, red);
+    __syncthreads();
+    const double p = add_wave_values<B>(red);
+    a = lane_value(p, B / kWave - 1);
+    b = lane_value(p, 2 * (B / kWave) - 1);
 }
 
 // Team-wide sum of (xr, xi) at barrier generation `gen` (1, 2, ... per barrier object; slots zeroed before
-// the launch), in the arithmetic of V (binary64 or binary32; partials travel as binary64, which holds a
-// binary32 exactly).  Returns false when the wait gave up (time limit, or another workgroup gave up); every
-// thread of the workgroup gets the same answer and the sum in (xr, xi).
+// the launch).  Returns false when the wait gave up (time limit, or another workgroup gave up); every thread
+// of the workgroup gets the same answer and the sum in (xr, xi).
 //
-// An all-gather: every member publishes its partial in its own slot of the generation's parity as tagged
-// words; then, in every member, wave 0 waits for the members' words of this generation (lane l for members
-// l, l + 64, ...; in teams of more than 256 one thread per member) and the partials are added in a fixed
-// order, so every member computes the same sum bit for bit after one memory round trip.  A member rewrites a slot of parity p only at generation g + 2:
-// its partial for g + 1 depends on the sum of g, so its reads of generation g have returned before it
-// publishes g + 1, and g + 2 follows only after every member's g + 1 has been seen.  (Arrivals counted
-// with one atomic per member serialise at the counter's address, and a gather to one member followed by a
-// broadcast costs two round trips.)  The team's workgroups share no other memory within a launch, so the
-// barrier orders nothing but these values.
-template <class V, bool kTogether = false>
-__device__ bool team_sum(V &xr, V &xi, const Team &tm, uint64_t gen, TeamShared<V> &sh)
+// An all-gather: every member publishes its partial in its own slot of the generation's parity; then, in every
+// member, wave 0 waits for the members' values of this generation and adds them in a fixed order, so every
+// member computes the same sum bit for bit after one memory round trip.  A member rewrites a slot of parity p
+// only at generation g + 2: its partial for g + 1 depends on the sum of g, so its reads of generation g have
+// returned before it publishes g + 1, and g + 2 follows only after every member's g + 1 has been seen.
+// (Arrivals counted with one atomic per member serialise at the counter's address.)  The team's workgroups
+// share no other memory within a launch, so the barrier orders nothing but these values.
+//
+// What bounds it is latency: 0.3 us for the workgroup's own sum and hand-out (512 threads), the rest the store
+// and the load that first sees it.  Bare barriers on MI355X (blocks go round the 8 XCDs, so a team of
+// consecutive blocks spans them all), this form against the one before it (two 8-byte words per value at 32
+// bytes per member, lane-read wave totals, sleeping polls; 1024 threads): T = 32 1.55 / 2.52 us, T = 64 1.65 /
+// 2.67, T = 128 1.98 / 3.22, T = 256 2.05 / 3.73.  Slots 64 bytes apart: at 32, four members' stores land on
+// one line that every XCD polls (T = 64 1.88 us).  A team inside one half of the XCDs saves the trip between
+// the halves: T = 64 1.36 us, T = 32 1.20.  Above 128 members two levels are faster than one wave's four
+// polls per lane (T = 256 2.70 us): members of equal rank % 8 (one XCD when ranks are block numbers)
+// meet at the first of them, which publishes their sum, and every member adds the 8 group sums.
+template <int B>
+__device__ bool team_sum(double &xr, double &xi, const Team &tm, uint64_t gen, TeamShared<B> &sh)
 {
+    constexpr unsigned W = B / kWave;
     const uint32_t tag = uint32_t(gen);
-    uint64_t *slots = tm.partials + uint64_t(gen & 1u) * tm.size * 4u;
     const unsigned lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    // this member's partial: wave totals, then thread 0 adds the wave values by a fixed tree and publishes
-    // it.  sh.red[0] is read by thread 0 only before the workgroup barrier below; a wave writes it again
-    // only in the next call, after that barrier, so no barrier is needed behind the read.
-    xr = wave_total(xr);
-    xi = wave_total(xi);
-    if (lane == 0) {
-        sh.red[0][2 * wave] = xr;
-        sh.red[0][2 * wave + 1] = xi;
-    }
+    // sh.red[0] is read by wave 0 only between the two workgroup barriers below; a wave writes it again only
+    // in the next call, after the second.  sh.sum and sh.failed are written again only after the first barrier
+    // of the next call, which every thread reaches after reading them here.
+    put_wave_values<B>(xr, xi, sh.red[0]);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        V sr, si;
-        add_wave_values(sh.red[0], sr, si);
-        uint64_t *slot = slots + uint64_t(tm.rank) * 4u;
-        put_tagged(slot, double(sr), tag);
-        put_tagged(slot + 2, double(si), tag);
-    }
-    if (tm.size <= 4u * kWave) {
-        // wave 0 gathers the members' partials (lane l waits for members l, l + 64, ... and adds them in that
-        // order) and adds the lanes' values with wave_total, which leaves the same bits in every lane and in
-        // every member; one workgroup barrier hands the sum on.  sh.sum and sh.failed are written again only
-        // after the first barrier of the next call, which every thread reaches after reading them here.
-        if (wave == 0) {
-            V ar = V(0), ai = V(0);
-            bool ok = true;
-            if (kTogether && tm.size > kWave) {
-                // 2 to 4 members per lane, waited for together and added in member order
-                const unsigned cnt = lane < tm.size ? (tm.size - lane + kWave - 1u) / kWave : 0u;
-                double a[4], b[4];
-                ok = wait_pairs4(slots + uint64_t(lane) * 4u, cnt, tag, tm, a, b);
-                for (unsigned i = 0; i < cnt && ok; ++i) {
-                    ar += V(a[i]);
-                    ai += V(b[i]);
-                }
-            } else {
-                for (unsigned w = lane; w < tm.size && ok; w += kWave) {
-                    double a = 0.0, b = 0.0;
-                    ok = wait_pair(slots + uint64_t(w) * 4u, tag, tm, a, b);
-                    ar += V(a);
-                    ai += V(b);
-                }
+    if (wave == 0) {
+        const unsigned stride = team_stride(tm.size);
+        const bool two = team_two_level(tm.size);
+        const unsigned part = (lane >> 5) * 16u;  // lanes 32 .. 63 handle im
+        const unsigned groups = 8u, per_group = tm.size / groups;
+        const unsigned pos = two ? (tm.rank % groups) * per_group + tm.rank / groups : tm.rank;
+        uint64_t *set = tm.partials + uint64_t(gen & 1u) * tm.size * (stride / 8u);
+        const auto slots = buffer_rsrc(set, tm.size * stride);
+        const double p = add_wave_values<B>(sh.red[0]);
+        if (lane == W - 1u || lane == 2u * W - 1u)
+            put_value(slots, pos * stride + (lane == W - 1u ? 0u : 16u), p, tag);
+        double v = 0.0;
+        bool ok = true;
+        if (two) {
+            const auto sums = buffer_rsrc(tm.partials + 2u * tm.size * (stride / 8u) + uint64_t(gen & 1u) * groups * kGroupWords,
+                                          groups * uint32_t(kGroupWords) * 8u);
+            const unsigned m = lane & 31u;
+            double x[1] = {0.0};
+            if (tm.rank < groups) {  // the group's first member; per_group <= 32
+                if (m < per_group)
+                    ok = wait_values<1>(slots, (pos + m) * stride + part, 0u, tag, &tm.sync->error, tm.timeout_ticks, x);
+                const double g = half_totals(x[0]);
+                const bool all_ok = __all(ok);
+                if (m == 31u && all_ok)
+                    put_value(sums, tm.rank * uint32_t(kGroupWords) * 8u + part, g, tag);
+                x[0] = 0.0;
             }
-            const V pr = wave_total(ar), pi = wave_total(ai);
-            const bool failed = __any(!ok);
-            if (lane == 0) {
-                sh.sum[0] = pr;
-                sh.sum[1] = pi;
-                sh.failed = failed;
+            if (ok && m < groups)
+                ok = wait_values<1>(sums, m * uint32_t(kGroupWords) * 8u + part, 0u, tag, &tm.sync->error,
+                                    tm.timeout_ticks, x);
+            v = x[0];
+        } else if (tm.size <= 32u) {
+            const unsigned m = lane & 31u;
+            double x[1] = {0.0};
+            if (m < tm.size)
+                ok = wait_values<1>(slots, m * stride + part, 0u, tag, &tm.sync->error, tm.timeout_ticks, x);
+            v = x[0];
+        } else {
+            double ar = 0.0, ai = 0.0;
+            for (unsigned m = lane; m < tm.size && ok; m += kWave) {
+                double x[2] = {0.0, 0.0};
+                ok = wait_values<2>(slots, m * stride, 16u, tag, &tm.sync->error, tm.timeout_ticks, x);
+                ar += x[0];
+                ai += x[1];
             }
+            v = fold_pair(ar, ai);
         }
-        __syncthreads();
-        xr = sh.sum[0];
-        xi = sh.sum[1];
-        return !sh.failed;
-    }
-    V pr = V(0), pi = V(0);
-    bool ok = true;
-    for (unsigned w = threadIdx.x; w < tm.size; w += kStreamBlock) {
-        double a = 0.0, b = 0.0;
-        ok = ok && wait_pair(slots + uint64_t(w) * 4u, tag, tm, a, b);
-        pr += V(a);
-        pi += V(b);
-    }
-    const bool failed = __syncthreads_or(!ok) != 0;
-    block_sum2(pr, pi, sh.red[1]);
-    if (threadIdx.x == 0) {
-        sh.sum[0] = pr;
-        sh.sum[1] = pi;
+        v = half_totals(v);
+        const bool failed = __any(!ok);
+        if (lane == 31u)
+            sh.sum[0] = v;
+        if (lane == 63u)
+            sh.sum[1] = v;
+        if (lane == 0u)
+            sh.failed = failed;
     }
     __syncthreads();
     xr = sh.sum[0];
     xi = sh.sum[1];
-    __syncthreads();  // sh.sum is rewritten by the next call before its first barrier on this path
-    return !failed;
+    return !sh.failed;
 }
 
 // First index q >= start with marks[q] >= x in the sorted list marks[0, m), given that every entry before
