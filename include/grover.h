@@ -273,12 +273,11 @@ int grover_iterate_static(void *hip_stream, void *state_dev, uint32_t n, uint32_
  * indices and iterations[i] iterations (k_opt(n[i], m[i]) when `iterations` is NULL).
  *
  * How the device divides the work is the tiling (split_n, team, resident):
- *   - states of 2^n <= 32768 amplitudes are iterated by one workgroup each, held on chip (16 16-byte
- *     vectors per thread: 8 in registers, 8 in LDS);
+ *   - states of 2^n <= 32768 amplitudes are iterated by one workgroup each (512 threads), held on chip (up to
+ *     32 16-byte vectors per thread, in registers);
  *   - with resident = r in {1, 2, 4, 8, 16}, a larger state is held on chip by a team of T workgroups,
- *     T the power of two >= 2^n / (2048 r) (r 16-byte vectors per thread, the first 8 in registers, the
- *     rest in LDS), when T does not exceed the grid: one team barrier per iteration and no memory traffic
- *     until the final write;
+ *     T the power of two >= 2^n / (2048 r) (at most 2 r 16-byte vectors per thread, in registers), when T does
+ *     not exceed the grid: one team barrier per iteration and no memory traffic until the final write;
  *   - the remaining states stream from memory every iteration: those with n >= split_n by teams of `team`
  *     workgroups each (team = grid size: the whole device per instance), the others one per workgroup.
  * The tiling changes the order of additions in the sums, so results of two tilings agree to rounding, and

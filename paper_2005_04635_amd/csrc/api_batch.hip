@@ -170,7 +170,7 @@ int apply_tiling(grover_batch *b, uint32_t split_n, uint32_t team_size, uint32_t
     uint64_t n_team = 0;
     for (uint32_t i : order) {
         const uint64_t nvec = b->nvec[i];
-        if (nvec <= uint64_t(kBatchHoldE) * 1024u) {
+        if (nvec <= kBatchAloneVecs) {
             phase_of(1, 0).push_back(i);
             continue;
         }
@@ -220,7 +220,7 @@ int apply_tiling(grover_batch *b, uint32_t split_n, uint32_t team_size, uint32_t
             streams = 1;
         if (phases[p].first.first == 1)
             for (uint32_t i : phases[p].second)
-                if (b->nvec[i] > uint64_t(kBatchHoldE) * 1024u)
+                if (b->nvec[i] > kBatchAloneVecs)
                     streams = 1;
     }
     b->streams = streams;
@@ -245,9 +245,9 @@ int select_grid(grover_batch *b, int clock_khz)
     int per_cu = 0;
     int per_cu_held = 0;
     const bool u32 = b->update == GROVER_UPDATE_F32;
-    BATCH_HIP(b, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_kernel_fn(true, u32), 1024, 0),
+    BATCH_HIP(b, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_kernel_fn(true, u32), kBatchBlock, 0),
               "occupancy");
-    BATCH_HIP(b, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_held, batch_kernel_fn(false, u32), 1024, 0),
+    BATCH_HIP(b, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_held, batch_kernel_fn(false, u32), kBatchBlock, 0),
               "occupancy");
     per_cu = std::min(per_cu, per_cu_held);
     const int max_grid = std::max(1, per_cu) * b->cu_count;
@@ -433,8 +433,7 @@ int grover_batch_init(grover_batch **out, const grover_batch_config *cfg, void *
         status = select_grid(b, clock_khz);
         if (status != GROVER_OK)
             throw status;
-        // default tiling until tuned: states held on chip by teams sized for 16 vectors per thread (8 in
-        // registers, 8 in LDS); states too large for that stream with teams of 2
+        // default tiling until tuned: states held on chip by teams sized for 16 vectors per thread; states too large for that stream with teams of 2
         status = apply_tiling(b, 19, b->grid >= 2 ? 2u : 1u, uint32_t(kBatchHoldE));
         if (status != GROVER_OK)
             throw status;

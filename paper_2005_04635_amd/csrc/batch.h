@@ -7,9 +7,9 @@ namespace grover {
 
 constexpr int kBatchMaxPhases = 12;
 constexpr uint64_t kBatchSlotWords = 16;  // barrier slot words per workgroup of the grid and phase
-constexpr int kBatchRegE = 8;                         // 16-byte vectors a thread holds in registers
-constexpr int kBatchLdsE = 8;                         // ... and in its own slots of LDS (128 KiB per workgroup)
-constexpr int kBatchHoldE = kBatchRegE + kBatchLdsE;  // 16 vectors = 32 complex64 amplitudes per thread
+constexpr int kBatchBlock = 512;  // threads per workgroup, one workgroup per CU
+constexpr int kBatchHoldE = 16;   // largest `resident`: 16-byte vectors per 1024 threads' worth of a member, 32 per thread
+constexpr uint64_t kBatchAloneVecs = uint64_t(kBatchHoldE) * 1024u;  // largest state one workgroup holds alone (n = 15)
 
 // One instance of a batch (device table, written by the host).
 struct BatchInstance {
@@ -25,9 +25,9 @@ struct BatchInstance {
 // A run is a sequence of phases.  Phase p has a queue of instances (ordered by decreasing work), a team
 // size team[p] (workgroups per instance; non-increasing from one phase to the next, each a divisor of the
 // previous one, so a team of phase p + 1 lies inside one team of phase p) and a mode: resident[p] > 0 holds
-// each instance's state on chip in the team's workgroups (at most that many 16-byte vectors per thread, the
-// first kBatchRegE in registers, the rest in LDS), 0 streams it from memory every iteration.  Team size 1 is
-// one workgroup per instance (on chip when the state fits kBatchHoldE vectors per thread, else streamed).
+// each instance's state on chip in the team's workgroups (at most 1024 times that many 16-byte vectors per
+// member, in registers), 0 streams it from memory every iteration.  Team size 1 is one workgroup per instance (on chip up
+// to kBatchAloneVecs, else streamed).
 struct BatchLaunch {
     void *state;
     const uint64_t *marks;

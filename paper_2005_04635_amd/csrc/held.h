@@ -1,127 +1,267 @@
-// Device code for states held on chip by a team of workgroups for all iterations (the batched kernel's
-// resident phases): one iteration's update of a thread's held vectors and the handling of the marked
-// amplitudes around it.  Thread tid of a member holds its vectors
-// e * 1024 + tid, e < ne: the first kHeldRegE in registers (x[e]), the others in its own slots of LDS
-// (held[(e - kHeldRegE) * 1024 + tid]; no other thread touches them, so they need no workgroup barrier).
-// Marked bits travel packed, two per vector (bits 2e, 2e + 1 of `mask` for vector e).
+// Device code for states held on chip by a team of workgroups of B threads for all iterations: the single-state
+// kernel (held form, and fused form on chip) and the batched kernel's resident phases.  Member `rank` owns the
+// contiguous vectors [base, base + per), thread tid the vectors e * B + tid, e < NE = per / B (or the one vector
+// tid < per when per < B): the first RE positions in registers, the others in the thread's own LDS slots (no
+// other thread touches them, so they need no workgroup barrier).  NE and RE are template parameters, so the
+// sweep has no branches.
 #pragma once
+
+#include <type_traits>
 
 #include "stream.h"
 
 namespace grover {
 
-constexpr int kHeldRegE = 8;                       // 16-byte vectors a thread holds in registers
-constexpr int kHeldLdsE = 8;                       // ... and in its own slots of LDS (128 KiB per workgroup)
-constexpr int kHeldHoldE = kHeldRegE + kHeldLdsE;  // 16 vectors = 32 complex64 amplitudes per thread
-
-// Update of one held vector as if it held no marked amplitude (c' = 2S/N - c per amplitude, the stored
-// values accumulated).  Marked amplitudes are handled around the sweep: their stored values are negated
-// before it (exactly), which makes this update produce 2S/N + c, their correct new value bit for bit, and
-// the sum is corrected after it by -2c' per marked amplitude (so it holds s c' for them, as the inversion
-// about the mean needs).  Every thread thus runs the same short update, and the few threads with marks
-// only add a few operations; the slowest wave sets the pace of every iteration.
-__device__ inline void unmarked_update(float4 &v, double mr, double mi, AccF64 &acc)
-{
-    v.x = float(mr - double(v.x));
-    v.y = float(mi - double(v.y));
-    v.z = float(mr - double(v.z));
-    v.w = float(mi - double(v.w));
-    acc.add(double(v.x), double(v.y));
-    acc.add(double(v.z), double(v.w));
-}
-
-// The same update in binary32 from 2S/N rounded to binary32 (mr, mi): one binary32 subtraction per part,
-// where the binary64 form takes a conversion, a binary64 subtraction and a rounding conversion.  A negated
-// marked value gives mr + c, the marked result of fl32(mr - s c), as above.
-__device__ inline void unmarked_update(float4 &v, float mr, float mi, AccF64 &acc)
-{
-    v.x = mr - v.x;
-    v.y = mi - v.y;
-    v.z = mr - v.z;
-    v.w = mi - v.w;
-    acc.add(double(v.x), double(v.y));
-    acc.add(double(v.z), double(v.w));
-}
-
-// Negates the stored values of the marked amplitudes among a thread's held vectors (bits 2e, 2e + 1 of
-// `mask` for vector e).
-__device__ inline void negate_marked(float4 (&x)[kHeldRegE], float4 *held, uint32_t mask)
-{
+// A storage vector as `parts` numbers, part p of amplitude amp(p); imag(p): an imaginary part.  H: the type
+// that a held part has; widen: complex64 parts held as binary64 values that binary32 represents.
+template <class T, bool U32, bool WIDE>
+struct Held {
+    static constexpr int parts = T::EPV * (T::kComplex ? 2 : 1);
+    using H = typename std::conditional<std::is_same<T, C64>::value && !WIDE, float, double>::type;
+    __device__ static constexpr int amp(int p) { return T::kComplex ? p / 2 : p; }
+    __device__ static constexpr bool imag(int p) { return T::kComplex && (p & 1); }
+    // one part of c' = 2S/N - c, rounded once to the storage (U32: one binary32 subtraction from 2S/N in binary32)
+    __device__ static inline H update(H c, double m, float m32)
+    {
+        if constexpr (U32)
+            return m32 - c;
+        else if constexpr (std::is_same<T, C64>::value)
+            return H(float(m - double(c)));
+        else
+            return m - c;
+    }
+    __device__ static inline void get(const typename T::vec &v, H (&x)[parts])
+    {
+        if constexpr (parts == 4) {
+            x[0] = v.x;
+            x[1] = v.y;
+            x[2] = v.z;
+            x[3] = v.w;
+        } else {
+            x[0] = v.x;
+            x[1] = v.y;
+        }
+    }
+    __device__ static inline typename T::vec vec(const H (&x)[parts])
+    {
+        if constexpr (parts == 4)
+            return make_float4(float(x[0]), float(x[1]), float(x[2]), float(x[3]));
+        else
+            return make_double2(x[0], x[1]);
+    }
+    // A vector's parts into the sum, amplitude by amplitude.  The empty asm hides that a binary32 part is still
+    // the value that was widened here: else the compiler keeps the widened values of all of them for the next
+    // iteration, which is what `widen` does where there is room, and spills elsewhere.
+    __device__ static inline void add(H (&x)[parts], AccF64 &acc)
+    {
 #pragma unroll
-    for (int e = 0; e < kHeldHoldE; ++e) {
-        const unsigned b = (mask >> (2 * e)) & 3u;
-        if (b != 0u) {
-            float4 v = e < kHeldRegE ? x[e] : held[(e - kHeldRegE) * kStreamBlock + threadIdx.x];
-            if (b & 1u) {
-                v.x = -v.x;
-                v.y = -v.y;
-            }
-            if (b & 2u) {
-                v.z = -v.z;
-                v.w = -v.w;
-            }
-            if (e < kHeldRegE)
-                x[e] = v;
+        for (int p = 0; p < parts; ++p) {
+            if (imag(p))
+                acc.i += double(x[p]);
             else
-                held[(e - kHeldRegE) * kStreamBlock + threadIdx.x] = v;
+                acc.r += double(x[p]);
+            if constexpr (std::is_same<H, float>::value)
+                asm volatile("" : "+v"(x[p]));
         }
     }
-}
-
-// After the sweep: the sum holds +c' for the marked amplitudes; subtracting 2c' makes it s c'.
-__device__ inline void correct_marked(const float4 (&x)[kHeldRegE], const float4 *held, uint32_t mask, AccF64 &acc)
-{
+    __device__ static inline void step(H (&x)[parts], double mr, double mi, float mr32, float mi32, AccF64 &acc)
+    {
 #pragma unroll
-    for (int e = 0; e < kHeldHoldE; ++e) {
-        const unsigned b = (mask >> (2 * e)) & 3u;
-        if (b != 0u) {
-            const float4 v = e < kHeldRegE ? x[e] : held[(e - kHeldRegE) * kStreamBlock + threadIdx.x];
-            if (b & 1u)
-                acc.add(-2.0 * double(v.x), -2.0 * double(v.y));
-            if (b & 2u)
-                acc.add(-2.0 * double(v.z), -2.0 * double(v.w));
-        }
+        for (int p = 0; p < parts; ++p)
+            x[p] = imag(p) ? update(x[p], mi, mi32) : update(x[p], mr, mr32);
+        add(x, acc);
     }
-}
+    // Marked amplitudes (bit a of `bits`: amplitude a of the vector) are handled around the sweep, which then
+    // treats every amplitude alike: their held values are negated before it (exactly), which makes the update
+    // 2S/N + c, their correct new value, and the sum is corrected after it by -2c' (so it holds s c').
+    __device__ static inline void negate(H (&x)[parts], unsigned bits)
+    {
+#pragma unroll
+        for (int p = 0; p < parts; ++p)
+            x[p] = (bits >> amp(p)) & 1u ? -x[p] : x[p];
+    }
+    __device__ static inline void correct(const H (&x)[parts], unsigned bits, AccF64 &acc)
+    {
+#pragma unroll
+        for (int p = 0; p < parts; ++p)
+            if ((bits >> amp(p)) & 1u) {
+                if (imag(p))
+                    acc.i += -2.0 * double(x[p]);
+                else
+                    acc.r += -2.0 * double(x[p]);
+            }
+    }
+};
 
-// One iteration over a thread's held vectors (e < ne in order: x[e] in registers for e < kHeldRegE, then the
-// LDS slots), each updated as unmarked.  When all 16 are held, the LDS vectors are loaded four at a time,
-// each group while the previous one (or the register half) is being updated, so that their latency hides
-// behind arithmetic.  M is the type of 2S/N: double for the binary64 update, float (already rounded) for
-// the binary32 one.
-template <class M>
-__device__ inline void held_sweep(float4 (&x)[kHeldRegE], float4 *held, unsigned ne, M mr, M mi, AccF64 &acc)
+// Marked bits of a thread's vectors, two per vector: bits 2 r, 2 r + 1 of word r / 16 for position r.
+template <int NE>
+struct MarkBits {
+    static constexpr int words = (NE + 15) / 16;
+    uint32_t w[words];
+    __device__ inline unsigned at(int r) const { return (w[r / 16] >> (2 * (r % 16))) & 3u; }
+    // a position in LDS: all in the last word
+    __device__ inline unsigned in_lds(int r) const { return (w[words - 1] >> (2 * (r % 16))) & 3u; }
+    __device__ inline void set(unsigned r, unsigned b)
+    {
+#pragma unroll
+        for (int i = 0; i < words; ++i)
+            w[i] |= int(r / 16u) == i ? b << (2u * (r % 16u)) : 0u;
+    }
+};
+
+// All iterations of one member's share, and the store back.  The state is loaded (kLoad) or starts as `fill`;
+// its oracle-signed sum is formed in the order the iterations add theirs, so consecutive calls compose bit for
+// bit.  `begin` is asked once, by the whole workgroup, before the first sum; `reduce` is the team's (or the
+// workgroup's) sum.  Returns false, nothing stored, when either says so.  `mine`: the thread's LDS slots, B apart.
+//
+// Position r of a thread holds vector e = r ^ swap, swap the same in every lane of a wave and chosen so that the
+// wave's first marked vector is at position 0: the few instructions for marks are then spent on position 0
+// alone, unless the wave holds marks in other rows too (`rest`, a bit per position).
+template <class T, bool U32, bool WIDE, int NE, int RE, int B, bool kLoad, class Begin, class Reduce>
+__device__ __forceinline__ bool held_run(typename T::vec *st, uint64_t base, uint64_t per, const uint64_t *marks,
+                                         uint64_t m, uint64_t iters, double scale, const typename T::vec &fill,
+                                         typename T::vec *mine, Begin begin, Reduce reduce)
 {
-    const unsigned tid = threadIdx.x;
-    if (ne == unsigned(kHeldHoldE)) {
-        constexpr int kG = 4;
-        static_assert(2 * kG == kHeldLdsE, "two groups cover the LDS half");
-        float4 y[kG], z[kG];
-#pragma unroll
-        for (int g = 0; g < kG; ++g)
-            y[g] = held[g * kStreamBlock + tid];
-#pragma unroll
-        for (int e = 0; e < kHeldRegE; ++e)
-            unmarked_update(x[e], mr, mi, acc);
-#pragma unroll
-        for (int g = 0; g < kG; ++g)
-            z[g] = held[(kG + g) * kStreamBlock + tid];
-#pragma unroll
-        for (int g = 0; g < kG; ++g) {
-            unmarked_update(y[g], mr, mi, acc);
-            held[g * kStreamBlock + tid] = y[g];
-        }
-#pragma unroll
-        for (int g = 0; g < kG; ++g) {
-            unmarked_update(z[g], mr, mi, acc);
-            held[(kG + g) * kStreamBlock + tid] = z[g];
+    using X = Held<T, U32, WIDE>;
+    using V = typename T::vec;
+    constexpr int LE = NE - RE;
+    static_assert(LE == 0 || (LE <= 16 && RE % 16 + LE <= 16), "the LDS positions' marked bits lie in one word");
+    const unsigned tid = threadIdx.x, wave = tid / kWave;
+    const bool active = NE > 1 || tid < per;
+
+    // this member's slice of the sorted marked list, and from it the wave's swap and the threads' marked bits
+    const uint64_t lo = m > 0 ? lower_bound_u64(marks, 0, m, base * T::EPV) : 0;
+    const uint64_t hi = m > 0 ? lower_bound_u64(marks, lo, m, (base + per) * T::EPV) : 0;
+    MarkBits<NE> mk{};
+    unsigned swap = 0u;
+    bool marked = false;  // this wave holds marked amplitudes (the same in every lane)
+    uint64_t rest = 0;    // positions above 0 that hold marks in some lane of this wave
+    if (hi - lo <= uint64_t(B)) {
+        for (uint64_t i = lo; i < hi; ++i) {
+            const uint64_t x = marks[i];
+            const unsigned v = unsigned(x / T::EPV - base), e = v / B, owner = v % B;
+            if (owner / kWave == wave) {
+                if (!marked)
+                    swap = e;
+                marked = true;
+                const unsigned r = e ^ swap;
+                if (owner == tid)
+                    mk.set(r, 1u << unsigned(x % T::EPV));
+                rest |= r > 0u ? uint64_t(1) << r : 0u;
+            }
         }
     } else {
-#pragma unroll
-        for (int e = 0; e < kHeldRegE; ++e)
-            if (unsigned(e) < ne)
-                unmarked_update(x[e], mr, mi, acc);
+#pragma unroll 1
+        for (unsigned r = 0; r < unsigned(NE); ++r) {
+            const unsigned b = active ? marked_bits<T::EPV>(marks, lo, hi, (base + uint64_t(r) * B + tid) * T::EPV) : 0u;
+            mk.set(r, b);
+            if (__any(b != 0u)) {
+                marked = true;
+                rest |= r > 0u ? uint64_t(1) << r : 0u;
+            }
+        }
     }
+    // the same in every lane of a wave: kept in scalar registers
+    swap = __builtin_amdgcn_readfirstlane(swap);
+    const unsigned is_marked = __builtin_amdgcn_readfirstlane(marked ? 1u : 0u);
+    const uint32_t rest_lo = __builtin_amdgcn_readfirstlane(uint32_t(rest)), rest_hi = __builtin_amdgcn_readfirstlane(uint32_t(rest >> 32));
+    auto in_rest = [&](int r) { return ((r < 32 ? rest_lo >> r : rest_hi >> (r - 32)) & 1u) != 0u; };
+    const bool has_rest = (rest_lo | rest_hi) != 0u;
+
+    typename X::H x[RE][X::parts];
+    // byte offset of position r's vector in this member's share
+    const auto rs = buffer_rsrc(st, uint32_t(per * 16u));
+    auto at = [&](unsigned r, unsigned t16) { return (r ^ swap) * unsigned(B * 16) + t16; };
+    AccF64 acc0;
+    auto correct_all = [&](AccF64 &acc) {
+        X::correct(x[0], mk.at(0), acc);
+        if (has_rest) {
+#pragma unroll
+            for (int r = 1; r < RE; ++r)
+                if (in_rest(r))
+                    X::correct(x[r], mk.at(r), acc);
+#pragma unroll 1
+            for (int r = RE; r < NE; ++r)
+                if (in_rest(r)) {
+                    typename X::H y[X::parts];
+                    X::get(mine[(r - RE) * B], y);
+                    X::correct(y, mk.in_lds(r), acc);
+                }
+        }
+    };
+    if (active) {
+#pragma unroll
+        for (int r = 0; r < RE; ++r)
+            X::get(kLoad ? bload16<kBufNT, V>(rs, at(r, tid * 16u)) : fill, x[r]);
+#pragma unroll 4
+        for (int r = RE; r < NE; ++r)
+            mine[(r - RE) * B] = kLoad ? bload16<kBufNT, V>(rs, at(r, tid * 16u)) : fill;
+#pragma unroll
+        for (int r = 0; r < RE; ++r)
+            X::add(x[r], acc0);
+#pragma unroll 2
+        for (int r = RE; r < NE; ++r) {
+            typename X::H y[X::parts];
+            X::get(mine[(r - RE) * B], y);
+            X::add(y, acc0);
+        }
+        if (is_marked)
+            correct_all(acc0);
+    }
+    double sr = acc0.r, si = acc0.i;
+    if (!begin() || !reduce(sr, si))
+        return false;
+    for (uint64_t it = 0; it < iters; ++it) {
+        const double mr = sr * scale, mi = si * scale;
+        const float mr32 = float(mr), mi32 = float(mi);
+        AccF64 acc;
+        if (active) {
+            if (is_marked) {
+                X::negate(x[0], mk.at(0));
+                if (has_rest) {
+#pragma unroll
+                    for (int r = 1; r < RE; ++r)
+                        if (in_rest(r))
+                            X::negate(x[r], mk.at(r));
+#pragma unroll 1
+                    for (int r = RE; r < NE; ++r)
+                        if (in_rest(r)) {
+                            typename X::H y[X::parts];
+                            X::get(mine[(r - RE) * B], y);
+                            X::negate(y, mk.in_lds(r));
+                            mine[(r - RE) * B] = X::vec(y);
+                        }
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < RE; ++r)
+                X::step(x[r], mr, mi, mr32, mi32, acc);
+#pragma unroll 4
+            for (int r = RE; r < NE; ++r) {
+                typename X::H y[X::parts];
+                X::get(mine[(r - RE) * B], y);
+                X::step(y, mr, mi, mr32, mi32, acc);
+                mine[(r - RE) * B] = X::vec(y);
+            }
+            if (is_marked)
+                correct_all(acc);
+        }
+        sr = acc.r;
+        si = acc.i;
+        if (!reduce(sr, si))
+            return false;
+    }
+    if (active) {
+        unsigned t16 = tid * 16u;
+        asm volatile("" : "+v"(t16));  // offsets computed again, not kept in registers since the loads
+#pragma unroll
+        for (int r = 0; r < RE; ++r)
+            bstore16<kBufNT>(X::vec(x[r]), rs, at(r, t16));
+#pragma unroll 4
+        for (int r = RE; r < NE; ++r)
+            bstore16<kBufNT>(mine[(r - RE) * B], rs, at(r, t16));
+    }
+    return true;
 }
 
 }  // namespace grover

@@ -1,29 +1,31 @@
 // Batched searches in one persistent launch (many independent instances of Algorithm 5, complex64 states,
-// binary64 sums, the update in binary64 or binary32).  The grid (one workgroup per CU, all co-resident) works through a sequence of
-// phases, each with its own queue ordered by decreasing work N * k and its own team size T:
-//   - in a phase with T > 1 the grid is split into teams of T consecutive workgroups; a team's leader takes
-//     the next instance and publishes it through the team barrier, and the team iterates it with one team
-//     barrier per iteration (which also reduces the sum).  The state is either held on chip by the team
-//     for all iterations (resident phases: the instance fits T * 1024 threads * the phase's vectors per
-//     thread, up to 8 in registers and 8 more in LDS) or streamed from memory every iteration, exactly as
-//     the fused single-instance kernel does;
-//   - in a phase with T = 1 every workgroup takes instances alone: held on chip (registers and LDS) when
-//     the state fits (n <= 15), otherwise streamed with workgroup-level sums only.
+// binary64 sums, the update in binary64 or binary32).  The grid (one workgroup of 512 threads per CU, all
+// co-resident) works through a sequence of phases, each with its own queue ordered by decreasing work N * k and
+// its own team size T:
+//   - in a phase with T > 1 the grid is split into teams of T workgroups; a team's leader takes the next
+//     instance and publishes it through the team barrier, and the team iterates it with one team barrier per
+//     iteration (which also reduces the sum).  The state is either held on chip by the team for all iterations
+//     (resident phases: the instance fits T * 512 threads * the phase's vectors per thread, up to 32, all in
+//     registers) or streamed from memory every iteration, as the fused single-instance kernel does;
+//   - in a phase with T = 1 every workgroup takes instances alone: held on chip when the state fits (n <= 15),
+//     otherwise streamed with workgroup-level sums only.
 // Team sizes do not increase from one phase to the next and each divides the previous one, so the members
 // of a team always come from one team of the previous phase (they finish it together) and no grid-wide
 // barrier is needed between phases.  Which phases exist and their parameters is the tiling the host
 // chooses; each instance starts from the uniform superposition.
+//
+// What bounds an iteration of a resident instance at n = 20 (T = 32): 2.2 us of update instructions (five per
+// part, 32 vectors per thread, 4.2 cycles per instruction and SIMD), 1.2 us for the team barrier.  512 threads
+// rather than 1024: all 32 vectors sit in registers (the other half of 16 went through LDS), and half the waves
+// pay the reduction.  Two workgroups of 16 vectors per CU, to update one instance while another waits, do not
+// overlap: a second workgroup on the CU lengthened the barrier from 1.4 to 2.9 us (T = 64), whatever the waves'
+// priorities and the pace of the polls, and an n = 20 iteration to 4.5 us.  1024 searches of n = 8 .. 20: 32.2 -> 23.8 ms on MI355X.
 #include "batch.h"
 #include "held.h"
 #include "stream.h"
 
 namespace grover {
 namespace {
-
-constexpr int kRegE = kHeldRegE;
-constexpr int kLdsE = kHeldLdsE;
-constexpr int kHoldE = kHeldHoldE;
-static_assert(kHeldRegE == kBatchRegE && kHeldLdsE == kBatchLdsE, "the batch tiling assumes the held layout");
 
 struct BatchArgs {
     float4 *state;
@@ -55,117 +57,56 @@ __device__ inline float4 uniform_vec(double amp)
     return make_float4(af, 0.0f, af, 0.0f);
 }
 
-// One instance streamed by the T workgroups of a team.  Returns false when a barrier gave up.
-template <bool U32>
-__device__ bool run_team_streamed(const BatchArgs &a, const BatchInstance &I, const Team &tm, uint64_t &gen,
-                                  TeamShared<kStreamBlock> &sh, uint32_t *table)
+// One instance streamed by the T workgroups of a team (or by one).  Returns false when a barrier gave up.
+template <bool U32, class Reduce>
+__device__ bool run_streamed(const BatchArgs &a, const BatchInstance &I, unsigned rank, unsigned size, uint32_t *table,
+                             Reduce reduce)
 {
-    const Share<C64> share{a.state + I.state_off, I.nvec, a.marks + I.marks_off, I.m, tm.rank, tm.size};
-    const bool use_table = build_mark_table(share, table);
+    const Share<C64> share{a.state + I.state_off, I.nvec, a.marks + I.marks_off, I.m, rank, size};
+    const bool use_table = build_mark_table<kBatchBlock>(share, table);
     AccF64 acc0;
-    stream_pass<C64, AccF64, kFill>(share, table, use_table, 0.0, 0.0, uniform_vec(I.amp), acc0);
+    stream_pass<kBatchBlock, C64, AccF64, kFill>(share, table, use_table, 0.0, 0.0, uniform_vec(I.amp), acc0);
     double sr = acc0.r, si = acc0.i;
-    if (!team_sum<kStreamBlock>(sr, si, tm, ++gen, sh))
+    if (!reduce(sr, si))
         return false;
     const float4 none{};
     for (uint64_t it = 0; it < I.iters; ++it) {
         const double mr = (sr * 2.0) / I.N, mi = (si * 2.0) / I.N;
         AccF64 acc;
-        stream_pass<C64, AccF64, kUpdate, U32>(share, table, use_table, mr, mi, none, acc);
-        sr = acc.r;
-        si = acc.i;
-        if (!team_sum<kStreamBlock>(sr, si, tm, ++gen, sh))
-            return false;
-    }
-    return true;
-}
-
-// One instance held on chip by a team for all its iterations: member `rank` owns the contiguous vectors
-// [rank * per, (rank + 1) * per), per = nvec / T a power of two <= kHoldE * 1024, thread `tid` the vectors
-// rank * per + e * 1024 + tid, e < ne = per / 1024 (or, when per < 1024, the one vector tid < per): the
-// first kRegE in registers, the others in the thread's own slots of LDS (held[(e - kRegE) * 1024 + tid]; no
-// other thread touches them, so no workgroup barrier is needed around them).  Marked bits travel packed, two
-// per vector.  `reduce` is the team's (or the workgroup's) sum; the state is written to memory once, at
-// the end.  Returns false when a barrier gave up.
-template <bool U32, class Reduce>
-__device__ bool run_held(const BatchArgs &a, const BatchInstance &I, uint64_t base, uint64_t per, float4 *held,
-                         TeamShared<kStreamBlock> &sh, Reduce reduce)
-{
-    float4 *st = a.state + I.state_off + base;
-    const uint64_t *marks = a.marks + I.marks_off;
-    const unsigned tid = threadIdx.x;
-    const unsigned ne = per >= kStreamBlock ? unsigned(per / kStreamBlock) : 1u;  // 1, 2, 4, 8 or 16
-    const bool active = tid < per;
-    const float4 fill = uniform_vec(I.amp);
-    // 2/N is a power of two, so S * (2/N) rounds to the same binary64 value as 2S / N
-    const double scale = 2.0 / I.N;
-    uint32_t mask = 0u;
-    AccF64 acc0;
-    if (active) {
-#pragma unroll 1
-        for (unsigned e = 0; e < ne; ++e) {
-            const uint64_t v = uint64_t(e) * kStreamBlock + tid;
-            const unsigned bits = marked_bits<2>(marks, 0, I.m, (base + v) * 2u);
-            mask |= uint32_t(bits) << (2 * e);
-            accum_vec<C64>(fill, bits, acc0);
-            if (e >= unsigned(kRegE))
-                held[(e - kRegE) * kStreamBlock + tid] = fill;
-        }
-    }
-    float4 x[kRegE];
-#pragma unroll
-    for (int e = 0; e < kRegE; ++e)
-        x[e] = fill;
-    double sr = acc0.r, si = acc0.i;
-    if (!reduce(sr, si))
-        return false;
-    for (uint64_t it = 0; it < I.iters; ++it) {
-        const double mr = sr * scale, mi = si * scale;
-        AccF64 acc;
-        if (active) {
-            if (mask != 0u)
-                negate_marked(x, held, mask);
-            if constexpr (U32)
-                held_sweep(x, held, ne, float(mr), float(mi), acc);
-            else
-                held_sweep(x, held, ne, mr, mi, acc);
-            if (mask != 0u)
-                correct_marked(x, held, mask, acc);
-        }
+        stream_pass<kBatchBlock, C64, AccF64, kUpdate, U32>(share, table, use_table, mr, mi, none, acc);
         sr = acc.r;
         si = acc.i;
         if (!reduce(sr, si))
             return false;
     }
-    if (active) {
-#pragma unroll
-        for (int e = 0; e < kHoldE; ++e)
-            if (unsigned(e) < ne)
-                st[uint64_t(e) * kStreamBlock + tid] = e < kRegE ? x[e] : held[(e - kRegE) * kStreamBlock + tid];
-    }
     return true;
 }
 
-// One instance iterated by one workgroup, its state streamed from memory.
-template <bool U32>
-__device__ void run_single_streamed(const BatchArgs &a, const BatchInstance &I, TeamShared<kStreamBlock> &sh,
-                                    uint32_t *table)
+// One instance held on chip by a team for all its iterations (member `rank` owns the contiguous vectors
+// [rank * per, (rank + 1) * per), per = nvec / T a power of two), from the uniform state, in registers; written to
+// memory once, at the end.  Returns false when a barrier gave up.
+template <bool U32, int NE, class Reduce>
+__device__ __forceinline__ bool run_held_ne(const BatchArgs &a, const BatchInstance &I, uint64_t base, uint64_t per,
+                                            Reduce reduce)
 {
-    const Share<C64> share{a.state + I.state_off, I.nvec, a.marks + I.marks_off, I.m, 0, 1};
-    const bool use_table = build_mark_table(share, table);
-    AccF64 acc0;
-    stream_pass<C64, AccF64, kFill>(share, table, use_table, 0.0, 0.0, uniform_vec(I.amp), acc0);
-    double sr = acc0.r, si = acc0.i;
-    unsigned parity = 0;
-    block_allsum(sr, si, parity++, sh);
-    const float4 none{};
-    for (uint64_t it = 0; it < I.iters; ++it) {
-        const double mr = (sr * 2.0) / I.N, mi = (si * 2.0) / I.N;
-        AccF64 acc;
-        stream_pass<C64, AccF64, kUpdate, U32>(share, table, use_table, mr, mi, none, acc);
-        sr = acc.r;
-        si = acc.i;
-        block_allsum(sr, si, parity++, sh);
+    // 2/N is a power of two, so S * (2/N) rounds to the same binary64 value as 2S / N
+    return held_run<C64, U32, !U32 && NE <= 16, NE, NE, kBatchBlock, false>(
+        a.state + I.state_off + base, base, per, a.marks + I.marks_off, I.m, I.iters, 2.0 / I.N, uniform_vec(I.amp),
+        static_cast<float4 *>(nullptr), []() { return true; }, reduce);
+}
+
+template <bool U32, class Reduce>
+__device__ __forceinline__ bool run_held(const BatchArgs &a, const BatchInstance &I, uint64_t base, uint64_t per,
+                                         Reduce reduce)
+{
+    switch (per < uint64_t(kBatchBlock) ? 1u : unsigned(per / kBatchBlock)) {
+    case 1: return run_held_ne<U32, 1>(a, I, base, per, reduce);
+    case 2: return run_held_ne<U32, 2>(a, I, base, per, reduce);
+    case 4: return run_held_ne<U32, 4>(a, I, base, per, reduce);
+    case 8: return run_held_ne<U32, 8>(a, I, base, per, reduce);
+    case 16: return run_held_ne<U32, 16>(a, I, base, per, reduce);
+    case 32: return run_held_ne<U32, 32>(a, I, base, per, reduce);
+    default: return false;
     }
 }
 
@@ -175,20 +116,18 @@ __device__ void run_single_streamed(const BatchArgs &a, const BatchInstance &I, 
 // it through the error word instead of computing.  U32: the update in binary32 from 2S/N rounded to
 // binary32; otherwise in binary64.
 template <bool kStreams, bool U32>
-__global__ __launch_bounds__(kStreamBlock) void batch_kernel(BatchArgs a)
+__global__ __launch_bounds__(kBatchBlock) void batch_kernel(BatchArgs a)
 {
-    __shared__ TeamShared<kStreamBlock> sh;
-    __shared__ uint32_t table[kMarkWords];
-    __shared__ uint64_t taken;
-    __shared__ float4 held[kLdsE * kStreamBlock];  // on-chip state beyond the registers (128 KiB)
+    __shared__ TeamShared<kBatchBlock> sh;
+    __shared__ uint32_t table[kStreams ? kMarkWords : 1];
     const uint32_t grid = gridDim.x;
-    const unsigned major = xcd_major_block();
     if (a.probe) {
         const Team tm{a.sync, a.partials, grid, blockIdx.x, a.timeout_ticks};
         double zr = 0.0, zi = 0.0;
-        (void)team_sum<kStreamBlock>(zr, zi, tm, 1u, sh);
+        (void)team_sum<kBatchBlock>(zr, zi, tm, 1u, sh);
         return;
     }
+    const unsigned major = xcd_major_block();
     for (uint32_t p = 0; p < a.nphases; ++p) {
         const uint64_t q0 = a.qoff[p], count = a.qoff[p + 1] - q0;
         const unsigned T = a.team[p];
@@ -197,62 +136,45 @@ __global__ __launch_bounds__(kStreamBlock) void batch_kernel(BatchArgs a)
         const unsigned teams = grid / T, team_id = block / T;
         if (count == 0 || team_id >= teams)
             continue;
-        if (T == 1) {
-            for (;;) {
-                if (threadIdx.x == 0)
-                    taken = atomicAdd(&a.heads[p], 1ull);
-                __syncthreads();
-                // the index is the same in every lane; saying so keeps the instance's fields in scalar registers
-                const uint64_t q = __builtin_amdgcn_readfirstlane(uint32_t(taken)) |
-                                   (uint64_t(__builtin_amdgcn_readfirstlane(uint32_t(taken >> 32))) << 32);
-                __syncthreads();
-                if (q >= count)
-                    break;
-                const BatchInstance I = a.inst[a.queue[q0 + q]];
-                unsigned parity = 0;
-                if (I.nvec <= uint64_t(kHoldE) * kStreamBlock)
-                    (void)run_held<U32>(a, I, 0, I.nvec, held, sh, [&](double &r, double &i) {
-                        block_allsum(r, i, parity++, sh);
-                        return true;
-                    });
-                else if (kStreams)
-                    run_single_streamed<U32>(a, I, sh, table);
-                else
-                    flag_error(a.sync + uint64_t(p) * grid + block);
-            }
-            continue;
-        }
         const Team tm{a.sync + uint64_t(p) * grid + team_id,
                       a.partials + uint64_t(p) * kBatchSlotWords * grid + uint64_t(team_id) * team_words(T), T, block % T,
                       a.timeout_ticks};
         uint64_t gen = 0;
+        unsigned parity = 0;
+        auto reduce = [&](double &r, double &i) {
+            if (T == 1u) {
+                block_allsum<kBatchBlock>(r, i, parity++, sh);
+                return true;
+            }
+            return team_sum<kBatchBlock>(r, i, tm, ++gen, sh);
+        };
         for (;;) {
-            // the leader takes the next instance and contributes its index to a team sum (exact in binary64:
-            // one integer below 2^53 plus zeros), which hands it to every member
+            // the leader takes the next instance and contributes its index to a sum (exact in binary64: one
+            // integer below 2^53 plus zeros), which hands it to every member
             double zr = 0.0, zi = 0.0;
             if (tm.rank == 0 && threadIdx.x == 0)
                 zr = double(atomicAdd(&a.heads[p], 1ull));
-            if (!team_sum<kStreamBlock>(zr, zi, tm, ++gen, sh))
+            if (!reduce(zr, zi))
                 return;
-            const uint64_t qv = uint64_t(zr);  // the same in every lane (a team sum); made scalar below
+            const uint64_t qv = uint64_t(zr);  // the same in every lane; made scalar, as the instance's fields are
             const uint64_t q = __builtin_amdgcn_readfirstlane(uint32_t(qv)) |
                                (uint64_t(__builtin_amdgcn_readfirstlane(uint32_t(qv >> 32))) << 32);
             if (q >= count)
                 break;
             const BatchInstance I = a.inst[a.queue[q0 + q]];
             bool ok;
-            if (a.resident[p]) {
+            if (T == 1u ? I.nvec <= kBatchAloneVecs : a.resident[p] != 0u) {
                 const uint64_t per = I.nvec / T;
-                ok = run_held<U32>(a, I, uint64_t(tm.rank) * per, per, held, sh,
-                                   [&](double &r, double &i) { return team_sum<kStreamBlock>(r, i, tm, ++gen, sh); });
+                ok = run_held<U32>(a, I, uint64_t(tm.rank) * per, per, reduce);
             } else if (kStreams) {
-                ok = run_team_streamed<U32>(a, I, tm, gen, sh, table);
+                ok = run_streamed<U32>(a, I, tm.rank, T, table, reduce);
             } else {
-                flag_error(tm.sync);
                 ok = false;
             }
-            if (!ok)
+            if (!ok) {
+                flag_error(tm.sync);
                 return;
+            }
         }
     }
 }
@@ -316,7 +238,7 @@ hipError_t launch_batch(const BatchLaunch &L)
         return e;
     void *args[] = {&a};
     return hipLaunchCooperativeKernel(batch_kernel_fn(L.streams != 0u, L.update != 0u), dim3(L.grid),
-                                      dim3(kStreamBlock), args, 0, L.stream);
+                                      dim3(kBatchBlock), args, 0, L.stream);
 }
 
 }  // namespace grover

@@ -16,12 +16,11 @@
 // thread are held widened to binary64 (values that a binary32 represents), which saves one of five
 // instructions per part.  One optimal search (or 801 iterations at n = 24), 1024-thread workgroups of at most 16
 // vectors and the earlier barrier (n = 24 and complex128: the streaming fused kernel) -> this kernel on MI355X:
-// complex64 n = 16 (binary32 update) 0.634 -> 0.349 ms, n = 20 3.48 -> 2.10, n = 24 14.1 -> 6.44 (8.0 us per
-// iteration); complex128 n = 21 4.61 -> 1.96 ms (2.4 us per iteration).
+// complex64 n = 16 (binary32 update) 0.635 -> 0.311 ms, n = 20 3.49 -> 2.07, n = 24 14.1 -> 6.44 (8.0 us per
+// iteration); complex128 n = 21 4.61 -> 1.98 ms (2.5 us per iteration).
 #include <algorithm>
-#include <type_traits>
 
-#include "stream.h"
+#include "held.h"
 
 namespace grover {
 namespace {
@@ -45,113 +44,11 @@ struct ChipArgs {
     uint32_t probe;  // 1: one team barrier only (residency check)
 };
 
-// A storage vector as `parts` numbers, part p of amplitude amp(p); imag(p): an imaginary part.  H: the type
-// that a held part has; widen: complex64 parts held as binary64 values that binary32 represents.
-template <class T, bool U32, bool WIDE>
-struct Held {
-    static constexpr int parts = T::EPV * (T::kComplex ? 2 : 1);
-    using H = typename std::conditional<std::is_same<T, C64>::value && !WIDE, float, double>::type;
-    __device__ static constexpr int amp(int p) { return T::kComplex ? p / 2 : p; }
-    __device__ static constexpr bool imag(int p) { return T::kComplex && (p & 1); }
-    // one part of c' = 2S/N - c, rounded once to the storage (U32: one binary32 subtraction from 2S/N in binary32)
-    __device__ static inline H update(H c, double m, float m32)
-    {
-        if constexpr (U32)
-            return m32 - c;
-        else if constexpr (std::is_same<T, C64>::value)
-            return H(float(m - double(c)));
-        else
-            return m - c;
-    }
-    __device__ static inline void get(const typename T::vec &v, H (&x)[parts])
-    {
-        if constexpr (parts == 4) {
-            x[0] = v.x;
-            x[1] = v.y;
-            x[2] = v.z;
-            x[3] = v.w;
-        } else {
-            x[0] = v.x;
-            x[1] = v.y;
-        }
-    }
-    __device__ static inline typename T::vec vec(const H (&x)[parts])
-    {
-        if constexpr (parts == 4)
-            return make_float4(float(x[0]), float(x[1]), float(x[2]), float(x[3]));
-        else
-            return make_double2(x[0], x[1]);
-    }
-    // A vector's parts into the sum, amplitude by amplitude.  The empty asm hides that a binary32 part is still
-    // the value that was widened here: else the compiler keeps the widened values of all of them for the next
-    // iteration, which is what `widen` does where there is room, and spills elsewhere.
-    __device__ static inline void add(H (&x)[parts], AccF64 &acc)
-    {
-#pragma unroll
-        for (int p = 0; p < parts; ++p) {
-            if (imag(p))
-                acc.i += double(x[p]);
-            else
-                acc.r += double(x[p]);
-            if constexpr (std::is_same<H, float>::value)
-                asm volatile("" : "+v"(x[p]));
-        }
-    }
-    __device__ static inline void step(H (&x)[parts], double mr, double mi, float mr32, float mi32, AccF64 &acc)
-    {
-#pragma unroll
-        for (int p = 0; p < parts; ++p)
-            x[p] = imag(p) ? update(x[p], mi, mi32) : update(x[p], mr, mr32);
-        add(x, acc);
-    }
-    // Marked amplitudes (bit a of `bits`: amplitude a of the vector) are handled around the sweep, which then
-    // treats every amplitude alike: their held values are negated before it (exactly), which makes the update
-    // 2S/N + c, their correct new value, and the sum is corrected after it by -2c' (so it holds s c').
-    __device__ static inline void negate(H (&x)[parts], unsigned bits)
-    {
-#pragma unroll
-        for (int p = 0; p < parts; ++p)
-            x[p] = (bits >> amp(p)) & 1u ? -x[p] : x[p];
-    }
-    __device__ static inline void correct(const H (&x)[parts], unsigned bits, AccF64 &acc)
-    {
-#pragma unroll
-        for (int p = 0; p < parts; ++p)
-            if ((bits >> amp(p)) & 1u) {
-                if (imag(p))
-                    acc.i += -2.0 * double(x[p]);
-                else
-                    acc.r += -2.0 * double(x[p]);
-            }
-    }
-};
-
-// Marked bits of a thread's vectors, two per vector: bits 2 r, 2 r + 1 of word r / 16 for position r.
-template <int NE>
-struct MarkBits {
-    static constexpr int words = (NE + 15) / 16;
-    uint32_t w[words];
-    __device__ inline unsigned at(int r) const { return (w[r / 16] >> (2 * (r % 16))) & 3u; }
-    // a position in LDS, r >= kChipRegE: all in the last word
-    __device__ inline unsigned in_lds(int r) const { return (w[words - 1] >> (2 * (r % 16))) & 3u; }
-    __device__ inline void set(unsigned r, unsigned b)
-    {
-#pragma unroll
-        for (int i = 0; i < words; ++i)
-            w[i] |= int(r / 16u) == i ? b << (2u * (r % 16u)) : 0u;
-    }
-};
-
-// Position r of a thread holds vector e = r ^ swap, swap the same in every lane of a wave and chosen so that the
-// wave's first marked vector is at position 0: the few instructions for marks are then spent on position 0
-// alone, unless the wave holds marks in other rows too (`rest`, a bit per position).
 template <class T, bool U32, int NE>
 __global__ __launch_bounds__(kChipBlock) void chip_iterate_kernel(ChipArgs a)
 {
     constexpr int RE = NE > kChipRegE ? kChipRegE : NE, LE = NE - RE;
-    static_assert(LE == 0 || (LE <= 16 && RE % 16 == 0), "the LDS positions' marked bits fill one word");
     constexpr bool kWide = std::is_same<T, C64>::value && !U32 && NE <= 16;
-    using X = Held<T, U32, kWide>;
     using V = typename T::vec;
     __shared__ TeamShared<kChipBlock> sh;
     __shared__ V held[LE > 0 ? LE * kChipBlock : 1];
@@ -171,146 +68,11 @@ __global__ __launch_bounds__(kChipBlock) void chip_iterate_kernel(ChipArgs a)
     uint32_t error = 0u;
     if (threadIdx.x == 0)
         error = __hip_atomic_load(&a.sync->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned tid = threadIdx.x, wave = tid / kWave;
-    const uint64_t per = a.per, base = uint64_t(rank) * per;
-    const bool active = NE > 1 || tid < per;
-    V *st = static_cast<V *>(a.state) + base;
-
-    // this member's slice of the sorted marked list, and from it the wave's swap and the threads' marked bits
-    const uint64_t lo = a.m > 0 ? lower_bound_u64(a.marks, 0, a.m, base * T::EPV) : 0;
-    const uint64_t hi = a.m > 0 ? lower_bound_u64(a.marks, lo, a.m, (base + per) * T::EPV) : 0;
-    MarkBits<NE> mk{};
-    unsigned swap = 0u;
-    bool marked = false;  // this wave holds marked amplitudes (the same in every lane)
-    uint64_t rest = 0;    // positions above 0 that hold marks in some lane of this wave
-    if (hi - lo <= 512u) {
-        for (uint64_t i = lo; i < hi; ++i) {
-            const uint64_t x = a.marks[i];
-            const unsigned v = unsigned(x / T::EPV - base), e = v / kChipBlock, owner = v % kChipBlock;
-            if (owner / kWave == wave) {
-                if (!marked)
-                    swap = e;
-                marked = true;
-                const unsigned r = e ^ swap;
-                if (owner == tid)
-                    mk.set(r, 1u << unsigned(x % T::EPV));
-                rest |= r > 0u ? uint64_t(1) << r : 0u;
-            }
-        }
-    } else {
-#pragma unroll 1
-        for (unsigned r = 0; r < unsigned(NE); ++r) {
-            const unsigned b = active ? marked_bits<T::EPV>(a.marks, lo, hi, (base + uint64_t(r) * kChipBlock + tid) * T::EPV) : 0u;
-            mk.set(r, b);
-            if (__any(b != 0u)) {
-                marked = true;
-                rest |= r > 0u ? uint64_t(1) << r : 0u;
-            }
-        }
-    }
-    // the same in every lane of a wave: kept in scalar registers
-    swap = __builtin_amdgcn_readfirstlane(swap);
-    const unsigned is_marked = __builtin_amdgcn_readfirstlane(marked ? 1u : 0u);
-    const uint32_t rest_lo = __builtin_amdgcn_readfirstlane(uint32_t(rest)), rest_hi = __builtin_amdgcn_readfirstlane(uint32_t(rest >> 32));
-    auto in_rest = [&](int r) { return ((r < 32 ? rest_lo >> r : rest_hi >> (r - 32)) & 1u) != 0u; };
-    const bool has_rest = (rest_lo | rest_hi) != 0u;
-
-    typename X::H x[RE][X::parts];
-    V *mine = held + tid;
-    // byte offset of position r's vector in this member's share
-    const auto rs = buffer_rsrc(st, uint32_t(per * 16u));
-    auto at = [&](unsigned r, unsigned t16) { return (r ^ swap) * (kChipBlock * 16u) + t16; };
-    AccF64 acc0;
-    auto correct_all = [&](AccF64 &acc) {
-        X::correct(x[0], mk.at(0), acc);
-        if (has_rest) {
-#pragma unroll
-            for (int r = 1; r < RE; ++r)
-                if (in_rest(r))
-                    X::correct(x[r], mk.at(r), acc);
-#pragma unroll 1
-            for (int r = RE; r < NE; ++r)
-                if (in_rest(r)) {
-                    typename X::H y[X::parts];
-                    X::get(mine[(r - RE) * kChipBlock], y);
-                    X::correct(y, mk.in_lds(r), acc);
-                }
-        }
-    };
-    if (active) {
-#pragma unroll
-        for (int r = 0; r < RE; ++r)
-            X::get(bload16<kBufNT, V>(rs, at(r, tid * 16u)), x[r]);
-#pragma unroll 4
-        for (int r = RE; r < NE; ++r)
-            mine[(r - RE) * kChipBlock] = bload16<kBufNT, V>(rs, at(r, tid * 16u));
-#pragma unroll
-        for (int r = 0; r < RE; ++r)
-            X::add(x[r], acc0);
-#pragma unroll 2
-        for (int r = RE; r < NE; ++r) {
-            typename X::H y[X::parts];
-            X::get(mine[(r - RE) * kChipBlock], y);
-            X::add(y, acc0);
-        }
-        if (is_marked)
-            correct_all(acc0);
-    }
-    double sr = acc0.r, si = acc0.i;
-    if (__syncthreads_or(error != 0u))
-        return;
-    if (!team_sum<kChipBlock>(sr, si, tm, ++gen, sh))
-        return;
-    for (uint64_t it = 0; it < a.iters; ++it) {
-        const double mr = sr * a.scale, mi = si * a.scale;
-        const float mr32 = float(mr), mi32 = float(mi);
-        AccF64 acc;
-        if (active) {
-            if (is_marked) {
-                X::negate(x[0], mk.at(0));
-                if (has_rest) {
-#pragma unroll
-                    for (int r = 1; r < RE; ++r)
-                        if (in_rest(r))
-                            X::negate(x[r], mk.at(r));
-#pragma unroll 1
-                    for (int r = RE; r < NE; ++r)
-                        if (in_rest(r)) {
-                            typename X::H y[X::parts];
-                            X::get(mine[(r - RE) * kChipBlock], y);
-                            X::negate(y, mk.in_lds(r));
-                            mine[(r - RE) * kChipBlock] = X::vec(y);
-                        }
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < RE; ++r)
-                X::step(x[r], mr, mi, mr32, mi32, acc);
-#pragma unroll 4
-            for (int r = RE; r < NE; ++r) {
-                typename X::H y[X::parts];
-                X::get(mine[(r - RE) * kChipBlock], y);
-                X::step(y, mr, mi, mr32, mi32, acc);
-                mine[(r - RE) * kChipBlock] = X::vec(y);
-            }
-            if (is_marked)
-                correct_all(acc);
-        }
-        sr = acc.r;
-        si = acc.i;
-        if (!team_sum<kChipBlock>(sr, si, tm, ++gen, sh))
-            return;
-    }
-    if (active) {
-        unsigned t16 = tid * 16u;
-        asm volatile("" : "+v"(t16));  // offsets computed again, not kept in registers since the loads
-#pragma unroll
-        for (int r = 0; r < RE; ++r)
-            bstore16<kBufNT>(X::vec(x[r]), rs, at(r, t16));
-#pragma unroll 4
-        for (int r = RE; r < NE; ++r)
-            bstore16<kBufNT>(mine[(r - RE) * kChipBlock], rs, at(r, t16));
-    }
+    const uint64_t base = uint64_t(rank) * a.per;
+    (void)held_run<T, U32, kWide, NE, RE, kChipBlock, true>(
+        static_cast<V *>(a.state) + base, base, a.per, a.marks, a.m, a.iters, a.scale, V{}, held + threadIdx.x,
+        [&]() { return !__syncthreads_or(error != 0u); },
+        [&](double &r, double &i) { return team_sum<kChipBlock>(r, i, tm, ++gen, sh); });
 }
 
 template <class T, bool U32>

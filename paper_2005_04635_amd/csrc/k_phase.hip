@@ -31,6 +31,8 @@ namespace grover {
 namespace {
 
 constexpr int kPV = 6;  // values a barrier reduces
+constexpr int kStreamBlock = 1024;
+constexpr int kStreamUnroll = kStreamTile / kStreamBlock;  // 16-byte vectors per thread per tile
 
 struct C2 {
     double re, im;
@@ -195,7 +197,7 @@ __device__ inline bool tile_marked(const PhaseArgs &a, const uint32_t *table, bo
 __device__ inline bool build_phase_table(const PhaseArgs &a, const PhaseTeam &tm, uint32_t *table)
 {
     const Share<C64> share{nullptr, a.nvec, a.marks, a.m, tm.rank, tm.size};
-    return build_mark_table(share, table);
+    return build_mark_table<kStreamBlock>(share, table);
 }
 
 // Forward pass over a team's share.  mode 0: write the uniform state; mode 1: c' = alpha - O(phi) c.

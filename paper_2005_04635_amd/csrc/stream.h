@@ -10,9 +10,7 @@
 
 namespace grover {
 
-constexpr int kStreamBlock = 1024;  // one workgroup per CU: fewest barrier participants, 16 waves per CU
-constexpr int kStreamUnroll = 4;    // 16-byte vectors per thread per tile
-constexpr int kStreamTile = kStreamBlock * kStreamUnroll;
+constexpr int kStreamTile = 4096;   // 16-byte vectors per tile: kStreamTile / B per thread of a B-thread workgroup
 constexpr int kMarkWords = 1024;    // LDS bitmap of a workgroup's tiles that hold marked amplitudes
 constexpr int kTileMarks = 8;       // marks of one tile held in registers
 
@@ -38,9 +36,8 @@ struct Team {
 // 32 bits of the value and the barrier generation (mod 2^32).  A reader that sees the current tag in both has
 // both halves of this generation's value, and no memory fence (which on this GPU writes back or invalidates a
 // whole L2) is needed to order the value against a separate flag.  Slots are zeroed before a launch and
-// generations start at 1.  Device-scope (sc1) 16-byte buffer accesses; the loads are volatile.
-constexpr int kBufDevice = 16;                            // sc1
-constexpr int kBufDeviceVolatile = 16 | int(0x80000000);  // sc1, and never hoisted or merged by the compiler
+// generations start at 1.  Device-scope (sc1) 16-byte buffer accesses.
+constexpr int kBufDevice = 16;  // sc1
 
 __device__ inline void put_value(__amdgpu_buffer_rsrc_t slots, uint32_t off, double x, uint32_t tag)
 {
@@ -55,27 +52,43 @@ __device__ inline void put_value(__amdgpu_buffer_rsrc_t slots, uint32_t off, dou
 
 // Bounded wait for NV values of generation `tag`, value q at byte offset off + q * stride: the loads of a
 // round are issued together.  Gives up when the error word is set or the wall-clock limit passes (then
-// setting the error word); both are looked at in the first and every 16th unsuccessful round only.
+// setting the error word); both are looked at in the first round and every 16th, the error word by a load
+// issued with that round's others (on its own it would add a memory round trip to nearly every barrier: the
+// first round mostly comes too early).  The clock is first read in the 16th round, for the same reason: the
+// limit counts from there, and a limit of zero gives up in the first round.
 template <int NV>
 __device__ inline bool wait_values(__amdgpu_buffer_rsrc_t slots, uint32_t off, uint32_t stride, uint32_t tag,
                                    uint32_t *error, uint64_t timeout_ticks, double (&x)[NV])
 {
-    const uint64_t t0 = wall_clock64();
+    uint64_t t0 = 0;
+    const auto error_word = buffer_rsrc(error, 4u);
     u32x4 w[NV];
     for (unsigned round = 0;; ++round) {
+        const bool look = (round & 15u) == 0u;
+        uint32_t failed = 0u;
         bool ready = true;
+        asm volatile("" ::: "memory");  // the loads are of this round (volatile ones would be of system scope)
 #pragma unroll
         for (int q = 0; q < NV; ++q)
-            w[q] = __builtin_amdgcn_raw_buffer_load_b128(slots, off + uint32_t(q) * stride, 0, kBufDeviceVolatile);
+            w[q] = __builtin_amdgcn_raw_buffer_load_b128(slots, off + uint32_t(q) * stride, 0, kBufDevice);
+        if (look)
+            failed = __builtin_amdgcn_raw_buffer_load_b32(error_word, 0u, 0, kBufDevice);
 #pragma unroll
         for (int q = 0; q < NV; ++q)
             ready = ready && w[q].x == tag && w[q].z == tag;
         if (ready)
             break;
-        if ((round & 15u) == 0u) {
-            if (__hip_atomic_load(error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
+        if (look) {
+            if (failed != 0u)
                 return false;
-            if (uint64_t(wall_clock64()) - t0 > timeout_ticks) {
+            bool late = timeout_ticks == 0u;
+            if (round >= 16u) {
+                const uint64_t now = wall_clock64();
+                if (round == 16u)
+                    t0 = now;
+                late = late || now - t0 > timeout_ticks;
+            }
+            if (late) {
                 __hip_atomic_store(error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 return false;
             }
@@ -87,13 +100,22 @@ __device__ inline bool wait_values(__amdgpu_buffer_rsrc_t slots, uint32_t off, u
     return true;
 }
 
+// This thread's index in the workgroup, computed afresh: what is derived from it (lane masks, slot offsets) is
+// then recomputed at each barrier in a few instructions instead of being kept in registers across the sweep, where
+// it costs held state or spills.
+__device__ inline unsigned fresh_tid()
+{
+    unsigned t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // Adds the wave values that `red` holds (re of waves 0 .. W-1, then im): lane W - 1 gets the sum of re, lane
 // 2 W - 1 that of im.  Called by one whole wave.
 template <int B>
-__device__ inline double add_wave_values(const double *red)
+__device__ inline double add_wave_values(const double *red, unsigned lane)
 {
     constexpr unsigned W = B / kWave;
-    const unsigned lane = threadIdx.x % kWave;
     double p = lane < 2 * W ? red[lane] : 0.0;
     if (W > 1)
         p += dpp_row_shifted<0x111>(p);
@@ -108,9 +130,9 @@ __device__ inline double add_wave_values(const double *red)
 
 // Each wave's sums of (re, im) into red.
 template <int B>
-__device__ inline void put_wave_values(double xr, double xi, double *red)
+__device__ inline void put_wave_values(double xr, double xi, double *red, unsigned tid)
 {
-    const unsigned lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const unsigned lane = tid % kWave, wave = tid / kWave;
     const double v = half_totals(fold_pair(xr, xi));
     if (lane == 31)
         red[wave] = v;
@@ -126,9 +148,10 @@ template <int B>
 __device__ inline void block_allsum(double &a, double &b, unsigned parity, TeamShared<B> &sh)
 {
     double *red = sh.red[parity & 1u];
-    put_wave_values<B>(a, b, red);
+    const unsigned tid = fresh_tid();
+    put_wave_values<B>(a, b, red, tid);
     __syncthreads();
-    const double p = add_wave_values<B>(red);
+    const double p = add_wave_values<B>(red, tid % kWave);
     a = lane_value(p, B / kWave - 1);
     b = lane_value(p, 2 * (B / kWave) - 1);
 }
@@ -159,11 +182,11 @@ __device__ bool team_sum(double &xr, double &xi, const Team &tm, uint64_t gen, T
 {
     constexpr unsigned W = B / kWave;
     const uint32_t tag = uint32_t(gen);
-    const unsigned lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const unsigned tid = fresh_tid(), lane = tid % kWave, wave = tid / kWave;
     // sh.red[0] is read by wave 0 only between the two workgroup barriers below; a wave writes it again only
     // in the next call, after the second.  sh.sum and sh.failed are written again only after the first barrier
     // of the next call, which every thread reaches after reading them here.
-    put_wave_values<B>(xr, xi, sh.red[0]);
+    put_wave_values<B>(xr, xi, sh.red[0], tid);
     __syncthreads();
     if (wave == 0) {
         const unsigned stride = team_stride(tm.size);
@@ -173,7 +196,7 @@ __device__ bool team_sum(double &xr, double &xi, const Team &tm, uint64_t gen, T
         const unsigned pos = two ? (tm.rank % groups) * per_group + tm.rank / groups : tm.rank;
         uint64_t *set = tm.partials + uint64_t(gen & 1u) * tm.size * (stride / 8u);
         const auto slots = buffer_rsrc(set, tm.size * stride);
-        const double p = add_wave_values<B>(sh.red[0]);
+        const double p = add_wave_values<B>(sh.red[0], lane);
         if (lane == W - 1u || lane == 2u * W - 1u)
             put_value(slots, pos * stride + (lane == W - 1u ? 0u : 16u), p, tag);
         double v = 0.0;
@@ -183,10 +206,19 @@ __device__ bool team_sum(double &xr, double &xi, const Team &tm, uint64_t gen, T
                                           groups * uint32_t(kGroupWords) * 8u);
             const unsigned m = lane & 31u;
             double x[1] = {0.0};
-            if (tm.rank < groups) {  // the group's first member; per_group <= 32
-                if (m < per_group)
-                    ok = wait_values<1>(slots, (pos + m) * stride + part, 0u, tag, &tm.sync->error, tm.timeout_ticks, x);
-                const double g = half_totals(x[0]);
+            if (tm.rank < groups) {  // the group's first member; per_group <= 64
+                double g = 0.0;
+                if (per_group <= 32u) {
+                    if (m < per_group)
+                        ok = wait_values<1>(slots, (pos + m) * stride + part, 0u, tag, &tm.sync->error, tm.timeout_ticks, x);
+                    g = x[0];
+                } else {
+                    double y[2] = {0.0, 0.0};
+                    if (lane < per_group)
+                        ok = wait_values<2>(slots, (pos + lane) * stride, 16u, tag, &tm.sync->error, tm.timeout_ticks, y);
+                    g = fold_pair(y[0], y[1]);
+                }
+                g = half_totals(g);
                 const bool all_ok = __all(ok);
                 if (m == 31u && all_ok)
                     put_value(sums, tm.rank * uint32_t(kGroupWords) * 8u + part, g, tag);
@@ -275,15 +307,15 @@ struct Share {
 // Table of this workgroup's tiles that hold marked amplitudes (bit j = tile rank + j * size), built by the
 // whole workgroup.  Returns false when it cannot be used (too many tiles, or a marked list so long that
 // scanning it per workgroup costs more than checking every tile); every tile then takes the checked path.
-template <class T>
+template <int B, class T>
 __device__ bool build_mark_table(const Share<T> &sh, uint32_t *table)
 {
-    const bool use = sh.count() <= uint64_t(kMarkWords) * 32u && sh.m <= uint64_t(64) * kStreamBlock;
+    const bool use = sh.count() <= uint64_t(kMarkWords) * 32u && sh.m <= uint64_t(64) * B;
     if (use) {
-        for (unsigned w = threadIdx.x; w < kMarkWords; w += kStreamBlock)
+        for (unsigned w = threadIdx.x; w < kMarkWords; w += B)
             table[w] = 0u;
         __syncthreads();
-        for (uint64_t q = threadIdx.x; q < sh.m; q += kStreamBlock) {
+        for (uint64_t q = threadIdx.x; q < sh.m; q += B) {
             const uint64_t t = sh.marks[q] / T::EPV / kStreamTile;
             if (t % sh.size == sh.rank) {
                 const uint64_t j = t / sh.size;
@@ -302,11 +334,12 @@ enum PassMode { kAccumulate, kUpdate, kFill };
 // per-thread order of the sum is identical in all modes, so a fresh sum of a stored state equals, bit for
 // bit, the sum the pass that wrote it produced.  U32: the update in binary32 from 2S/N rounded to binary32
 // (complex64 storage only); otherwise in binary64.
-template <class T, class A, PassMode MODE, bool U32 = false>
+template <int B, class T, class A, PassMode MODE, bool U32 = false>
 __device__ inline void stream_pass(const Share<T> &sh, const uint32_t *table, bool use_table, double mr, double mi,
                                    const typename T::vec &fill, A &acc)
 {
     using V = typename T::vec;
+    constexpr int kUnroll = kStreamTile / B;
     const float mr32 = float(mr), mi32 = float(mi);
     auto update = [&](V &v, unsigned bits) {
         if constexpr (U32)
@@ -317,25 +350,37 @@ __device__ inline void stream_pass(const Share<T> &sh, const uint32_t *table, bo
     const unsigned tid = threadIdx.x;
     const uint64_t cnt = sh.count();
     uint64_t mp = 0;  // marked entries before this position lie in tiles already visited
+    auto plain = [&](uint64_t j) {  // a full tile without marked amplitudes
+        const uint64_t v0 = (sh.rank + j * sh.size) * kStreamTile;
+        return v0 + kStreamTile <= sh.nvec && !(use_table ? ((table[j >> 5] >> (j & 31)) & 1u) != 0u : sh.m > 0);
+    };
+    // The next plain tile's loads are issued before this one is updated: with 512 threads, two waves per SIMD are
+    // too few to keep loads in flight by themselves.
+    bool ahead = false;
+    V y[kUnroll];
     for (uint64_t j = 0; j < cnt; ++j) {
         const uint64_t t = sh.rank + j * sh.size;
         const uint64_t v0 = t * kStreamTile;
-        const bool full = v0 + kStreamTile <= sh.nvec;
-        const bool marked = use_table ? ((table[j >> 5] >> (j & 31)) & 1u) != 0u : sh.m > 0;
-        if (full && !marked) {
-            V x[kStreamUnroll];
+        if (plain(j)) {
+            V x[kUnroll];
             if (MODE != kFill) {
 #pragma unroll
-                for (int u = 0; u < kStreamUnroll; ++u)
-                    x[u] = load16<true>(sh.st + v0 + u * kStreamBlock + tid);
+                for (int u = 0; u < kUnroll; ++u)
+                    x[u] = ahead ? y[u] : load16<true>(sh.st + v0 + u * B + tid);
+                ahead = j + 1 < cnt && plain(j + 1);
+                if (ahead) {
+#pragma unroll
+                    for (int u = 0; u < kUnroll; ++u)
+                        y[u] = load16<true>(sh.st + v0 + sh.size * kStreamTile + u * B + tid);
+                }
             }
 #pragma unroll
-            for (int u = 0; u < kStreamUnroll; ++u) {
+            for (int u = 0; u < kUnroll; ++u) {
                 if (MODE == kUpdate) {
                     update(x[u], 0u);
-                    store16<true>(x[u], sh.st + v0 + u * kStreamBlock + tid);
+                    store16<true>(x[u], sh.st + v0 + u * B + tid);
                 } else if (MODE == kFill) {
-                    store16<true>(fill, sh.st + v0 + u * kStreamBlock + tid);
+                    store16<true>(fill, sh.st + v0 + u * B + tid);
                     accum_vec<T>(fill, 0u, acc);
                 } else {
                     accum_vec<T>(x[u], 0u, acc);
@@ -351,16 +396,16 @@ __device__ inline void stream_pass(const Share<T> &sh, const uint32_t *table, bo
 #pragma unroll
             for (int q = 0; q < kTileMarks; ++q)
                 mk[q] = in_regs && mp + q < mq ? sh.marks[mp + q] : ~uint64_t(0);
-            V x[kStreamUnroll];
+            V x[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kStreamUnroll; ++u) {
-                const uint64_t v = v0 + u * kStreamBlock + tid;
+            for (int u = 0; u < kUnroll; ++u) {
+                const uint64_t v = v0 + u * B + tid;
                 if (v < sh.nvec)
                     x[u] = MODE == kFill ? fill : load16<true>(sh.st + v);
             }
 #pragma unroll
-            for (int u = 0; u < kStreamUnroll; ++u) {
-                const uint64_t v = v0 + u * kStreamBlock + tid;
+            for (int u = 0; u < kUnroll; ++u) {
+                const uint64_t v = v0 + u * B + tid;
                 if (v < sh.nvec) {
                     const unsigned bits = in_regs ? bits_from_regs<T::EPV>(mk, v * T::EPV)
                                                   : marked_bits<T::EPV>(sh.marks, mp, mq, v * T::EPV);
