@@ -28,6 +28,7 @@ struct grover_phase {
     uint32_t team = 1;                           // workgroups per schedule, streamed form
     uint32_t form = GROVER_PHASE_FORM_AUTO;      // as chosen by grover_phase_set_form
     uint32_t held_team_f = 0, held_team_a = 0;   // on-chip form: workgroups per schedule (0: does not fit)
+    bool rest[2] = {false, false};               // ... and whether a wave holds marks in several rows
     uint64_t timeout_ticks = 0;
     bool forward_done = false;
     size_t device_bytes = 0;
@@ -126,6 +127,12 @@ int check_barriers(grover_phase *p)
     return GROVER_OK;
 }
 
+// Vectors a workgroup of the on-chip kernels holds for this state size.
+uint64_t held_vecs(const grover_phase *p, bool adjoint)
+{
+    return std::min<uint64_t>(p->nvec, adjoint ? kPhaseHeldAdjointVecs : kPhaseHeldForwardVecs);
+}
+
 // The teams wait on each other, so the grid must be co-resident: confirmed on the device with one barrier
 // of the whole grid under a short wait limit (shrinking on a time-out), as for the other persistent kernels.
 int select_grid(grover_phase *p, int clock_khz)
@@ -134,7 +141,9 @@ int select_grid(grover_phase *p, int clock_khz)
     for (bool held : {false, true})
         for (bool adjoint : {false, true}) {
             int pc = 0;
-            PHASE_HIP(p, hipOccupancyMaxActiveBlocksPerMultiprocessor(&pc, phase_kernel_fn(adjoint, held), 1024, 0),
+            PHASE_HIP(p,
+                      hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                          &pc, phase_kernel_fn(adjoint, held, held_vecs(p, adjoint), p->rest[adjoint]), int(phase_block(held)), 0),
                       "occupancy");
             per_cu = std::min(per_cu, pc);
         }
@@ -155,6 +164,8 @@ int select_grid(grover_phase *p, int clock_khz)
         for (uint32_t held : {0u, 1u})
             for (bool adjoint : {false, true}) {  // each launch zeroes the barriers first: check after each
                 L.held = held;
+                L.per = held_vecs(p, adjoint);
+                L.rest = p->rest[adjoint];
                 PHASE_HIP(p, launch_phase(L, adjoint), "phase grid check");
                 ok = ok && check_barriers(p) == GROVER_OK;
             }
@@ -197,6 +208,8 @@ int run(grover_phase *p, bool adjoint, const double *dloss, double *loss, double
     if (use_held(p)) {
         L.held = 1;
         L.team_size = adjoint ? p->held_team_a : p->held_team_f;
+        L.per = p->nvec / L.team_size;
+        L.rest = p->rest[adjoint];
     }
     L.loss = loss;
     L.dloss = dloss;
@@ -282,6 +295,8 @@ int grover_phase_init(grover_phase **out, const grover_phase_config *cfg, void *
             status = phip(p, e, "phase allocation");
             throw status;
         }
+        for (bool adjoint : {false, true})
+            p->rest[adjoint] = phase_rest(p->marks, held_vecs(p, adjoint));
         status = select_grid(p, clock_khz);
         if (status != GROVER_OK)
             throw status;

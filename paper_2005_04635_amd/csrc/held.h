@@ -109,14 +109,64 @@ struct MarkBits {
     }
 };
 
+// Where a wave of a B-thread member finds its marked amplitudes.  Position r of a thread holds vector e = r ^ swap,
+// swap the same in every lane of a wave and chosen so that the wave's first marked vector is at position 0: the
+// few instructions for marks are then spent on position 0 alone, unless the wave holds marks in other rows too
+// (in_rest, a bit per position).
+template <int NE, int B, int EPV>
+struct WaveMarks {
+    MarkBits<NE> mk{};
+    unsigned swap = 0u;
+    unsigned any = 0u;  // this wave holds marked amplitudes (the same in every lane, as swap and rest)
+    uint32_t rest_lo = 0u, rest_hi = 0u;
+    __device__ inline bool in_rest(int r) const { return ((r < 32 ? rest_lo >> r : rest_hi >> (r - 32)) & 1u) != 0u; }
+    __device__ inline bool has_rest() const { return (rest_lo | rest_hi) != 0u; }
+    // from the sorted list marks[0, m), for the vectors [base, base + per) of the member
+    __device__ inline void find(const uint64_t *marks, uint64_t m, uint64_t base, uint64_t per)
+    {
+        const unsigned tid = threadIdx.x, wave = tid / kWave;
+        const uint64_t lo = m > 0 ? lower_bound_u64(marks, 0, m, base * EPV) : 0;
+        const uint64_t hi = m > 0 ? lower_bound_u64(marks, lo, m, (base + per) * EPV) : 0;
+        bool marked = false;
+        uint64_t rest = 0;
+        if (hi - lo <= uint64_t(B)) {
+            for (uint64_t i = lo; i < hi; ++i) {
+                const uint64_t x = marks[i];
+                const unsigned v = unsigned(x / EPV - base), e = v / B, owner = v % B;
+                if (owner / kWave == wave) {
+                    if (!marked)
+                        swap = e;
+                    marked = true;
+                    const unsigned r = e ^ swap;
+                    if (owner == tid)
+                        mk.set(r, 1u << unsigned(x % EPV));
+                    rest |= r > 0u ? uint64_t(1) << r : 0u;
+                }
+            }
+        } else {
+            const bool active = NE > 1 || tid < per;
+#pragma unroll 1
+            for (unsigned r = 0; r < unsigned(NE); ++r) {
+                const unsigned b = active ? marked_bits<EPV>(marks, lo, hi, (base + uint64_t(r) * B + tid) * EPV) : 0u;
+                mk.set(r, b);
+                if (__any(b != 0u)) {
+                    marked = true;
+                    rest |= r > 0u ? uint64_t(1) << r : 0u;
+                }
+            }
+        }
+        // the same in every lane of a wave: kept in scalar registers
+        swap = __builtin_amdgcn_readfirstlane(swap);
+        any = __builtin_amdgcn_readfirstlane(marked ? 1u : 0u);
+        rest_lo = __builtin_amdgcn_readfirstlane(uint32_t(rest));
+        rest_hi = __builtin_amdgcn_readfirstlane(uint32_t(rest >> 32));
+    }
+};
+
 // All iterations of one member's share, and the store back.  The state is loaded (kLoad) or starts as `fill`;
 // its oracle-signed sum is formed in the order the iterations add theirs, so consecutive calls compose bit for
 // bit.  `begin` is asked once, by the whole workgroup, before the first sum; `reduce` is the team's (or the
 // workgroup's) sum.  Returns false, nothing stored, when either says so.  `mine`: the thread's LDS slots, B apart.
-//
-// Position r of a thread holds vector e = r ^ swap, swap the same in every lane of a wave and chosen so that the
-// wave's first marked vector is at position 0: the few instructions for marks are then spent on position 0
-// alone, unless the wave holds marks in other rows too (`rest`, a bit per position).
 template <class T, bool U32, bool WIDE, int NE, int RE, int B, bool kLoad, class Begin, class Reduce>
 __device__ __forceinline__ bool held_run(typename T::vec *st, uint64_t base, uint64_t per, const uint64_t *marks,
                                          uint64_t m, uint64_t iters, double scale, const typename T::vec &fill,
@@ -126,66 +176,30 @@ __device__ __forceinline__ bool held_run(typename T::vec *st, uint64_t base, uin
     using V = typename T::vec;
     constexpr int LE = NE - RE;
     static_assert(LE == 0 || (LE <= 16 && RE % 16 + LE <= 16), "the LDS positions' marked bits lie in one word");
-    const unsigned tid = threadIdx.x, wave = tid / kWave;
+    const unsigned tid = threadIdx.x;
     const bool active = NE > 1 || tid < per;
-
-    // this member's slice of the sorted marked list, and from it the wave's swap and the threads' marked bits
-    const uint64_t lo = m > 0 ? lower_bound_u64(marks, 0, m, base * T::EPV) : 0;
-    const uint64_t hi = m > 0 ? lower_bound_u64(marks, lo, m, (base + per) * T::EPV) : 0;
-    MarkBits<NE> mk{};
-    unsigned swap = 0u;
-    bool marked = false;  // this wave holds marked amplitudes (the same in every lane)
-    uint64_t rest = 0;    // positions above 0 that hold marks in some lane of this wave
-    if (hi - lo <= uint64_t(B)) {
-        for (uint64_t i = lo; i < hi; ++i) {
-            const uint64_t x = marks[i];
-            const unsigned v = unsigned(x / T::EPV - base), e = v / B, owner = v % B;
-            if (owner / kWave == wave) {
-                if (!marked)
-                    swap = e;
-                marked = true;
-                const unsigned r = e ^ swap;
-                if (owner == tid)
-                    mk.set(r, 1u << unsigned(x % T::EPV));
-                rest |= r > 0u ? uint64_t(1) << r : 0u;
-            }
-        }
-    } else {
-#pragma unroll 1
-        for (unsigned r = 0; r < unsigned(NE); ++r) {
-            const unsigned b = active ? marked_bits<T::EPV>(marks, lo, hi, (base + uint64_t(r) * B + tid) * T::EPV) : 0u;
-            mk.set(r, b);
-            if (__any(b != 0u)) {
-                marked = true;
-                rest |= r > 0u ? uint64_t(1) << r : 0u;
-            }
-        }
-    }
-    // the same in every lane of a wave: kept in scalar registers
-    swap = __builtin_amdgcn_readfirstlane(swap);
-    const unsigned is_marked = __builtin_amdgcn_readfirstlane(marked ? 1u : 0u);
-    const uint32_t rest_lo = __builtin_amdgcn_readfirstlane(uint32_t(rest)), rest_hi = __builtin_amdgcn_readfirstlane(uint32_t(rest >> 32));
-    auto in_rest = [&](int r) { return ((r < 32 ? rest_lo >> r : rest_hi >> (r - 32)) & 1u) != 0u; };
-    const bool has_rest = (rest_lo | rest_hi) != 0u;
+    WaveMarks<NE, B, T::EPV> wm;
+    wm.find(marks, m, base, per);
+    const bool has_rest = wm.has_rest();
 
     typename X::H x[RE][X::parts];
     // byte offset of position r's vector in this member's share
     const auto rs = buffer_rsrc(st, uint32_t(per * 16u));
-    auto at = [&](unsigned r, unsigned t16) { return (r ^ swap) * unsigned(B * 16) + t16; };
+    auto at = [&](unsigned r, unsigned t16) { return (r ^ wm.swap) * unsigned(B * 16) + t16; };
     AccF64 acc0;
     auto correct_all = [&](AccF64 &acc) {
-        X::correct(x[0], mk.at(0), acc);
+        X::correct(x[0], wm.mk.at(0), acc);
         if (has_rest) {
 #pragma unroll
             for (int r = 1; r < RE; ++r)
-                if (in_rest(r))
-                    X::correct(x[r], mk.at(r), acc);
+                if (wm.in_rest(r))
+                    X::correct(x[r], wm.mk.at(r), acc);
 #pragma unroll 1
             for (int r = RE; r < NE; ++r)
-                if (in_rest(r)) {
+                if (wm.in_rest(r)) {
                     typename X::H y[X::parts];
                     X::get(mine[(r - RE) * B], y);
-                    X::correct(y, mk.in_lds(r), acc);
+                    X::correct(y, wm.mk.in_lds(r), acc);
                 }
         }
     };
@@ -205,7 +219,7 @@ __device__ __forceinline__ bool held_run(typename T::vec *st, uint64_t base, uin
             X::get(mine[(r - RE) * B], y);
             X::add(y, acc0);
         }
-        if (is_marked)
+        if (wm.any)
             correct_all(acc0);
     }
     double sr = acc0.r, si = acc0.i;
@@ -216,19 +230,19 @@ __device__ __forceinline__ bool held_run(typename T::vec *st, uint64_t base, uin
         const float mr32 = float(mr), mi32 = float(mi);
         AccF64 acc;
         if (active) {
-            if (is_marked) {
-                X::negate(x[0], mk.at(0));
+            if (wm.any) {
+                X::negate(x[0], wm.mk.at(0));
                 if (has_rest) {
 #pragma unroll
                     for (int r = 1; r < RE; ++r)
-                        if (in_rest(r))
-                            X::negate(x[r], mk.at(r));
+                        if (wm.in_rest(r))
+                            X::negate(x[r], wm.mk.at(r));
 #pragma unroll 1
                     for (int r = RE; r < NE; ++r)
-                        if (in_rest(r)) {
+                        if (wm.in_rest(r)) {
                             typename X::H y[X::parts];
                             X::get(mine[(r - RE) * B], y);
-                            X::negate(y, mk.in_lds(r));
+                            X::negate(y, wm.mk.in_lds(r));
                             mine[(r - RE) * B] = X::vec(y);
                         }
                 }
@@ -243,7 +257,7 @@ __device__ __forceinline__ bool held_run(typename T::vec *st, uint64_t base, uin
                 X::step(y, mr, mi, mr32, mi32, acc);
                 mine[(r - RE) * B] = X::vec(y);
             }
-            if (is_marked)
+            if (wm.any)
                 correct_all(acc);
         }
         sr = acc.r;

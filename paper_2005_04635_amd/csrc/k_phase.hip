@@ -24,8 +24,11 @@
 // Storage is complex64 (float re, im); phases, sums and the element arithmetic are binary64.  A team of
 // `team_size` workgroups iterates one schedule at a time, with one team barrier per iteration that also
 // reduces six binary64 values; teams take schedules b = team, team + teams, ...
+#include <algorithm>
+#include <iterator>
+
+#include "held.h"
 #include "phase.h"
-#include "stream.h"
 
 namespace grover {
 namespace {
@@ -41,8 +44,8 @@ struct C2 {
 __device__ inline C2 cmul(C2 a, C2 b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
 
 struct PhaseShared {
-    double red[8 * (kStreamBlock / kWave)];  // wave sums, a row of 16 per value (two groups of four)
-    double sum[8];
+    double red[kPV * (kStreamBlock / kWave)];  // wave sums, value by value
+    double sum[kPV];
     int failed;
 };
 
@@ -60,66 +63,82 @@ struct PhaseTeam {
 // all members compute identical sums.  Slots are double-buffered by parity (a slot is rewritten two generations
 // later, after every member has read it).  Every thread gets the sums; false when the wait gave up.
 //
-// The values travel four at a time through a wave's rows of 16 lanes: a wave's four sums take one fold and four
-// row shifts together, the workgroup's 16 wave values of a value lie in one row, and a row gathers one value of
-// the members, 16 at a time and four of those together.  LDS words are written again only after the first
-// workgroup barrier of the next call, which every thread reaches after reading them.
-template <int NV = kPV>
-__device__ bool team_sum_n(double (&v)[kPV], const PhaseTeam &tm, uint64_t gen, PhaseShared &sh)
+// The first four values travel together through a wave's rows of 16 lanes: a wave's four sums take one fold and
+// four row shifts, the workgroup's wave values of a value lie in one row, and a row gathers one value of 64
+// members with four loads per lane.  Further values (only the marked amplitudes contribute to them: a wave that
+// holds none passes `more` false and skips their sums) take one load per lane each, waited for together with the
+// others.  LDS words are written again only after the first workgroup barrier of the next call, which every
+// thread reaches after reading them.
+template <int B, int NV>
+__device__ bool team_sum_n(double (&v)[kPV], const PhaseTeam &tm, uint64_t gen, PhaseShared &sh, bool more = true)
 {
-    static_assert(NV >= 1 && NV <= kPV && kPV <= 8, "values per barrier");
-    constexpr int kGroups = (NV + 3) / 4;
-    constexpr unsigned kW = kStreamBlock / kWave;
-    static_assert(kW == 16, "a row per value");
+    static_assert(NV >= 4 && NV <= kPV, "values per barrier");
+    constexpr int kMore = NV - 4;
+    constexpr unsigned kW = B / kWave;
+    static_assert(kW == 8 || kW == 16, "a row per value");
     const uint32_t tag = uint32_t(gen);
-    const unsigned lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const unsigned tid = fresh_tid(), lane = tid % kWave, wave = tid / kWave;
     const unsigned row = lane / 16u, in_row = lane % 16u;
-    // the value of a row within its group of four (fold_quad's order)
-    const unsigned of_row = (row & 1u) * 2u + (row >> 1);
-#pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
-        auto val = [&](int q) { return 4 * g + q < NV ? v[4 * g + q < kPV ? 4 * g + q : 0] : 0.0; };
-        const double t = row_totals(fold_quad(val(0), val(1), val(2), val(3)));
+    const unsigned q = (row & 1u) * 2u + (row >> 1);  // the value of a row (fold_quad's order)
+    {
+        const double t = row_totals(fold_quad(v[0], v[1], v[2], v[3]));
         if (in_row == 15u)
-            sh.red[(4u * g + of_row) * kW + wave] = t;
+            sh.red[q * kW + wave] = t;
+    }
+    if constexpr (kMore > 0) {
+        double t = 0.0;
+        if (more)
+            t = half_totals(fold_pair(v[4], kMore > 1 ? v[kPV - 1] : 0.0));
+        if (lane == 31u)
+            sh.red[4u * kW + wave] = t;
+        if (kMore > 1 && lane == 63u)
+            sh.red[5u * kW + wave] = t;
     }
     __syncthreads();
     if (wave == 0) {
         const auto slots = buffer_rsrc(tm.partials + uint64_t(gen & 1u) * tm.size * 16u, tm.size * 128u);
-        bool ok = true;
-#pragma unroll
-        for (int g = 0; g < kGroups; ++g) {
-            const unsigned q = 4u * g + of_row;
-            const double t = row_totals(sh.red[q * kW + in_row]);
-            if (in_row == 15u && q < unsigned(NV))
+        {
+            const double t = row_totals(in_row < kW ? sh.red[q * kW + in_row] : 0.0);
+            if (in_row == 15u)
                 put_value(slots, tm.rank * 128u + q * 16u, t, tag);
         }
+        if constexpr (kMore > 0) {
+            const double t = row_totals(row < unsigned(kMore) && in_row < kW ? sh.red[(4u + row) * kW + in_row] : 0.0);
+            if (in_row == 15u && row < unsigned(kMore))
+                put_value(slots, tm.rank * 128u + (4u + row) * 16u, t, tag);
+        }
+        bool ok = true;
+        double w = 0.0, u[2] = {0.0, 0.0};
+        for (unsigned m0 = 0; m0 < tm.size && ok; m0 += kWave) {
+            uint32_t off[4 + kMore];
+            bool use[4 + kMore];
+            double x[4 + kMore];
 #pragma unroll
-        for (int g = 0; g < kGroups; ++g) {
-            const unsigned q = 4u * g + of_row;
-            double w = 0.0;
-            for (unsigned m = in_row; m < tm.size && ok; m += 64u) {
-                // members m, m + 16, m + 32, m + 48: a team's size is mostly a power of two
-                double x[4] = {0.0, 0.0, 0.0, 0.0};
-                if (q < unsigned(NV)) {
-                    if (m + 48u < tm.size) {
-                        ok = wait_values<4>(slots, m * 128u + q * 16u, 16u * 128u, tag, &tm.sync->error, tm.timeout_ticks, x);
-                    } else {
-#pragma unroll
-                        for (unsigned i = 0; i < 3u; ++i) {
-                            double y[1] = {0.0};
-                            if (ok && m + 16u * i < tm.size)
-                                ok = wait_values<1>(slots, (m + 16u * i) * 128u + q * 16u, 0u, tag, &tm.sync->error,
-                                                    tm.timeout_ticks, y);
-                            x[i] = y[0];
-                        }
-                    }
-                }
-                w += (x[0] + x[1]) + (x[2] + x[3]);
+            for (unsigned i = 0; i < 4u; ++i) {
+                const unsigned m = m0 + in_row + 16u * i;
+                off[i] = m * 128u + q * 16u;
+                use[i] = m < tm.size;
             }
-            w = row_totals(w);
-            if (in_row == 15u && q < unsigned(NV))
-                sh.sum[q] = w;
+#pragma unroll
+            for (unsigned i = 0; i < unsigned(kMore); ++i) {
+                off[4 + i] = (m0 + lane) * 128u + (4u + i) * 16u;
+                use[4 + i] = m0 + lane < tm.size;
+            }
+            ok = wait_offsets<4 + kMore>(slots, off, use, tag, &tm.sync->error, tm.timeout_ticks, x);
+            w += (x[0] + x[1]) + (x[2] + x[3]);
+#pragma unroll
+            for (int i = 0; i < kMore; ++i)
+                u[i] += x[4 + i];
+        }
+        w = row_totals(w);
+        if (in_row == 15u)
+            sh.sum[q] = w;
+        if constexpr (kMore > 0) {
+            const double t = half_totals(fold_pair(u[0], u[1]));
+            if (lane == 31u)
+                sh.sum[4] = t;
+            if (lane == 63u)
+                sh.sum[5] = t;
         }
         const bool failed = __any(!ok);
         if (lane == 0)
@@ -127,8 +146,8 @@ __device__ bool team_sum_n(double (&v)[kPV], const PhaseTeam &tm, uint64_t gen, 
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < NV; ++q)
-        v[q] = sh.sum[q];
+    for (int i = 0; i < NV; ++i)
+        v[i] = sh.sum[i];
     return sh.failed == 0;
 }
 
@@ -139,6 +158,7 @@ struct PhaseArgs {
     const uint64_t *marks;
     uint64_t m;
     uint64_t nvec;
+    uint64_t per;  // on-chip form: vectors per member
     double N;
     float amp;  // uniform amplitude rounded to binary32
     uint32_t B, K, every, nck;
@@ -272,7 +292,7 @@ __global__ __launch_bounds__(kStreamBlock) void phase_forward_kernel(PhaseArgs a
     uint64_t gen = 0;
     if (a.probe) {
         double v[kPV] = {};
-        (void)team_sum_n(v, tm, ++gen, sh);
+        (void)team_sum_n<kStreamBlock, kPV>(v, tm, ++gen, sh);
         return;
     }
     const bool use_table = build_phase_table(a, tm, table);
@@ -280,7 +300,7 @@ __global__ __launch_bounds__(kStreamBlock) void phase_forward_kernel(PhaseArgs a
         float4 *st = a.state + uint64_t(b) * a.nvec;
         double v[kPV] = {};
         forward_pass(a, st, nullptr, tm, table, use_table, 0, {0.0, 0.0}, {1.0, 0.0}, v);
-        if (!team_sum_n(v, tm, ++gen, sh))
+        if (!team_sum_n<kStreamBlock, kPV>(v, tm, ++gen, sh))
             return;
         for (uint32_t k = 1; k <= a.K; ++k) {
             const double ph = a.phi[uint64_t(b) * a.K + k - 1], th = a.theta[uint64_t(b) * a.K + k - 1];
@@ -294,7 +314,7 @@ __global__ __launch_bounds__(kStreamBlock) void phase_forward_kernel(PhaseArgs a
                              : nullptr;
             double w[kPV] = {};
             forward_pass(a, st, ck, tm, table, use_table, 1, alpha, ephi, w);
-            if (!team_sum_n(w, tm, ++gen, sh))
+            if (!team_sum_n<kStreamBlock, kPV>(w, tm, ++gen, sh))
                 return;
 #pragma unroll
             for (int q = 0; q < kPV; ++q)
@@ -426,7 +446,7 @@ __global__ __launch_bounds__(kStreamBlock) void phase_adjoint_kernel(PhaseArgs a
     uint64_t gen = 0;
     if (a.probe) {
         double v[kPV] = {};
-        (void)team_sum_n(v, tm, ++gen, sh);
+        (void)team_sum_n<kStreamBlock, kPV>(v, tm, ++gen, sh);
         return;
     }
     const bool leader = tm.rank == 0 && threadIdx.x == 0;
@@ -436,7 +456,7 @@ __global__ __launch_bounds__(kStreamBlock) void phase_adjoint_kernel(PhaseArgs a
         float4 *lam = a.lambda + uint64_t(b) * a.nvec;
         double v[kPV] = {};
         lambda_seed_pass(a, st, lam, tm, table, use_table, a.dloss[b], v);
-        if (!team_sum_n(v, tm, ++gen, sh))
+        if (!team_sum_n<kStreamBlock, kPV>(v, tm, ++gen, sh))
             return;
         C2 sc{a.aux[2u * b], a.aux[2u * b + 1u]}, sl{v[2], v[3]};
         for (uint32_t k = a.K; k >= 1; --k) {
@@ -454,7 +474,7 @@ __global__ __launch_bounds__(kStreamBlock) void phase_adjoint_kernel(PhaseArgs a
                                     : nullptr;
             double w[kPV] = {};
             reverse_pass(a, st, lam, src, anchor, tm, table, use_table, beta_c, beta_l, {cos(ph), sin(ph)}, w);
-            if (!team_sum_n(w, tm, ++gen, sh))
+            if (!team_sum_n<kStreamBlock, kPV>(w, tm, ++gen, sh))
                 return;
             if (leader)  // -2 Im(sum over marked of conj(nu) y)
                 a.dphi[pk] = -2.0 * w[5];
@@ -465,44 +485,18 @@ __global__ __launch_bounds__(kStreamBlock) void phase_adjoint_kernel(PhaseArgs a
 }
 
 // ------------------------------------------------------------------------------ on-chip form
-// For states small enough to stay on chip the same iteration and reverse sweep run with each state held in
-// its team's registers and LDS for all K steps, so that the only memory traffic is the checkpoints, the
-// final state and the reads of the checkpoints in the reverse sweep.  Team size T (a power of two, set by
-// the host from the state size): member `rank` owns the contiguous vectors [rank * per, (rank + 1) * per),
-// per = nvec / T, and thread tid the vectors rank * per + e * 1024 + tid, e < ne = per / 1024 (or, when
-// per < 1024, the one vector tid < per).  Forward: up to 16 vectors per thread, 8 in registers and 8 in
-// its own LDS slots.  Adjoint: up to 8 vectors of the state in registers and 8 of the adjoint state in LDS.
-// The marked set is the same for every schedule and step, so each thread finds the marked bits of its
-// vectors once per launch (two per vector, packed); threads without marks take a shorter update.
-constexpr int kHeldReg = 8;
-constexpr int kHeldLds = 8;
-
-struct HeldShare {
-    uint64_t base, per;
-    unsigned ne;
-    bool active;
-};
-
-__device__ inline HeldShare held_share(uint64_t nvec, const PhaseTeam &tm)
-{
-    HeldShare h;
-    h.per = nvec / tm.size;
-    h.base = uint64_t(tm.rank) * h.per;
-    h.ne = h.per >= kStreamBlock ? unsigned(h.per / kStreamBlock) : 1u;
-    h.active = threadIdx.x < h.per;
-    return h;
-}
-
-__device__ inline uint32_t held_mask(const PhaseArgs &a, const HeldShare &h)
-{
-    uint32_t mask = 0u;
-    if (h.active && a.m > 0)
-        for (unsigned e = 0; e < h.ne; ++e) {
-            const uint64_t v = h.base + uint64_t(e) * kStreamBlock + threadIdx.x;
-            mask |= uint32_t(marked_bits<2>(a.marks, 0, a.m, v * 2u)) << (2 * e);
-        }
-    return mask;
-}
+// For states small enough to stay on chip the same iteration and reverse sweep run with each state held in its
+// team's registers for all K steps, so that the only memory traffic is the checkpoints, the final state and the
+// reads of the checkpoints in the reverse sweep.  Team size T (a power of two, set by the host from the state
+// size): member `rank` owns the contiguous vectors [rank * per, (rank + 1) * per), per = nvec / T, and thread tid
+// the vectors rank * per + e * 512 + tid, e < NE = per / 512 (or, when per < 512, the one vector tid < per).
+// Forward: up to 32 vectors per thread; adjoint: up to 16 of the state and 16 of the adjoint state.  The marked
+// set is the same for every schedule and step, so each wave finds its marks once per launch (WaveMarks).
+//
+// What bounds a step is the update's instructions (five per part: 2.2 us with 32 vectors per thread) and the team
+// barrier (1.2-1.5 us).  512 threads rather than 1024 keep all held vectors in registers (half of them went through
+// LDS) and halve the waves that pay the reduction.
+constexpr int kHeldBlock = 512;
 
 // e^{i phi_k} and e^{i theta_k} of one schedule for a chunk of kTrigChunk steps, computed once by the
 // workgroup's threads (step k0 + i by thread i) into LDS instead of at every step by every thread: on chip a
@@ -518,7 +512,7 @@ struct TrigTable {
 
 __device__ inline void fill_trig(const PhaseArgs &a, uint32_t b, uint32_t k0, TrigTable &t)
 {
-    for (uint32_t i = threadIdx.x; i < kTrigChunk && k0 + i < a.K; i += kStreamBlock) {
+    for (uint32_t i = threadIdx.x; i < kTrigChunk && k0 + i < a.K; i += kHeldBlock) {
         const uint64_t pk = uint64_t(b) * a.K + k0 + i;
         double sp, cp, sth, cth;
         sincos(a.phi[pk], &sp, &cp);
@@ -531,71 +525,75 @@ __device__ inline void fill_trig(const PhaseArgs &a, uint32_t b, uint32_t k0, Tr
     __syncthreads();
 }
 
-// One forward step of one held vector: c' = alpha - O(phi) c; the stored values' sums go to w
-// ({sum, marked sum, marked |c|^2}, as forward_pass).  kMarks = false: the vector holds no marked amplitude.
-template <bool kMarks>
-__device__ inline void held_forward_vec(float4 &x, unsigned bits, C2 alpha, C2 ephi, double (&w)[kPV])
+// A held vector's four parts {re, im, re, im}.
+using Vec4 = float[4];
+
+__device__ inline void unpack(const float4 &v, Vec4 &x)
 {
-    if (!kMarks || bits == 0u) {
-        x.x = float(alpha.re - double(x.x));
-        x.y = float(alpha.im - double(x.y));
-        x.z = float(alpha.re - double(x.z));
-        x.w = float(alpha.im - double(x.w));
-        w[0] += double(x.x) + double(x.z);
-        w[1] += double(x.y) + double(x.w);
-        return;
-    }
-    C2 c0 = lo(x), c1 = hi(x);
-    if (bits & 1u)
-        c0 = cmul(ephi, c0);
-    if (bits & 2u)
-        c1 = cmul(ephi, c1);
-    x = pack({alpha.re - c0.re, alpha.im - c0.im}, {alpha.re - c1.re, alpha.im - c1.im});
-    const C2 r0 = lo(x), r1 = hi(x);
-    w[0] += r0.re + r1.re;
-    w[1] += r0.im + r1.im;
-    if (bits & 1u) {
-        w[2] += r0.re;
-        w[3] += r0.im;
-        w[4] += r0.re * r0.re + r0.im * r0.im;
-    }
-    if (bits & 2u) {
-        w[2] += r1.re;
-        w[3] += r1.im;
-        w[4] += r1.re * r1.re + r1.im * r1.im;
-    }
+    x[0] = v.x;
+    x[1] = v.y;
+    x[2] = v.z;
+    x[3] = v.w;
+}
+__device__ inline float4 packed(const Vec4 &x) { return make_float4(x[0], x[1], x[2], x[3]); }
+
+// A vector's parts into (sr, si).  The empty asm hides that the parts are still the values widened here: else the
+// compiler keeps all the widened values for the next step, which there are no registers for.  It takes the sums
+// too, so that the additions stay ahead of it and need no copies of the parts.
+__device__ inline void add_parts(Vec4 &x, double &sr, double &si)
+{
+    sr += double(x[0]) + double(x[2]);
+    si += double(x[1]) + double(x[3]);
+    asm("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(sr), "+v"(si));
 }
 
-// One forward step over a thread's held vectors (registers, then LDS), each also written to the checkpoint
-// `ck` (this member's part of it) when one is due.
-template <bool kMarks>
-__device__ inline void held_forward_sweep(float4 (&x)[kHeldReg], float4 *held, const HeldShare &h, uint32_t mask,
-                                          C2 alpha, C2 ephi, float4 *ck, double (&w)[kPV])
+// Makes the parts other values to the compiler in this branch, so that it does not merge the branch's widening
+// conversions with another branch's and compute all of them ahead of both.
+template <int NE>
+__device__ inline void own_values(Vec4 (&x)[NE])
 {
-    const unsigned tid = threadIdx.x;
 #pragma unroll
-    for (int e = 0; e < kHeldReg; ++e)
-        if (unsigned(e) < h.ne) {
-            held_forward_vec<kMarks>(x[e], (mask >> (2 * e)) & 3u, alpha, ephi, w);
-            if (ck)
-                store16<true>(x[e], ck + uint64_t(e) * kStreamBlock + tid);
-        }
-    if (h.ne > unsigned(kHeldReg)) {
+    for (int r = 0; r < NE; ++r)
 #pragma unroll
-        for (int e = 0; e < kHeldLds; ++e) {
-            float4 y = held[e * kStreamBlock + tid];
-            held_forward_vec<kMarks>(y, (mask >> (2 * (kHeldReg + e))) & 3u, alpha, ephi, w);
-            held[e * kStreamBlock + tid] = y;
-            if (ck)
-                store16<true>(y, ck + uint64_t(kHeldReg + e) * kStreamBlock + tid);
-        }
-    }
+        for (int p = 0; p < 4; ++p)
+            asm volatile("" : "+v"(x[r][p]));
 }
 
-__global__ __launch_bounds__(kStreamBlock) void phase_forward_held_kernel(PhaseArgs a)
+// One step of one vector without marked amplitudes: c' = m - c.
+__device__ inline void plain_step(Vec4 &x, C2 m, double &sr, double &si)
+{
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+        x[p] = float((p & 1 ? m.im : m.re) - double(x[p]));
+    add_parts(x, sr, si);
+}
+
+// One forward step of a vector that may hold marked amplitudes: c' = alpha - O(phi) c; the stored values' sums go to
+// w ({sum, marked sum, marked |c|^2}, as forward_pass).
+__device__ inline void marked_forward(Vec4 &x, unsigned bits, C2 alpha, C2 ephi, double (&w)[kPV])
+{
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const C2 c{double(x[2 * e]), double(x[2 * e + 1])};
+        const C2 o = (bits >> e) & 1u ? cmul(ephi, c) : c;
+        x[2 * e] = float(alpha.re - o.re);
+        x[2 * e + 1] = float(alpha.im - o.im);
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+        if ((bits >> e) & 1u) {
+            const C2 r{double(x[2 * e]), double(x[2 * e + 1])};
+            w[2] += r.re;
+            w[3] += r.im;
+            w[4] += r.re * r.re + r.im * r.im;
+        }
+    add_parts(x, w[0], w[1]);
+}
+
+template <int NE, bool kRest>
+__global__ __launch_bounds__(kHeldBlock) void phase_forward_held_kernel(PhaseArgs a)
 {
     __shared__ PhaseShared sh;
-    __shared__ float4 held[kHeldLds * kStreamBlock];
     __shared__ TrigTable trig;
     const unsigned T = a.team_size, teams = gridDim.x / T, team_id = xcd_major_block() / T;
     if (team_id >= teams)
@@ -605,42 +603,46 @@ __global__ __launch_bounds__(kStreamBlock) void phase_forward_held_kernel(PhaseA
     uint64_t gen = 0;
     if (a.probe) {
         double v[kPV] = {};
-        (void)team_sum_n(v, tm, ++gen, sh);
+        (void)team_sum_n<kHeldBlock, 4>(v, tm, ++gen, sh);
         return;
     }
     const unsigned tid = threadIdx.x;
-    const HeldShare h = held_share(a.nvec, tm);
-    const uint32_t mask = held_mask(a, h);
+    const uint64_t per = a.per, base = uint64_t(tm.rank) * per;
+    const bool active = NE > 1 || tid < per;
+    WaveMarks<NE, kHeldBlock, 2> wm;
+    wm.find(a.marks, a.m, base, per);
     const double inv_n = 1.0 / a.N;  // N is a power of two: x * (1/N) rounds as x / N
-    const float4 fill = make_float4(a.amp, 0.0f, a.amp, 0.0f);
+    auto at = [&](unsigned r, unsigned t16) { return (r ^ wm.swap) * unsigned(kHeldBlock * 16) + t16; };
+    auto store = [&](float4 *to, Vec4 (&x)[NE]) {
+        const auto rs = buffer_rsrc(to, uint32_t(per * 16u));
+        const unsigned t16 = fresh_tid() * 16u;
+#pragma unroll
+        for (int r = 0; r < NE; ++r)
+            bstore16<kBufNT>(packed(x[r]), rs, at(r, t16));
+    };
     for (uint32_t b = team_id; b < a.B; b += teams) {
-        float4 *st = a.state + uint64_t(b) * a.nvec + h.base;
-        float4 x[kHeldReg];
+        float4 *st = a.state + uint64_t(b) * a.nvec + base;
+        Vec4 x[NE];
         double v[kPV] = {};
-        if (h.active) {
-#pragma unroll
-            for (int e = 0; e < kHeldReg; ++e)
-                x[e] = fill;
-            if (h.ne > unsigned(kHeldReg))
-#pragma unroll
-                for (int e = 0; e < kHeldLds; ++e)
-                    held[e * kStreamBlock + tid] = fill;
+        if (active) {
             // the sums of the uniform state, as the first pass of the streamed form computes them
-            for (unsigned e = 0; e < h.ne; ++e) {
-                const unsigned bits = (mask >> (2 * e)) & 3u;
-                const C2 r{double(a.amp), 0.0};
-                v[0] += r.re + r.re;
-                v[1] += r.im + r.im;
-                for (unsigned q = 0; q < 2; ++q)
-                    if ((bits >> q) & 1u) {
-                        v[2] += r.re;
-                        v[3] += r.im;
-                        v[4] += r.re * r.re + r.im * r.im;
-                    }
+#pragma unroll
+            for (int r = 0; r < NE; ++r) {
+                unpack(make_float4(a.amp, 0.0f, a.amp, 0.0f), x[r]);
+                v[0] += double(a.amp) + double(a.amp);
             }
+            if (wm.any)
+#pragma unroll
+                for (int r = 0; r < (kRest ? NE : 1); ++r)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+                        if ((wm.mk.at(r) >> e) & 1u) {
+                            v[2] += double(a.amp);
+                            v[4] += double(a.amp) * double(a.amp);
+                        }
         }
         // the next step needs the total and the marked sum (4 values); the last one also the marked |c|^2
-        if (!team_sum_n<4>(v, tm, ++gen, sh))
+        if (!team_sum_n<kHeldBlock, 4>(v, tm, ++gen, sh))
             return;
         for (uint32_t k = 1; k <= a.K; ++k) {
             const uint32_t i = (k - 1u) % kTrigChunk;
@@ -650,33 +652,32 @@ __global__ __launch_bounds__(kStreamBlock) void phase_forward_held_kernel(PhaseA
             const C2 S = {v[0] + (ephi.re - 1.0) * v[2] - ephi.im * v[3], v[1] + (ephi.re - 1.0) * v[3] + ephi.im * v[2]};
             const C2 f = cmul({1.0 - eth.re, -eth.im}, S);
             const C2 alpha{f.re * inv_n, f.im * inv_n};
-            float4 *ck = (k % a.every == 0 && k < a.K)
-                             ? a.ckpt + (uint64_t(b) * a.nck + (k / a.every - 1u)) * a.nvec + h.base
-                             : nullptr;
             double w[kPV] = {};
-            if (h.active) {
-                if (mask == 0u)
-                    held_forward_sweep<false>(x, held, h, mask, alpha, ephi, ck, w);
+            if (active) {
+                if (wm.any)
+                    marked_forward(x[0], wm.mk.at(0), alpha, ephi, w);
                 else
-                    held_forward_sweep<true>(x, held, h, mask, alpha, ephi, ck, w);
+                    plain_step(x[0], alpha, w[0], w[1]);
+#pragma unroll
+                for (int r = 1; r < NE; ++r) {
+                    if (kRest && wm.in_rest(r))
+                        marked_forward(x[r], wm.mk.at(r), alpha, ephi, w);
+                    else
+                        plain_step(x[r], alpha, w[0], w[1]);
+                }
+                if (k % a.every == 0 && k < a.K)
+                    store(a.ckpt + (uint64_t(b) * a.nck + (k / a.every - 1u)) * a.nvec + base, x);
             }
-            if (!(k == a.K ? team_sum_n<5>(w, tm, ++gen, sh) : team_sum_n<4>(w, tm, ++gen, sh)))
+            if (!(k == a.K ? team_sum_n<kHeldBlock, 5>(w, tm, ++gen, sh, wm.any != 0u)
+                           : team_sum_n<kHeldBlock, 4>(w, tm, ++gen, sh)))
                 return;
 #pragma unroll
             for (int q = 0; q < kPV; ++q)
                 v[q] = w[q];
         }
         // the final state goes to memory: the adjoint starts from it, and it is the result
-        if (h.active) {
-#pragma unroll
-            for (int e = 0; e < kHeldReg; ++e)
-                if (unsigned(e) < h.ne)
-                    store16<true>(x[e], st + uint64_t(e) * kStreamBlock + tid);
-            if (h.ne > unsigned(kHeldReg))
-#pragma unroll
-                for (int e = 0; e < kHeldLds; ++e)
-                    store16<true>(held[e * kStreamBlock + tid], st + uint64_t(kHeldReg + e) * kStreamBlock + tid);
-        }
+        if (active)
+            store(st, x);
         if (tm.rank == 0 && tid == 0) {
             a.loss[b] = 1.0 - v[4];
             a.aux[2u * b] = v[0];
@@ -685,75 +686,49 @@ __global__ __launch_bounds__(kStreamBlock) void phase_forward_held_kernel(PhaseA
     }
 }
 
-// One reverse step of one held pair (state vector xc, adjoint vector xl), as reverse_pass: with anchor set
-// the state c_{j-1} is given (cin: a checkpoint or the uniform state) instead of being rebuilt.
-template <bool kMarks>
-__device__ inline void held_reverse_vec(float4 &xc, float4 &xl, const float4 &cin, bool anchor, unsigned bits,
-                                        C2 beta_c, C2 beta_l, C2 ephi, double (&w)[kPV])
+// One reverse step of one pair of vectors (state xc, adjoint state xl) that may hold marked amplitudes, as
+// reverse_pass: with anchor set xc is c_{j-1} already (a checkpoint or the uniform state) instead of being rebuilt.
+__device__ inline void marked_reverse(Vec4 &xc, Vec4 &xl, bool anchor, unsigned bits, C2 beta_c, C2 beta_l, C2 ephi,
+                                      double (&w)[kPV])
 {
-    if (!kMarks || bits == 0u) {
+    const C2 emphi{ephi.re, -ephi.im};
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const bool mk = (bits >> e) & 1u;
+        const C2 c{double(xc[2 * e]), double(xc[2 * e + 1])}, l{double(xl[2 * e]), double(xl[2 * e + 1])};
+        C2 y;
         if (anchor) {
-            xc = cin;
+            y = mk ? cmul(ephi, c) : c;
         } else {
-            xc.x = float(beta_c.re - double(xc.x));
-            xc.y = float(beta_c.im - double(xc.y));
-            xc.z = float(beta_c.re - double(xc.z));
-            xc.w = float(beta_c.im - double(xc.w));
+            y = {beta_c.re - c.re, beta_c.im - c.im};
+            const C2 o = mk ? cmul(emphi, y) : y;
+            xc[2 * e] = float(o.re);
+            xc[2 * e + 1] = float(o.im);
         }
-        xl.x = float(beta_l.re - double(xl.x));
-        xl.y = float(beta_l.im - double(xl.y));
-        xl.z = float(beta_l.re - double(xl.z));
-        xl.w = float(beta_l.im - double(xl.w));
-    } else {
-        const C2 emphi{ephi.re, -ephi.im};
-        C2 cp[2], lp[2];
-        const C2 cs[2] = {lo(anchor ? cin : xc), hi(anchor ? cin : xc)}, ls[2] = {lo(xl), hi(xl)};
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const bool mk = (bits >> e) & 1u;
-            C2 y;
-            if (anchor) {
-                cp[e] = cs[e];
-                y = mk ? cmul(ephi, cs[e]) : cs[e];
-            } else {
-                y = {beta_c.re - cs[e].re, beta_c.im - cs[e].im};
-                cp[e] = mk ? cmul(emphi, y) : y;
-            }
-            const C2 nu{beta_l.re - ls[e].re, beta_l.im - ls[e].im};
-            lp[e] = mk ? cmul(emphi, nu) : nu;
-            if (mk)  // Im(conj(nu) y), the only part the gradient uses
-                w[4] += nu.re * y.im - nu.im * y.re;
-        }
-        xc = pack(cp[0], cp[1]);
-        xl = pack(lp[0], lp[1]);
+        const C2 nu{beta_l.re - l.re, beta_l.im - l.im};
+        const C2 p = mk ? cmul(emphi, nu) : nu;
+        xl[2 * e] = float(p.re);
+        xl[2 * e + 1] = float(p.im);
+        if (mk)  // Im(conj(nu) y), the only part the gradient uses
+            w[4] += nu.re * y.im - nu.im * y.re;
     }
-    w[0] += double(xc.x) + double(xc.z);
-    w[1] += double(xc.y) + double(xc.w);
-    w[2] += double(xl.x) + double(xl.z);
-    w[3] += double(xl.y) + double(xl.w);
+    add_parts(xc, w[0], w[1]);
+    add_parts(xl, w[2], w[3]);
 }
 
-template <bool kMarks>
-__device__ inline void held_reverse_sweep(float4 (&xc)[kHeldReg], float4 *held, const HeldShare &h, uint32_t mask,
-                                          const float4 *src, bool anchor, float amp, C2 beta_c, C2 beta_l, C2 ephi,
-                                          double (&w)[kPV])
+__device__ inline void plain_reverse(Vec4 &xc, Vec4 &xl, bool anchor, C2 beta_c, C2 beta_l, double (&w)[kPV])
 {
-    const unsigned tid = threadIdx.x;
-    const float4 uniform = make_float4(amp, 0.0f, amp, 0.0f);
-#pragma unroll
-    for (int e = 0; e < kHeldReg; ++e)
-        if (unsigned(e) < h.ne) {
-            const float4 cin = anchor && src ? load16<true>(src + uint64_t(e) * kStreamBlock + tid) : uniform;
-            float4 xl = held[e * kStreamBlock + tid];
-            held_reverse_vec<kMarks>(xc[e], xl, cin, anchor, (mask >> (2 * e)) & 3u, beta_c, beta_l, ephi, w);
-            held[e * kStreamBlock + tid] = xl;
-        }
+    if (anchor)
+        add_parts(xc, w[0], w[1]);
+    else
+        plain_step(xc, beta_c, w[0], w[1]);
+    plain_step(xl, beta_l, w[2], w[3]);
 }
 
-__global__ __launch_bounds__(kStreamBlock) void phase_adjoint_held_kernel(PhaseArgs a)
+template <int NE, bool kRest>
+__global__ __launch_bounds__(kHeldBlock) void phase_adjoint_held_kernel(PhaseArgs a)
 {
     __shared__ PhaseShared sh;
-    __shared__ float4 held[kHeldLds * kStreamBlock];  // the adjoint state
     __shared__ TrigTable trig;
     const unsigned T = a.team_size, teams = gridDim.x / T, team_id = xcd_major_block() / T;
     if (team_id >= teams)
@@ -763,40 +738,59 @@ __global__ __launch_bounds__(kStreamBlock) void phase_adjoint_held_kernel(PhaseA
     uint64_t gen = 0;
     if (a.probe) {
         double v[kPV] = {};
-        (void)team_sum_n(v, tm, ++gen, sh);
+        (void)team_sum_n<kHeldBlock, 5>(v, tm, ++gen, sh);
         return;
     }
     const unsigned tid = threadIdx.x;
     const bool leader = tm.rank == 0 && tid == 0;
-    const HeldShare h = held_share(a.nvec, tm);
-    const uint32_t mask = held_mask(a, h);
+    const uint64_t per = a.per, base = uint64_t(tm.rank) * per;
+    const bool active = NE > 1 || tid < per;
+    WaveMarks<NE, kHeldBlock, 2> wm;
+    wm.find(a.marks, a.m, base, per);
     const double inv_n = 1.0 / a.N;
-    for (uint32_t b = team_id; b < a.B; b += teams) {
-        float4 *st = a.state + uint64_t(b) * a.nvec + h.base;
-        const double g = a.dloss[b];
-        float4 xc[kHeldReg];
-        double v[kPV] = {};
-        // the final state of the forward run, and the seed lambda = -g c on the marked entries
-        if (h.active) {
+    auto at = [&](unsigned r, unsigned t16) { return (r ^ wm.swap) * unsigned(kHeldBlock * 16) + t16; };
+    auto load = [&](const float4 *from, Vec4 (&x)[NE]) {
+        const auto rs = buffer_rsrc(from, uint32_t(per * 16u));
+        const unsigned t16 = fresh_tid() * 16u;
 #pragma unroll
-            for (int e = 0; e < kHeldReg; ++e)
-                if (unsigned(e) < h.ne) {
-                    xc[e] = load16<true>(st + uint64_t(e) * kStreamBlock + tid);
-                    const unsigned bits = (mask >> (2 * e)) & 3u;
-                    float4 out = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    if (bits) {
-                        const C2 c0 = lo(xc[e]), c1 = hi(xc[e]);
-                        const C2 l0 = (bits & 1u) ? C2{-g * c0.re, -g * c0.im} : C2{0.0, 0.0};
-                        const C2 l1 = (bits & 2u) ? C2{-g * c1.re, -g * c1.im} : C2{0.0, 0.0};
-                        out = pack(l0, l1);
-                        const C2 r0 = lo(out), r1 = hi(out);
-                        v[2] += r0.re + r1.re;
-                        v[3] += r0.im + r1.im;
-                    }
-                    held[e * kStreamBlock + tid] = out;
+        for (int r = 0; r < NE; ++r)
+            unpack(bload16<kBufNT, float4>(rs, at(r, t16)), x[r]);
+    };
+    for (uint32_t b = team_id; b < a.B; b += teams) {
+        float4 *st = a.state + uint64_t(b) * a.nvec + base;
+        const double g = a.dloss[b];
+        Vec4 xc[NE], xl[NE];
+        double v[kPV] = {};
+        // c_{k-1} of an anchor step k ((k - 1) % every == 0), loaded before the barrier that precedes the step so
+        // that the loads travel while it waits; the state they replace is no longer needed then
+        auto anchor_step = [&](uint32_t k) { return (k - 1u) % a.every == 0u; };
+        auto fetch_anchor = [&](uint32_t k) {
+            if (k - 1u > 0u) {
+                load(a.ckpt + (uint64_t(b) * a.nck + ((k - 1u) / a.every - 1u)) * a.nvec + base, xc);
+            } else {
+#pragma unroll
+                for (int r = 0; r < NE; ++r)
+                    unpack(make_float4(a.amp, 0.0f, a.amp, 0.0f), xc[r]);
+            }
+        };
+        // the final state of the forward run, and the seed lambda = -g c on the marked entries
+        if (active) {
+            load(st, xc);
+#pragma unroll
+            for (int r = 0; r < NE; ++r) {
+                unpack(make_float4(0.0f, 0.0f, 0.0f, 0.0f), xl[r]);
+                if (r == 0 ? wm.any != 0u : kRest && wm.in_rest(r)) {
+                    const unsigned bits = wm.mk.at(r);
+#pragma unroll
+                    for (int p = 0; p < 4; ++p)
+                        xl[r][p] = (bits >> (p / 2)) & 1u ? float(-g * double(xc[r][p])) : 0.0f;
+                    add_parts(xl[r], v[2], v[3]);
                 }
+            }
+            if (anchor_step(a.K))
+                fetch_anchor(a.K);
         }
-        if (!team_sum_n<4>(v, tm, ++gen, sh))  // the seed's sum, in v[2], v[3]
+        if (!team_sum_n<kHeldBlock, 4>(v, tm, ++gen, sh))  // the seed's sum, in v[2], v[3]
             return;
         C2 sc{a.aux[2u * b], a.aux[2u * b + 1u]}, sl{v[2], v[3]};
         for (uint32_t k = a.K; k >= 1; --k) {
@@ -811,20 +805,42 @@ __global__ __launch_bounds__(kStreamBlock) void phase_adjoint_held_kernel(PhaseA
             const C2 om{1.0 - emth.re, -emth.im};
             const C2 fc = cmul(om, sc), fl = cmul(om, sl);
             const C2 beta_c{fc.re * inv_n, fc.im * inv_n}, beta_l{fl.re * inv_n, fl.im * inv_n};
-            const bool anchor = (k - 1u) % a.every == 0u;
-            const float4 *src = (anchor && k - 1u > 0u)
-                                    ? a.ckpt + (uint64_t(b) * a.nck + ((k - 1u) / a.every - 1u)) * a.nvec + h.base
-                                    : nullptr;
+            const bool anchor = anchor_step(k);
             double w[kPV] = {};
-            if (h.active) {
+            if (active) {
                 const C2 ephi{trig.v[0][i], trig.v[1][i]};
-                if (mask == 0u)
-                    held_reverse_sweep<false>(xc, held, h, mask, src, anchor, a.amp, beta_c, beta_l, ephi, w);
+                if (wm.any)
+                    marked_reverse(xc[0], xl[0], anchor, wm.mk.at(0), beta_c, beta_l, ephi, w);
                 else
-                    held_reverse_sweep<true>(xc, held, h, mask, src, anchor, a.amp, beta_c, beta_l, ephi, w);
+                    plain_reverse(xc[0], xl[0], anchor, beta_c, beta_l, w);
+                if constexpr (kRest) {
+#pragma unroll
+                    for (int r = 1; r < NE; ++r) {
+                        if (wm.in_rest(r))
+                            marked_reverse(xc[r], xl[r], anchor, wm.mk.at(r), beta_c, beta_l, ephi, w);
+                        else
+                            plain_reverse(xc[r], xl[r], anchor, beta_c, beta_l, w);
+                    }
+                } else {
+                    if (anchor) {
+                        own_values<NE>(xc);
+#pragma unroll
+                        for (int r = 1; r < NE; ++r)
+                            add_parts(xc[r], w[0], w[1]);
+                    } else {
+#pragma unroll
+                        for (int r = 1; r < NE; ++r)
+                            plain_step(xc[r], beta_c, w[0], w[1]);
+                    }
+#pragma unroll
+                    for (int r = 1; r < NE; ++r)
+                        plain_step(xl[r], beta_l, w[2], w[3]);
+                }
+                if (k > 1u && anchor_step(k - 1u))
+                    fetch_anchor(k - 1u);
             }
             // sum c, sum lambda and Im(sum over marked of conj(nu) y): 5 values
-            if (!team_sum_n<5>(w, tm, ++gen, sh))
+            if (!team_sum_n<kHeldBlock, 5>(w, tm, ++gen, sh, wm.any != 0u))
                 return;
             if (leader)  // -2 Im(sum over marked of conj(nu) y)
                 a.dphi[pk] = -2.0 * w[4];
@@ -832,11 +848,13 @@ __global__ __launch_bounds__(kStreamBlock) void phase_adjoint_held_kernel(PhaseA
             sl = {w[2], w[3]};
         }
         // back at the uniform state: written out, as the streamed form leaves it
-        if (h.active)
+        if (active) {
+            const auto rs = buffer_rsrc(st, uint32_t(per * 16u));
+            const unsigned t16 = fresh_tid() * 16u;
 #pragma unroll
-            for (int e = 0; e < kHeldReg; ++e)
-                if (unsigned(e) < h.ne)
-                    store16<true>(xc[e], st + uint64_t(e) * kStreamBlock + tid);
+            for (int r = 0; r < NE; ++r)
+                bstore16<kBufNT>(packed(xc[r]), rs, at(r, t16));
+        }
     }
 }
 
@@ -853,13 +871,62 @@ __global__ void phase_reset_kernel(uint64_t *words, uint64_t nwords, uint64_t *s
 
 }  // namespace
 
-const void *phase_kernel_fn(bool adjoint, bool held)
+namespace {
+
+template <int NE>
+const void *held_kernel(bool adjoint, bool rest)
+{
+    if constexpr (NE <= int(kPhaseHeldAdjointVecs / kHeldBlock))
+        if (adjoint)
+            return rest ? reinterpret_cast<const void *>(&phase_adjoint_held_kernel<NE, true>)
+                        : reinterpret_cast<const void *>(&phase_adjoint_held_kernel<NE, false>);
+    return rest ? reinterpret_cast<const void *>(&phase_forward_held_kernel<NE, true>)
+                : reinterpret_cast<const void *>(&phase_forward_held_kernel<NE, false>);
+}
+
+}  // namespace
+
+uint32_t phase_block(bool held) { return held ? kHeldBlock : kStreamBlock; }
+
+// The on-chip kernels are compiled per number of vectors a thread holds (a member holds `per` of them, at most
+// kPhaseHeldForwardVecs or kPhaseHeldAdjointVecs), with and without code for a wave whose marks lie in several
+// rows (phase_rest): a few marked amplitudes in a state rarely do, and the branch at every vector costs a sweep
+// its scheduling.
+const void *phase_kernel_fn(bool adjoint, bool held, uint64_t per, bool rest)
 {
     if (held)
-        return adjoint ? reinterpret_cast<const void *>(&phase_adjoint_held_kernel)
-                       : reinterpret_cast<const void *>(&phase_forward_held_kernel);
+        switch (per / kHeldBlock) {
+        case 0:
+        case 1: return held_kernel<1>(adjoint, false);
+        case 2: return held_kernel<2>(adjoint, rest);
+        case 4: return held_kernel<4>(adjoint, rest);
+        case 8: return held_kernel<8>(adjoint, rest);
+        case 16: return held_kernel<16>(adjoint, rest);
+        default: return adjoint ? held_kernel<16>(adjoint, rest) : held_kernel<32>(adjoint, rest);
+        }
     return adjoint ? reinterpret_cast<const void *>(&phase_adjoint_kernel)
                    : reinterpret_cast<const void *>(&phase_forward_kernel);
+}
+
+// Does some wave of a member of `per` vectors hold marked amplitudes in two rows?
+bool phase_rest(const std::vector<uint64_t> &marks, uint64_t per)
+{
+    // sorted marks: a wave's marks in one row are adjacent, so remember the last row of each wave of the member
+    uint64_t member = ~uint64_t(0);
+    int64_t row[kHeldBlock / kWave];
+    for (const uint64_t i : marks) {
+        const uint64_t v = i / 2, at = v % per;
+        if (v / per != member) {
+            member = v / per;
+            std::fill(std::begin(row), std::end(row), -1);
+        }
+        const unsigned wave = unsigned(at % kHeldBlock) / kWave;
+        const int64_t e = int64_t(at / kHeldBlock);
+        if (row[wave] >= 0 && row[wave] != e)
+            return true;
+        row[wave] = e;
+    }
+    return false;
 }
 
 hipError_t launch_phase(const PhaseLaunch &L, bool adjoint)
@@ -871,6 +938,7 @@ hipError_t launch_phase(const PhaseLaunch &L, bool adjoint)
     a.marks = L.marks;
     a.m = L.m;
     a.nvec = L.nvec;
+    a.per = L.per;
     a.N = L.N;
     a.amp = L.amp;
     a.B = L.B;
@@ -899,8 +967,8 @@ hipError_t launch_phase(const PhaseLaunch &L, bool adjoint)
     if (e != hipSuccess)
         return e;
     void *args[] = {&a};
-    return hipLaunchCooperativeKernel(phase_kernel_fn(adjoint, L.held != 0u), dim3(L.grid), dim3(kStreamBlock), args,
-                                      0, L.stream);
+    return hipLaunchCooperativeKernel(phase_kernel_fn(adjoint, L.held != 0u, L.per, L.rest != 0u), dim3(L.grid),
+                                      dim3(phase_block(L.held != 0u)), args, 0, L.stream);
 }
 
 }  // namespace grover

@@ -24,6 +24,7 @@ struct PhaseLaunch {
     const uint64_t *marks;
     uint64_t m;
     uint64_t nvec;
+    uint64_t per;          // on-chip form: vectors per member (nvec / team_size)
     double N;
     float amp;
     uint32_t B, K, every, nck;
@@ -36,18 +37,23 @@ struct PhaseLaunch {
     uint32_t team_size;
     uint32_t teams_alloc;  // barrier objects zeroed before the launch
     uint32_t probe;
+    uint32_t rest;  // on-chip form: some wave holds marks in several rows
     uint32_t held;  // 1: the on-chip kernels (team_size set from the state size)
     int grid;
     uint64_t timeout_ticks;
     hipStream_t stream;
 };
 
-// Largest state (vectors) the on-chip kernels hold per thread: forward 16 vectors, adjoint 8 of the state
-// and 8 of the adjoint state.
+// Vectors a workgroup of the on-chip kernels (512 threads) holds at most: forward 32 per thread, adjoint 16 of the
+// state and 16 of the adjoint state.
 constexpr uint64_t kPhaseHeldForwardVecs = 16 * 1024;
 constexpr uint64_t kPhaseHeldAdjointVecs = 8 * 1024;
 
-const void *phase_kernel_fn(bool adjoint, bool held);
+// The kernel and its workgroup size; on-chip kernels differ by the vectors per member and by
+// whether some wave of a member holds marks in several rows (phase_rest).
+const void *phase_kernel_fn(bool adjoint, bool held, uint64_t per, bool rest);
+bool phase_rest(const std::vector<uint64_t> &marks, uint64_t per);
+uint32_t phase_block(bool held);
 hipError_t launch_phase(const PhaseLaunch &L, bool adjoint);
 
 }  // namespace grover

@@ -50,15 +50,15 @@ __device__ inline void put_value(__amdgpu_buffer_rsrc_t slots, uint32_t off, dou
     __builtin_amdgcn_raw_buffer_store_b128(w, slots, off, 0, kBufDevice);
 }
 
-// Bounded wait for NV values of generation `tag`, value q at byte offset off + q * stride: the loads of a
-// round are issued together.  Gives up when the error word is set or the wall-clock limit passes (then
-// setting the error word); both are looked at in the first round and every 16th, the error word by a load
-// issued with that round's others (on its own it would add a memory round trip to nearly every barrier: the
+// Bounded wait for the values of generation `tag` at the byte offsets off[q] that use[q] names (the others read as
+// zero): the loads of a round are issued together.  Gives up when the error word is set or the wall-clock limit
+// passes (then setting the error word); both are looked at in the first round and every 16th, the error word by a
+// load issued with that round's others (on its own it would add a memory round trip to nearly every barrier: the
 // first round mostly comes too early).  The clock is first read in the 16th round, for the same reason: the
 // limit counts from there, and a limit of zero gives up in the first round.
 template <int NV>
-__device__ inline bool wait_values(__amdgpu_buffer_rsrc_t slots, uint32_t off, uint32_t stride, uint32_t tag,
-                                   uint32_t *error, uint64_t timeout_ticks, double (&x)[NV])
+__device__ inline bool wait_offsets(__amdgpu_buffer_rsrc_t slots, const uint32_t (&off)[NV], const bool (&use)[NV],
+                                    uint32_t tag, uint32_t *error, uint64_t timeout_ticks, double (&x)[NV])
 {
     uint64_t t0 = 0;
     const auto error_word = buffer_rsrc(error, 4u);
@@ -70,12 +70,12 @@ __device__ inline bool wait_values(__amdgpu_buffer_rsrc_t slots, uint32_t off, u
         asm volatile("" ::: "memory");  // the loads are of this round (volatile ones would be of system scope)
 #pragma unroll
         for (int q = 0; q < NV; ++q)
-            w[q] = __builtin_amdgcn_raw_buffer_load_b128(slots, off + uint32_t(q) * stride, 0, kBufDevice);
+            w[q] = __builtin_amdgcn_raw_buffer_load_b128(slots, off[q], 0, kBufDevice);
         if (look)
             failed = __builtin_amdgcn_raw_buffer_load_b32(error_word, 0u, 0, kBufDevice);
 #pragma unroll
         for (int q = 0; q < NV; ++q)
-            ready = ready && w[q].x == tag && w[q].z == tag;
+            ready = ready && (!use[q] || (w[q].x == tag && w[q].z == tag));
         if (ready)
             break;
         if (look) {
@@ -96,8 +96,23 @@ __device__ inline bool wait_values(__amdgpu_buffer_rsrc_t slots, uint32_t off, u
     }
 #pragma unroll
     for (int q = 0; q < NV; ++q)
-        x[q] = __longlong_as_double((long long)(((unsigned long long)w[q].y << 32) | w[q].w));
+        x[q] = use[q] ? __longlong_as_double((long long)(((unsigned long long)w[q].y << 32) | w[q].w)) : 0.0;
     return true;
+}
+
+// The same for NV values at off + q * stride.
+template <int NV>
+__device__ inline bool wait_values(__amdgpu_buffer_rsrc_t slots, uint32_t off, uint32_t stride, uint32_t tag,
+                                   uint32_t *error, uint64_t timeout_ticks, double (&x)[NV])
+{
+    uint32_t offs[NV];
+    bool use[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        offs[q] = off + uint32_t(q) * stride;
+        use[q] = true;
+    }
+    return wait_offsets<NV>(slots, offs, use, tag, error, timeout_ticks, x);
 }
 
 // This thread's index in the workgroup, computed afresh: what is derived from it (lane masks, slot offsets) is
