@@ -166,7 +166,8 @@ int grover_apply_hadamard_all_blocked(grover_ctx *ctx);
  *   seed         U_j = SplitMix64_j(seed) >> 11, generated on the device.
  *   out          shots uint64 indices; a device pointer when out_is_device != 0, else host memory (the call
  *                then synchronises).  Returns GROVER_E_INVAL when every q_i is 0 (reported after a sync).
- * Allocates an N-entry uint64 CDF on first use (kept by the context). */
+ * On first use, for N > 16384 (complex128: 8192), allocates N/16 uint64 prefix sums (complex128: N/8; from
+ * n = 25 on N/64) and at most N/4096 + 1 more, kept by the context. */
 int grover_sample(grover_ctx *ctx, uint64_t shots, uint64_t seed, uint64_t *out, int out_is_device);
 
 /* grover_sample_u53 — as grover_sample with caller-supplied uniforms u53[0..shots) (host or device memory

@@ -56,7 +56,7 @@ void release(grover_ctx *c)
     if (c->owns_state && c->state)
         (void)hipFree(c->state);
     for (void *p : {(void *)c->marks_dev, (void *)c->partials, (void *)c->sync, (void *)c->red_partials,
-                    (void *)c->red_out, (void *)c->cdf, (void *)c->block_sums, (void *)c->shots_buf,
+                    (void *)c->red_out, (void *)c->group_prefix, (void *)c->block_sums, (void *)c->shots_buf,
                     (void *)c->u53_buf, (void *)c->flag_dev})
         if (p)
             (void)hipFree(p);
@@ -555,9 +555,11 @@ static int sample_impl(grover_ctx *c, const uint64_t *u53, int u53_is_device, bo
         return fail(c, GROVER_E_INVAL, "null output");
     if (!device_uniforms && shots > 0 && !u53)
         return fail(c, GROVER_E_INVAL, "null uniforms");
-    if (!c->cdf) {
-        GROVER_HIP(c, dev_alloc(&c->cdf, size_t(c->N) * sizeof(uint64_t)), "CDF allocation");
-        GROVER_HIP(c, dev_alloc(&c->block_sums, sample_block_count(c->N) * sizeof(uint64_t)), "CDF allocation");
+    if (sample_group_words(c->dtype, c->N) > 0) {  // each on its own, so that a call after a failed one completes the pair
+        if (!c->group_prefix)
+            GROVER_HIP(c, dev_alloc(&c->group_prefix, sample_group_words(c->dtype, c->N) * sizeof(uint64_t)), "CDF allocation");
+        if (!c->block_sums)
+            GROVER_HIP(c, dev_alloc(&c->block_sums, sample_block_words(c->N) * sizeof(uint64_t)), "CDF allocation");
     }
     const uint64_t *u_dev = nullptr;
     if (!device_uniforms && shots > 0) {

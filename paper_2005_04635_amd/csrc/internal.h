@@ -513,9 +513,8 @@ struct grover_ctx {
     double *red_out = nullptr;        // 2 doubles
     double *host_pinned = nullptr;    // 2 doubles, pinned
     // sampler
-    uint64_t *cdf = nullptr;
-    uint64_t *block_sums = nullptr;
-    size_t block_sums_cap = 0;
+    uint64_t *group_prefix = nullptr;  // prefix sums of 8 to 64 amplitudes' probabilities, within CDF blocks
+    uint64_t *block_sums = nullptr;    // prefix sums of the CDF blocks, and the total
     uint64_t *shots_buf = nullptr;
     size_t shots_cap = 0;
     uint64_t *u53_buf = nullptr;
@@ -598,7 +597,8 @@ hipError_t launch_norm(grover_ctx *c, double *dev_out);
 
 hipError_t launch_sample(grover_ctx *c, const uint64_t *u53_dev, uint64_t seed, bool device_uniforms,
                          uint64_t shots, uint64_t *out_dev);
-size_t sample_block_count(uint64_t N);
+size_t sample_group_words(uint32_t dtype, uint64_t N);
+size_t sample_block_words(uint64_t N);
 
 hipError_t launch_oracle_flip(grover_ctx *c);
 hipError_t launch_hadamard_all(grover_ctx *c);
