@@ -394,7 +394,7 @@ int grover_init(grover_ctx **out, const grover_config *cfg, void *hip_stream, vo
 
         if (form == GROVER_FORM_RESIDENT) {
             c->grid = 1;
-            c->block = kResidentBlock;
+            c->block = int(resident_block(c));
         } else if (form == GROVER_FORM_HELD) {
             c->grid = int(c->held_team);
             c->block = 512;

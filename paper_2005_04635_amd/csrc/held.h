@@ -121,24 +121,35 @@ struct WaveMarks {
     uint32_t rest_lo = 0u, rest_hi = 0u;
     __device__ inline bool in_rest(int r) const { return ((r < 32 ? rest_lo >> r : rest_hi >> (r - 32)) & 1u) != 0u; }
     __device__ inline bool has_rest() const { return (rest_lo | rest_hi) != 0u; }
-    // from the sorted list marks[0, m), for the vectors [base, base + per) of the member
+    // From the sorted list marks[0, m), for the vectors [base, base + per) of the member.  A short list (or a member's
+    // part of it) is read a wave at a time and gone through mark by mark; a long one is searched per vector.
     __device__ inline void find(const uint64_t *marks, uint64_t m, uint64_t base, uint64_t per)
     {
+        constexpr uint64_t kList = 128;
         const unsigned tid = threadIdx.x, wave = tid / kWave;
-        const uint64_t lo = m > 0 ? lower_bound_u64(marks, 0, m, base * EPV) : 0;
-        const uint64_t hi = m > 0 ? lower_bound_u64(marks, lo, m, (base + per) * EPV) : 0;
+        uint64_t lo = 0, hi = m;
+        if (m > uint64_t(kWave)) {
+            lo = lower_bound_u64(marks, 0, m, base * EPV);
+            hi = lower_bound_u64(marks, lo, m, (base + per) * EPV);
+        }
         bool marked = false;
         uint64_t rest = 0;
-        if (hi - lo <= uint64_t(B)) {
-            for (uint64_t i = lo; i < hi; ++i) {
-                const uint64_t x = marks[i];
-                const unsigned v = unsigned(x / EPV - base), e = v / B, owner = v % B;
-                if (owner / kWave == wave) {
+        if (hi - lo <= kList) {
+            for (uint64_t c = lo; c < hi; c += kWave) {
+                const uint64_t mine = c + tid % kWave < hi ? marks[c + tid % kWave] : ~uint64_t(0);
+                const unsigned cnt = unsigned(hi - c < uint64_t(kWave) ? hi - c : uint64_t(kWave));
+                for (unsigned k = 0; k < cnt; ++k) {
+                    const uint64_t x = (uint64_t(unsigned(__builtin_amdgcn_readlane(int(mine >> 32), int(k)))) << 32) |
+                                       unsigned(__builtin_amdgcn_readlane(int(mine), int(k)));
+                    const uint64_t v = x / EPV - base;  // huge when x lies before the member
+                    if (v >= per || unsigned(v) % B / kWave != wave)
+                        continue;
+                    const unsigned e = unsigned(v) / B;
                     if (!marked)
                         swap = e;
                     marked = true;
                     const unsigned r = e ^ swap;
-                    if (owner == tid)
+                    if (unsigned(v) % B == tid)
                         mk.set(r, 1u << unsigned(x % EPV));
                     rest |= r > 0u ? uint64_t(1) << r : 0u;
                 }
@@ -146,11 +157,14 @@ struct WaveMarks {
         } else {
             const bool active = NE > 1 || tid < per;
 #pragma unroll 1
-            for (unsigned r = 0; r < unsigned(NE); ++r) {
-                const unsigned b = active ? marked_bits<EPV>(marks, lo, hi, (base + uint64_t(r) * B + tid) * EPV) : 0u;
-                mk.set(r, b);
+            for (unsigned e = 0; e < unsigned(NE); ++e) {
+                const unsigned b = active ? marked_bits<EPV>(marks, lo, hi, (base + uint64_t(e) * B + tid) * EPV) : 0u;
                 if (__any(b != 0u)) {
+                    if (!marked)
+                        swap = e;
                     marked = true;
+                    const unsigned r = e ^ swap;
+                    mk.set(r, b);
                     rest |= r > 0u ? uint64_t(1) << r : 0u;
                 }
             }

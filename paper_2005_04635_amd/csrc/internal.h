@@ -17,7 +17,6 @@ namespace grover {
 constexpr int kWave = 64;                 // CDNA wavefront width
 constexpr uint32_t kMaxQubits = 34;       // 2^34 complex64 = 128 GiB, half of one MI355X's HBM
 constexpr uint32_t kResidentMaxQubits = 14;  // on-chip path: 2^14 amplitudes in one workgroup
-constexpr int kResidentBlock = 1024;
 constexpr uint64_t kHashMarkCap = uint64_t(1) << 26;  // largest hash-defined marked list kept
 
 // ------------------------------------------------------------------------------------ bfloat16 helpers
@@ -563,6 +562,7 @@ hipError_t launch_fused_external(const FusedExternal &x);
 // The message the last failing grover_init or grover_iterate_static left on the calling thread.
 void set_thread_error(const std::string &msg);
 
+unsigned resident_block(const grover_ctx *c);  // its workgroup size
 hipError_t launch_resident_iterate(grover_ctx *c, uint64_t k);
 
 // Held form (complex64, binary64 sums): workgroups that hold a state of nvec vectors, 0 when it does not fit

@@ -162,13 +162,19 @@ __device__ inline void put_wave_values(double xr, double xi, double *red, unsign
 template <int B>
 __device__ inline void block_allsum(double &a, double &b, unsigned parity, TeamShared<B> &sh)
 {
-    double *red = sh.red[parity & 1u];
-    const unsigned tid = fresh_tid();
-    put_wave_values<B>(a, b, red, tid);
-    __syncthreads();
-    const double p = add_wave_values<B>(red, tid % kWave);
-    a = lane_value(p, B / kWave - 1);
-    b = lane_value(p, 2 * (B / kWave) - 1);
+    if constexpr (B == kWave) {  // one wave: no exchange
+        const double v = half_totals(fold_pair(a, b));
+        a = lane_value(v, 31);
+        b = lane_value(v, 63);
+    } else {
+        double *red = sh.red[parity & 1u];
+        const unsigned tid = fresh_tid();
+        put_wave_values<B>(a, b, red, tid);
+        __syncthreads();
+        const double p = add_wave_values<B>(red, tid % kWave);
+        a = lane_value(p, B / kWave - 1);
+        b = lane_value(p, 2 * (B / kWave) - 1);
+    }
 }
 
 // Team-wide sum of (xr, xi) at barrier generation `gen` (1, 2, ... per barrier object; slots zeroed before

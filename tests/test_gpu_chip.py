@@ -1,4 +1,4 @@
-"""The on-chip kernel of the held and the fused form at the sizes where it can go wrong: every number of vectors
+"""The on-chip kernels (one workgroup; a team, in the held and the fused form) at the sizes where it can go wrong: every number of vectors
 per thread it is compiled for (1 to 64, registers and LDS), members smaller than a workgroup, the smallest and the
 largest team, and marked sets that sit in one row, in several rows of a wave, or too densely to be listed.
 
@@ -37,11 +37,17 @@ def marked(n, how):
         return [N // 3]
     if how == "rows":  # several rows of one wave, both amplitudes of a vector, the first and the last amplitude
         return sorted({i % N for i in (0, 1, 1024, 1026, 3 * 1024 + 7, N // 2, N // 2 + 1024, N - 1)})
+    if how == "row":  # a whole row of vectors above the first
+        return list(range(N // 2, N // 2 + 1024))
     return list(range(0, N, 2)) + [1]  # too many for a member to list
 
 
 CASES = ([(n, "c64", "held", "rows", "f64") for n in (1, 2, 8, 9, 10, 11, 13, 15, 17, 19, 20, 21, 22, 23)]
          + [(n, "c64", "held", how, up) for n in (10, 12, 14, 18) for how in ("one", "dense") for up in ("f64", "f32")]
+         + [(n, d, "resident", how, "f64") for n in (1, 3, 6, 7, 8, 9, 10, 11, 12, 13, 14) for d in ("f64", "c64", "c128")
+            for how in ("rows", "dense")]
+         + [(n, "c64", "resident", "rows", "f32") for n in (5, 8, 10, 12, 14)]
+         + [(n, "c64", form, "row", "f64") for n, form in ((11, "resident"), (14, "resident"), (16, "held"), (22, "held"))]
          + [(n, d, "fused", "rows", "f64") for d in ("f64", "c128") for n in (14, 15, 18, 20, 22)]
          + [(24, "f64", "fused", "rows", "f64"), (23, "c128", "fused", "rows", "f64"), (23, "f64", "fused", "one", "f64"),
             (24, "c64", "auto", "rows", "f64"), (24, "c64", "fused", "one", "f32"), (16, "c64", "fused", "dense", "f64"),

@@ -13,12 +13,13 @@ from test_gpu_phase import G, cuda, forward_bound, grad_bound, loss_bound  # noq
 pytestmark = pytest.mark.gpu
 
 CASES = [(n, how, every) for n in (9, 10, 11, 12, 13, 14, 15, 16) for how in ("one", "rows") for every in (1, 3, 20)]
+CASES += [(n, "row", 3) for n in (11, 12, 14, 15)]  # a whole row of vectors above the first, more marks than are listed
 
 
 @pytest.mark.parametrize("n,how,every", CASES)
 def test_on_chip_phase(G, orc, n, how, every):  # noqa: F811
     N, K = 1 << n, 7
-    marks = [N // 3] if how == "one" else sorted({i % N for i in (0, 1, 1024, 1026, 5 * 1024 + 4, N // 2, N - 1)})
+    marks = [N // 3] if how == "one" else list(range(N // 2, N // 2 + 1024)) if how == "row" else sorted({i % N for i in (0, 1, 1024, 1026, 5 * 1024 + 4, N // 2, N - 1)})
     print(f"phase on chip n={n} marks={how} every={every}", flush=True)
     phi, theta = workloads.phase_schedule(K, seed=700 + n, spread=0.3, batch=2)
     eng = G.GroverPhase(n, marks, K, batch=2, checkpoint_every=every).set_form("held")
