@@ -147,9 +147,10 @@ int grover_apply_hadamard_all(grover_ctx *ctx);
 
 /* grover_gate_iterate_blocked / grover_apply_hadamard_all_blocked — the same operators (Algorithm 2's
  * iteration; H^n) with H^n computed as a blocked Walsh-Hadamard transform: qubits are transformed in
- * groups held in LDS (12 or 13 low qubits per pass, then 8 or 9 per pass), with unnormalised butterflies in
+ * groups held on chip (11 to 14 low qubits per pass, then up to 11 per pass), with unnormalised butterflies in
  * binary64 and the normalisation applied once (2^(-n/2) for H^n; for the iteration the exact 2^(-n) of
- * both transforms, with the conditional phase shift fused into the first transform's last pass).  At
+ * both transforms).  Neighbouring passes of one group are merged, with the conditional phase shift or the
+ * oracle between them: k iterations of g groups are 2k(g - 1) + 1 passes, and one launch for n <= 14.  At
  * n = 28 an H^n is 3 passes instead of 28.  Results equal the single-qubit path's up to rounding (one
  * rounding to the storage type per pass instead of per qubit).  Asynchronous; GROVER_E_UNSUPPORTED for
  * bfloat16 storage. */

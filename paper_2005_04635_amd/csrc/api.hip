@@ -521,10 +521,7 @@ int grover_gate_iterate_blocked(grover_ctx *ctx, uint64_t k)
         return GROVER_E_INVAL;
     if (ctx->dtype == GROVER_CBF16)
         return fail(ctx, GROVER_E_UNSUPPORTED, "the gate-level path has no bfloat16 form");
-    for (uint64_t it = 0; it < k; ++it) {
-        GROVER_HIP(ctx, launch_oracle_flip(ctx), "oracle flip");
-        GROVER_HIP(ctx, launch_gate_diffusion_blocked(ctx), "blocked Walsh-Hadamard passes");
-    }
+    GROVER_HIP(ctx, launch_gate_iterate_blocked(ctx, k), "blocked Walsh-Hadamard passes");
     return GROVER_OK;
 }
 

@@ -1,229 +1,549 @@
 // Blocked Walsh-Hadamard transform for the gate-level comparison path (H^n of Algorithms 1 and 2).
 //
-// H^n factorises over qubits, and any set of qubits can be transformed together once their amplitudes are
-// in one workgroup's LDS.  So instead of n passes over the state (one per qubit, Algorithm 1 literally), the
-// transform takes ceil((n - L) / H) + 1 passes:
-//   - a low pass: each workgroup loads 2^L contiguous amplitudes and applies the butterflies of qubits
-//     0 .. L-1;
-//   - high passes over qubits q0 .. q0+H-1: each workgroup loads a tile of 2^H rows (stride 2^q0) by C
-//     contiguous columns (C amplitudes = one 128-byte or 256-byte segment per row, so loads coalesce) and
-//     applies the butterflies along the rows.
-// Butterflies are unnormalised, (a, b) -> (a + b, a - b), in binary64 in LDS, three stages per register
-// round; the storage type is rounded once per pass.  The normalisation is one multiplication in the last
-// pass: 2^(-n/2) for H^n alone (exact for even n), and for the conventional iteration H^n (2|0><0| - I) H^n
-// the two transforms together need 2^(-n), an exact power of two, applied in the last pass of the second
-// transform; the conditional phase shift (negate every amplitude but index 0) is applied in the last pass
-// of the first.  At n = 28 with complex storage this is 3 passes per H^n instead of 28.
+// H^n factorises over qubits, and any set of qubits can be transformed together once their amplitudes are in one
+// workgroup.  So instead of n passes over the state (one per qubit, Algorithm 1 literally), the qubits are split into
+// groups and each group takes one pass, over tiles of 2^B amplitudes:
+//   - the low group, qubits 0 .. B-1: a tile is 2^B contiguous amplitudes;
+//   - high groups of r <= B - c qubits: a tile is 2^r rows (stride 2^q0) by 2^c contiguous columns, and segments of
+//     2^c amplitudes are at least 64 bytes, 128 where two groups can have it.
+// The groups commute, so the two transforms of a conventional iteration, H^n (2|0><0| - I) H^n, visit them in opposite
+// orders and the group in the middle is transformed, phase-shifted and transformed again while its tile is on chip;
+// likewise the last group of one iteration and the first of the next, with the scale and the next oracle's flips in
+// between.  k iterations of a state of g groups take 2k(g - 1) + 1 passes (2kg and k launches for the oracle
+// otherwise), and a state of one group takes all k iterations in one launch.
+//
+// Butterflies are unnormalised, (a, b) -> (a + b, a - b), in binary64; the storage type is rounded once per pass.  The
+// normalisation of an iteration is the exact power of two 2^-n (2^(-n/2) for H^n alone, exact for even n).  The phase
+// shift is applied as I - 2|0><0|, which touches index 0 only, and its sign goes into the scale.
+//
+// What bounds a pass: HBM (two transfers of every amplitude), then LDS.  A tile lives in registers, 16 or 32 amplitudes
+// per thread, so that a round in registers takes four or five stages, and 14 qubits need two or three rounds with an
+// exchange through LDS between them (eight amplitudes per thread with the tile in LDS took four rounds for 12).  A complex
+// exchange sends the real and the imaginary parts in turn through 2^B words, which lets a tile of 2^14 fit the 160 KiB;
+// there only one workgroup fits a CU, and its next tile is loaded meanwhile.
+//
+// On MI355X, n = 25 complex64: 116 us for a pass that goes one way (4.6 TB/s), 175 and 197 us for the low and the high
+// group there and back, whose 28 and 22 binary64 stages and four exchanges are not hidden behind the one tile in flight;
+// four iterations 3200 -> 1640 us (24 passes of 133 us before).  n = 22: 242 -> 45 us per iteration; n = 12, in one
+// launch: 12.5 -> 2.8; n = 28, 13 passes of four iterations at 4.3 TB/s for 24: 6.1 -> 3.3 ms per iteration.
+#include <algorithm>
 #include <cmath>
 
+#include "stream.h"
 #include "wht.h"
 
 namespace grover {
 namespace {
 
-constexpr int kWhtBlock = 512;
-constexpr int kWhtCols = 16;           // columns of a high-pass tile
-constexpr uint32_t kNegExceptZero = 1;  // store flags
-constexpr uint32_t kScale = 2;
 
-// Storage <-> binary64 value held in LDS.
+// Amplitudes per thread, log2, for tiles of 2^B: a round's window of local bits.  Three windows, one of them at bit 4,
+// cover bits 0 .. 4 + 2 value_bits - 1.
+constexpr int value_bits(int B) { return B <= 12 ? 4 : 5; }
+
+constexpr uint32_t kMaxTileBits = 14;
+constexpr int kAnyCols = -1;
+
+// What a pass does.
+enum Kind {
+    kLow,       // the low group once; the oracle's flips before it, the scale after it
+    kLowBack,   // the low group, the scale and the oracle's flips, the low group again
+    kHigh,      // a high group once; the scale after it
+    kHighBack,  // the last high group, the phase shift, the same group again
+    kAll,       // all iterations of a state that is one tile
+};
+
+struct WhtArgs {
+    void *state;
+    const uint64_t *marks;
+    uint64_t m;
+    uint64_t tiles;
+    uint64_t iters;   // of the one-group kernel
+    double scale;
+    uint32_t top;     // bits of a tile's local index in use: the tile's B, or n where the state is smaller
+    uint32_t c;       // low local bits that are columns; the stages are on bits c .. top-1
+    uint32_t q0;      // qubit of local bit c
+    uint32_t flips;   // whether kLow flips
+};
+
+// Storage <-> the binary64 parts held in registers.
 template <class T>
 struct Wht;
 template <>
 struct Wht<C64> {
     using E = float2;
-    using V = double2;
-    static constexpr int kLowQ = 12;   // 2^12 x 16 B = 64 KiB of LDS (+ 1/8 padding)
-    static constexpr int kHighQ = 8;   // 2^8 rows x 16 columns x 16 B = 64 KiB
-    __device__ static V in(E x) { return make_double2(x.x, x.y); }
-    __device__ static E out(V x) { return make_float2(float(x.x), float(x.y)); }
+    static constexpr int kParts = 2, kStride = 1;
+    static constexpr bool kPrefetch = true;
+    __device__ static void in(E x, double *re, double *im) { *re = x.x, *im = x.y; }
+    __device__ static E out(double re, double im) { return make_float2(float(re), float(im)); }
 };
 template <>
 struct Wht<C128> {
     using E = double2;
-    using V = double2;
-    static constexpr int kLowQ = 12;
-    static constexpr int kHighQ = 8;
-    __device__ static V in(E x) { return x; }
-    __device__ static E out(V x) { return x; }
+    static constexpr int kParts = 2, kStride = 1;
+    static constexpr bool kPrefetch = false;  // two tiles do not fit the registers
+    __device__ static void in(E x, double *re, double *im) { *re = x.x, *im = x.y; }
+    __device__ static E out(double re, double im) { return make_double2(re, im); }
 };
 template <>
 struct Wht<F64Real> {
     using E = double;
-    using V = double;
-    static constexpr int kLowQ = 13;  // 2^13 x 8 B = 64 KiB (+ 1/8 padding)
-    static constexpr int kHighQ = 9;  // 2^9 x 16 x 8 B = 64 KiB
-    __device__ static V in(E x) { return x; }
-    __device__ static E out(V x) { return x; }
+    static constexpr int kParts = 1, kStride = 1;
+    static constexpr bool kPrefetch = true;
+    __device__ static void in(E x, double *re, double *) { *re = x; }
+    __device__ static E out(double re, double) { return re; }
 };
-
-__device__ inline double2 vadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
-__device__ inline double2 vsub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
-__device__ inline double vadd(double a, double b) { return a + b; }
-__device__ inline double vsub(double a, double b) { return a - b; }
-__device__ inline double2 vscale(double2 a, double s) { return make_double2(a.x * s, a.y * s); }
-__device__ inline double vscale(double a, double s) { return a * s; }
-__device__ inline double2 vneg(double2 a) { return make_double2(-a.x, -a.y); }
-__device__ inline double vneg(double a) { return -a; }
-
-template <class V>
-__device__ inline V finish(V v, uint64_t global_index, uint32_t flags, double scale)
-{
-    if (flags & kScale)
-        v = vscale(v, scale);
-    if ((flags & kNegExceptZero) && global_index != 0)
-        v = vneg(v);
-    return v;
-}
-
-// The block a workgroup transforms is a [rows][cols] array whose element (row, col) is amplitude
-// base + row * 2^rowshift + col of the state, kept in LDS at buf[row * cols + col].  A single column (the
-// low pass) is padded by one element every eight: the register rounds read eight rows 2^s apart per thread,
-// and without the padding the lanes of a wavefront fall on half the LDS banks.  Rows of 16 columns (the
-// high passes) already spread a wavefront over all banks.
-template <class T>
-struct Block {
-    typename Wht<T>::E *st;
-    typename Wht<T>::V *buf;
-    uint64_t base;
-    uint32_t rowshift;
-    uint32_t rows;
-    uint32_t cols;
-    __device__ uint64_t global(uint32_t row, uint32_t col) const { return base + (uint64_t(row) << rowshift) + col; }
-    __device__ uint32_t lds(uint32_t row, uint32_t col) const { return cols == 1 ? row + (row >> 3) : row * cols + col; }
+// The real or the imaginary parts of a complex state, which no step of an iteration mixes: a workgroup for each.
+template <class R>
+struct PartOf {};
+template <class R>
+struct Wht<PartOf<R>> {
+    using E = R;
+    static constexpr int kParts = 1, kStride = 2;
+    static constexpr bool kPrefetch = false;
+    __device__ static void in(E x, double *re, double *) { *re = double(x); }
+    __device__ static E out(double re, double) { return R(re); }
 };
-
-// One round of R = 2^LR butterfly stages s .. s+LR-1 along the rows: each thread takes groups of R rows
-// spaced 2^s apart (one column) and transforms them in registers.  The first round reads the state itself
-// and the last one writes it (applying the store flags), so a pass touches LDS only between rounds.
-template <class T, int LR, bool FIRST, bool LAST>
-__device__ inline void wht_round(const Block<T> &B, uint32_t s, uint32_t flags, double scale)
+// Orders LDS accesses only: loads of the next tile stay in flight across it.
+__device__ __forceinline__ void lds_sync()
 {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// A tile of 2^B amplitudes, 2^v to a thread, v = value_bits(B).  In the layout S, value k of thread t is local index
+// spot<S>(t) | k << S: the thread holds the bits S .. S+v-1 of the index.  Three layouts are in use: 4 (loads and stores
+// of 16 neighbours, stages 4 .. 3+v), 0 (stages 0 .. 3) and B - v (stages 4+v .. B-1, and the stores of a pass that goes
+// one way).
+// C: columns of the tile of a high group, log2 (kAnyCols: those of the arguments); 0 for contiguous amplitudes.  kPart:
+// the state may be smaller than the tile.
+template <class T, int B, int C, bool kPart>
+struct Tile {
     using W = Wht<T>;
-    using V = typename W::V;
-    constexpr int R = 1 << LR;
-    const uint32_t h = 1u << s;
-    const uint32_t groups = (B.rows >> LR) * B.cols;
-    for (uint32_t g = threadIdx.x; g < groups; g += blockDim.x) {
-        const uint32_t col = g % B.cols, rg = g / B.cols;
-        const uint32_t row0 = ((rg >> s) << (s + LR)) | (rg & (h - 1u));
-        V x[R];
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-            const uint32_t row = row0 + uint32_t(k) * h;
-            x[k] = FIRST ? W::in(B.st[B.global(row, col)]) : B.buf[B.lds(row, col)];
-        }
-#pragma unroll
-        for (int t = 0; t < LR; ++t) {
-#pragma unroll
-            for (int k = 0; k < R; ++k) {
-                if (k & (1 << t))
-                    continue;
-                const V a = x[k], b = x[k | (1 << t)];
-                x[k] = vadd(a, b);
-                x[k | (1 << t)] = vsub(a, b);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-            const uint32_t row = row0 + uint32_t(k) * h;
-            if (LAST) {
-                const uint64_t gi = B.global(row, col);
-                B.st[gi] = W::out(finish(x[k], gi, flags, scale));
-            } else {
-                B.buf[B.lds(row, col)] = x[k];
-            }
-        }
-    }
-    if (!LAST)
-        __syncthreads();
-}
+    using E = typename W::E;
+    static constexpr bool kRows = C != 0;
+    static constexpr int kValBits = value_bits(B), kVals = 1 << kValBits;
+    static constexpr uint32_t kMid = 4 + kValBits;  // the first stage of the top layout
+    static constexpr int kThreads = 1 << (B - kValBits);
+    static constexpr int kTop = B - kValBits;
+    static constexpr int kWords = (1 << B) + (1 << (B - 5));
 
-template <class T, int LR>
-__device__ inline void wht_round_at(const Block<T> &B, uint32_t s, bool first, bool last, uint32_t flags, double scale)
-{
-    if (first && last)
-        wht_round<T, LR, true, true>(B, s, flags, scale);
-    else if (first)
-        wht_round<T, LR, true, false>(B, s, flags, scale);
-    else if (last)
-        wht_round<T, LR, false, true>(B, s, flags, scale);
-    else
-        wht_round<T, LR, false, false>(B, s, flags, scale);
-}
+    double x[W::kParts][kVals];
 
-// All q = log2(rows) stages along the rows, three at a time (the last round takes the remainder).
-template <class T>
-__device__ inline void wht_rows(const Block<T> &B, uint32_t q, uint32_t flags, double scale)
-{
-    uint32_t s = 0;
-    while (s < q) {
-        const uint32_t lr = q - s < 3u ? q - s : 3u;
-        const bool first = s == 0, last = s + lr == q;
-        if (lr == 3)
-            wht_round_at<T, 3>(B, s, first, last, flags, scale);
-        else if (lr == 2)
-            wht_round_at<T, 2>(B, s, first, last, flags, scale);
-        else
-            wht_round_at<T, 1>(B, s, first, last, flags, scale);
-        s += lr;
-    }
-}
-
-// Low pass: qubits 0 .. L-1 of the block of 2^L amplitudes starting at blockIdx.x * 2^L.
-template <class T>
-__global__ __launch_bounds__(kWhtBlock) void wht_low_kernel(void *state, uint32_t L, uint32_t flags, double scale)
-{
-    using W = Wht<T>;
-    __shared__ typename W::V buf[(1u << W::kLowQ) + (1u << W::kLowQ) / 8];
-    const Block<T> B{static_cast<typename W::E *>(state), buf, uint64_t(blockIdx.x) << L, 0u, 1u << L, 1u};
-    wht_rows<T>(B, L, flags, scale);
-}
-
-// High pass: qubits q0 .. q0+H-1.  Tile t covers the 2^H rows index = hi * 2^(q0+H) + row * 2^q0 + lo,
-// lo in [c0, c0 + kWhtCols), with c0 = (t mod 2^q0 / kWhtCols) * kWhtCols and hi = t div (2^q0 / kWhtCols).
-template <class T>
-__global__ __launch_bounds__(kWhtBlock) void wht_high_kernel(void *state, uint32_t q0, uint32_t H, uint32_t flags,
-                                                            double scale)
-{
-    using W = Wht<T>;
-    __shared__ typename W::V buf[(1u << W::kHighQ) * kWhtCols];
-    const uint64_t chunks = (uint64_t(1) << q0) / kWhtCols;
-    const uint64_t t = blockIdx.x;
-    const uint64_t base = ((t / chunks) << (q0 + H)) | ((t % chunks) * kWhtCols);
-    const Block<T> B{static_cast<typename W::E *>(state), buf, base, q0, 1u << H, uint32_t(kWhtCols)};
-    wht_rows<T>(B, H, flags, scale);
-}
-
-// The unnormalised transform of all n qubits, with `flags` / `scale` applied by its last pass.
-template <class T>
-hipError_t wht(grover_ctx *c, uint32_t flags, double scale)
-{
-    using W = Wht<T>;
-    void *state = c->state;
-    const uint32_t n = c->n;
-    const uint32_t L = n < uint32_t(W::kLowQ) ? n : uint32_t(W::kLowQ);
+    template <int S>
+    static __device__ __forceinline__ uint32_t spot(uint32_t t)
     {
-        uint32_t l = L, f = (L == n) ? flags : 0u;
-        double sc = scale;
-        void *args[] = {&state, &l, &f, &sc};
-        const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(&wht_low_kernel<T>),
-                                             dim3(unsigned(c->N >> L)), dim3(kWhtBlock), args, 0, c->stream);
-        if (e != hipSuccess)
-            return e;
+        return ((t >> S) << (S + kValBits)) | (t & ((1u << S) - 1u));
     }
-    for (uint32_t q0 = L; q0 < n; q0 += uint32_t(W::kHighQ)) {
-        uint32_t q = q0, h = n - q0 < uint32_t(W::kHighQ) ? n - q0 : uint32_t(W::kHighQ);
-        uint32_t f = (q0 + h == n) ? flags : 0u;
-        double sc = scale;
-        void *args[] = {&state, &q, &h, &f, &sc};
-        const uint64_t tiles = c->N >> h >> 4;  // 2^(n - h) / kWhtCols
-        const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(&wht_high_kernel<T>), dim3(unsigned(tiles)),
-                                             dim3(kWhtBlock), args, 0, c->stream);
-        if (e != hipSuccess)
-            return e;
+
+    // LDS word of a local index: one word in 32 is left out, so that threads 32 words apart fall on different banks.
+    // The word of spot | k << S is the sum of the two words, as the two have no bit in common.
+    static __device__ __forceinline__ constexpr uint32_t word(uint32_t e) { return e + (e >> 5); }
+
+    // Butterflies of the stages s with lo <= s < hi that lie in the layout S.
+    template <int S>
+    __device__ __forceinline__ void stages(uint32_t lo, uint32_t hi)
+    {
+#pragma unroll
+        for (int b = 0; b < kValBits; ++b) {
+            if (uint32_t(S + b) < lo || uint32_t(S + b) >= hi)
+                continue;
+#pragma unroll
+            for (int p = 0; p < W::kParts; ++p) {
+                __builtin_amdgcn_sched_barrier(0);  // a stage in place: nothing else's results beside it
+#pragma unroll
+                for (int k = 0; k < kVals; ++k) {
+                    if (k & (1 << b))
+                        continue;
+                    const double u = x[p][k], v = x[p][k | (1 << b)];
+                    x[p][k] = u + v;
+                    x[p][k | (1 << b)] = u - v;
+                }
+            }
+        }
     }
-    return hipSuccess;
+
+    // From layout F to layout S.
+    template <int F, int S>
+    __device__ __forceinline__ void exchange(double *buf)
+    {
+        const uint32_t t = fresh_tid();
+        double *const from = buf + word(spot<F>(t));
+        double *const to = buf + word(spot<S>(t));
+#pragma unroll
+        for (int p = 0; p < W::kParts; ++p) {
+#pragma unroll
+            for (int k = 0; k < kVals; ++k)
+                from[word(uint32_t(k) << F)] = x[p][k];
+            lds_sync();
+#pragma unroll
+            for (int k = 0; k < kVals; ++k)
+                x[p][k] = to[word(uint32_t(k) << S)];
+            lds_sync();
+        }
+    }
+
+    // All stages c .. top-1, from layout 4 to the top one.
+    __device__ __forceinline__ void forward(uint32_t c, uint32_t top, double *buf)
+    {
+        stages<4>(c, top < kMid ? top : kMid);
+        if (c < 4u) {
+            exchange<4, 0>(buf);
+            stages<0>(c, top < 4u ? top : 4u);
+            exchange<0, kTop>(buf);
+        } else {
+            exchange<4, kTop>(buf);
+        }
+        stages<kTop>(c < kMid ? kMid : c, top);
+    }
+
+    // The same in the opposite order, from the top layout to layout 4.
+    __device__ __forceinline__ void backward(uint32_t c, uint32_t top, double *buf)
+    {
+        stages<kTop>(c < kMid ? kMid : c, top);
+        if (c < 4u) {
+            exchange<kTop, 0>(buf);
+            stages<0>(c, top < 4u ? top : 4u);
+            exchange<0, 4>(buf);
+        } else {
+            exchange<kTop, 4>(buf);
+        }
+        stages<4>(c, top < kMid ? top : kMid);
+    }
+
+    __device__ __forceinline__ void scaled(double s)
+    {
+#pragma unroll
+        for (int p = 0; p < W::kParts; ++p)
+#pragma unroll
+            for (int k = 0; k < kVals; ++k)
+                x[p][k] *= s;
+    }
+
+    __device__ __forceinline__ void negate_first()
+    {
+#pragma unroll
+        for (int p = 0; p < W::kParts; ++p)
+            x[p][0] = -x[p][0];
+    }
+
+    // Negates the values whose bit in `table` (one per local index) is set, in layout S.
+    template <int S>
+    __device__ __forceinline__ void flip(const uint32_t *table)
+    {
+        const uint32_t e0 = spot<S>(fresh_tid());
+#pragma unroll
+        for (int k = 0; k < kVals; ++k) {
+            if (k % 4 == 0)
+                __builtin_amdgcn_sched_barrier(0);
+            const uint32_t e = e0 | uint32_t(k) << S;
+            if ((table[e >> 5] >> (e & 31u)) & 1u) {
+#pragma unroll
+                for (int p = 0; p < W::kParts; ++p)
+                    x[p][k] = -x[p][k];
+            }
+        }
+    }
+
+    // Offset in the state of a local index, from the tile's first amplitude; additive over disjoint bits.  Made anew
+    // for each load and store: as many offsets as a thread has values do not fit beside the values.
+    struct Offsets {
+        uint32_t c, q0;
+        __device__ __forceinline__ explicit Offsets(const WhtArgs &a) : c(C == kAnyCols ? a.c : uint32_t(C)), q0(a.q0)
+        {
+            asm volatile("" : "+s"(q0));
+        }
+        __device__ __forceinline__ uint64_t operator()(uint32_t e) const
+        {
+            return kRows ? (uint64_t(e >> c) << q0) | (e & ((1u << c) - 1u)) : e;
+        }
+    };
+
+    // First amplitude of tile t: consecutive tiles are neighbours along the columns.
+    static __device__ __forceinline__ uint64_t first(const WhtArgs &a, uint64_t t)
+    {
+        if (!kRows)
+            return t << a.top;
+        const uint32_t chunk_bits = a.q0 - a.c;
+        return ((t >> chunk_bits) << (a.q0 + a.top - a.c)) | ((t & ((uint64_t(1) << chunk_bits) - 1u)) << a.c);
+    }
+
+    // Where part `part` of an amplitude is, in units of E.
+    static __device__ __forceinline__ uint64_t place(const WhtArgs &a, uint64_t tile, uint32_t part, uint64_t offset)
+    {
+        return (first(a, tile) + offset) * W::kStride + part;
+    }
+
+    template <int S>
+    static __device__ __forceinline__ void load(const WhtArgs &a, uint64_t tile, uint32_t part, E (&raw)[kVals])
+    {
+        const uint32_t e0 = spot<S>(fresh_tid());
+        const Offsets offset(a);
+        const E *const p = static_cast<const E *>(a.state) + place(a, tile, part, offset(e0));
+        if (!kPart || a.top == uint32_t(B)) {
+#pragma unroll
+            for (int k = 0; k < kVals; ++k) {
+                raw[k] = p[offset(uint32_t(k) << S) * W::kStride];
+                if (k % 4 == 3)
+                    __builtin_amdgcn_sched_barrier(0);  // keeps few of the addresses in registers at a time
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < kVals; ++k)
+                raw[k] = ((e0 | uint32_t(k) << S) >> a.top) == 0u ? p[offset(uint32_t(k) << S) * W::kStride] : E{};
+        }
+    }
+
+    template <int S>
+    __device__ __forceinline__ void store(const WhtArgs &a, uint64_t tile, uint32_t part) const
+    {
+        const uint32_t e0 = spot<S>(fresh_tid());
+        const Offsets offset(a);
+        E *const p = static_cast<E *>(a.state) + place(a, tile, part, offset(e0));
+#pragma unroll
+        for (int k = 0; k < kVals; ++k) {
+            if (!kPart || a.top == uint32_t(B) || ((e0 | uint32_t(k) << S) >> a.top) == 0u)
+                p[offset(uint32_t(k) << S) * W::kStride] = W::out(x[0][k], x[W::kParts - 1][k]);
+            if (k % 4 == 3)
+                __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    __device__ __forceinline__ void widen(const E (&raw)[kVals])
+    {
+#pragma unroll
+        for (int k = 0; k < kVals; ++k)
+            W::in(raw[k], &x[0][k], &x[W::kParts - 1][k]);
+        // here, not where the next tile's loads need the registers
+#pragma unroll
+        for (int p = 0; p < W::kParts; ++p)
+#pragma unroll
+            for (int k = 0; k < kVals; ++k)
+                asm volatile("" : "+v"(x[p][k]));
+    }
+};
+
+// The marks of [base, base + 2^top) as one bit per local index; returns whether there are any.  `mine` is mark
+// threadIdx.x, read once per workgroup.
+template <int B>
+__device__ __forceinline__ bool mark_bits(const WhtArgs &a, uint64_t base, uint64_t mine, uint32_t *table, uint32_t *any)
+{
+    constexpr uint64_t kThreads = 1u << (B - value_bits(B));
+    if (threadIdx.x < (1u << (B - 5)))  // 2^B bits
+        table[threadIdx.x] = 0u;
+    if (threadIdx.x == 0)
+        *any = 0u;
+    lds_sync();
+    uint64_t i = threadIdx.x, end = a.m;
+    if (a.m > 16u * kThreads) {  // a long list: from the first mark at or above base
+        uint64_t lo = 0, hi = a.m;
+        while (lo < hi) {
+            const uint64_t mid = (lo + hi) / 2;
+            if (a.marks[mid] < base)
+                lo = mid + 1;
+            else
+                hi = mid;
+        }
+        i += lo;
+        end = a.m - lo < (uint64_t(1) << a.top) ? a.m : lo + (uint64_t(1) << a.top);
+    }
+    for (; i < end; i += kThreads) {
+        const uint64_t d = (i == threadIdx.x ? mine : a.marks[i]) - base;
+        if ((d >> a.top) == 0u) {
+            atomicOr(&table[d >> 5], 1u << (d & 31u));
+            *any = 1u;
+        }
+    }
+    lds_sync();
+    return *any != 0u;
+}
+
+// Number of this block in an order that gives four consecutive numbers to one XCD (blocks go round the 8 XCDs in launch
+// order): the two halves of a 128-byte line and the two parts of its amplitudes meet in one L2.  Longer runs would put
+// the XCDs a power of two apart in memory, on the same channels (16 MiB
+// states, H^n: n = 20 complex128 20.6 us, 29.6 with an eighth of the tiles in a row; n = 21 real 18.6 and 27.7).
+__device__ __forceinline__ unsigned four_by_xcd()
+{
+    const unsigned b = blockIdx.x;
+    return gridDim.x % 32u == 0u ? (b & ~31u) | (b & 7u) << 2 | (b >> 3 & 3u) : b;
+}
+
+// A pass (T: the storage, or the parts of one; kKind: what it does; C: columns of a high group's tile, log2).
+template <class T, int B, Kind kKind, int C>
+__global__ __launch_bounds__(1 << (B - value_bits(B)), 2) void wht_kernel(WhtArgs a)
+{
+    constexpr bool kRows = C != 0;
+    constexpr bool kPart = B == 11 && (kKind == kLow || kKind == kAll);
+    using Tl = Tile<T, B, C, kPart>;
+    // the largest tile leaves room for one workgroup per CU: it takes several tiles, and loads the next one early
+    constexpr bool kSeveral = B == int(kMaxTileBits) && Wht<T>::kStride == 1, kPrefetch = kSeveral && Wht<T>::kPrefetch;
+    __shared__ double buf[Tl::kWords];
+    __shared__ uint32_t table[kRows ? 1 : 1 << (B - 5)];
+    __shared__ uint32_t any;
+    const uint32_t c = C == kAnyCols ? a.c : uint32_t(C), top = kPart ? a.top : uint32_t(B);
+    const bool flips = !kRows && (kKind != kLow || a.flips) && a.m > 0;
+    const uint64_t mine = flips && threadIdx.x < a.m ? a.marks[threadIdx.x] : 0u;
+    typename Tl::E raw[Tl::kVals];
+    Tl tl;
+    constexpr unsigned kStride = unsigned(Wht<T>::kStride);
+    const unsigned number = four_by_xcd();
+    uint64_t tile = number / kStride;
+    const uint32_t part = kStride == 1u ? 0u : number % kStride;
+    if (kPrefetch)
+        Tl::template load<4>(a, tile, part, raw);
+#pragma unroll 1
+    do {
+        if (!kPrefetch)
+            Tl::template load<4>(a, tile, part, raw);
+        tl.widen(raw);
+        const uint64_t next = tile + gridDim.x / kStride;
+        if (kPrefetch && next < a.tiles)
+            Tl::template load<4>(a, next, part, raw);
+        const bool marked = flips && mark_bits<B>(a, tile << top, mine, table, &any);
+        if constexpr (kKind == kAll) {
+#pragma unroll 1
+            for (uint64_t it = 0; it < a.iters; ++it) {
+                if (marked)
+                    tl.template flip<4>(table);
+                tl.forward(c, top, buf);
+                if (threadIdx.x == 0)
+                    tl.negate_first();
+                tl.backward(c, top, buf);
+                tl.scaled(a.scale);
+            }
+            tl.template store<4>(a, tile, part);
+        } else if constexpr (kKind == kLowBack || kKind == kHighBack) {
+            tl.forward(c, top, buf);
+            if constexpr (kRows) {
+                if (tile == 0 && threadIdx.x == 0)
+                    tl.negate_first();
+            } else {
+                tl.scaled(a.scale);
+                if (marked)
+                    tl.template flip<Tl::kTop>(table);
+            }
+            tl.backward(c, top, buf);
+            tl.template store<4>(a, tile, part);
+        } else {
+            if (marked)
+                tl.template flip<4>(table);
+            tl.forward(c, top, buf);
+            if (a.scale != 1.0)
+                tl.scaled(a.scale);
+            tl.template store<Tl::kTop>(a, tile, part);
+        }
+        tile = next;
+    } while (kSeveral && tile < a.tiles);
+}
+
+// How the n qubits are split: the low group takes `bits` of them, the others go evenly to `highs` groups.
+struct Split {
+    uint32_t bits = 0, highs = 0;
+};
+
+// One group up to n = 14: a workgroup's iteration in registers then costs less than two launches (n = 14 complex64 7.9 us,
+// 13.7 in two groups).  Above, as few groups as tiles of 2^14 and segments of 64 bytes allow (n = 25 complex64, two
+// groups 381 us per iteration; three, as n = 26 scaled, 420), and the smallest tile that does it: more and smaller
+// workgroups hide each other's loads (n = 23 complex64, 2^13 against 2^14: 87 and 98 us for the first iteration).  Three
+// groups keep 2^12, below which segments would be no longer.
+Split split(const grover_ctx *c)
+{
+    Split s;
+    const uint32_t n = c->n, elem = uint32_t(elem_bytes(c->dtype));
+    if (n <= kMaxTileBits) {
+        s.bits = std::max(n, 11u);
+        return s;
+    }
+    const uint32_t cols = elem == 16u ? 2u : 3u;  // columns of a 64-byte segment, log2
+    for (s.highs = 1;; ++s.highs) {
+        // n - bits <= highs * (bits - cols)
+        s.bits = (n + s.highs * cols + s.highs) / (s.highs + 1u);
+        if (s.bits > kMaxTileBits)
+            continue;
+        s.bits = std::max(s.bits, s.highs == 1u ? 11u : 12u);
+        return s;
+    }
+}
+
+// Whether the real and the imaginary parts go to workgroups of their own: where the tiles are too few to fill the
+// chip, half the work of each takes less time than the lines read twice, which caches hold at these sizes (n = 18
+// complex64 10.5 us per iteration against 17.2; at n = 20 the two are equal).
+bool by_parts(const grover_ctx *c)
+{
+    const Split s = split(c);
+    return s.highs == 0u || (s.highs == 1u && s.bits <= 11u);
+}
+
+// The kernel for tiles of 2^bits and segments of 2^c.  The columns are a constant of the kernel where a workgroup has
+// more than a wave: stages left out at run time cost registers and moves.
+template <class T, Kind kKind, int C>
+const void *kernel_of(uint32_t bits)
+{
+    if constexpr (C <= 0)
+        if (bits == 11)
+            return reinterpret_cast<const void *>(&wht_kernel<T, 11, kKind, C>);
+    if constexpr (C >= 0)
+        if (bits == 12)
+            return reinterpret_cast<const void *>(&wht_kernel<T, 12, kKind, C>);
+    // parts of a state of more than one group come in tiles of up to 2^12 only
+    if constexpr (C >= 0 && (Wht<T>::kStride == 1 || kKind == kLow || kKind == kAll)) {
+        if (bits == 13)
+            return reinterpret_cast<const void *>(&wht_kernel<T, 13, kKind, C>);
+        if (bits == kMaxTileBits)
+            return reinterpret_cast<const void *>(&wht_kernel<T, int(kMaxTileBits), kKind, C>);
+    }
+    return nullptr;
+}
+
+template <class T, Kind kKind>
+const void *kernel(uint32_t bits, uint32_t c)
+{
+    if constexpr (kKind == kHigh || kKind == kHighBack) {
+        if (bits == 11)
+            return kernel_of<T, kKind, kAnyCols>(bits);
+        switch (c) {
+        case 2:
+            if constexpr (sizeof(typename Wht<T>::E) == 16)
+                return kernel_of<T, kKind, 2>(bits);
+            return nullptr;
+        case 3: return kernel_of<T, kKind, 3>(bits);
+        case 4: return kernel_of<T, kKind, 4>(bits);
+        case 5: return kernel_of<T, kKind, 5>(bits);
+        default: return nullptr;
+        }
+    } else if constexpr (kKind == kAll && Wht<T>::kParts == 2) {
+        return nullptr;  // by parts
+    } else {
+        return kernel_of<T, kKind, 0>(bits);
+    }
+}
+
+// One pass of group g (0: the low one).
+template <class T, Kind kKind>
+hipError_t pass(grover_ctx *c, const Split &s, uint32_t g, double scale = 1.0, bool flips = false, uint64_t iters = 1)
+{
+    WhtArgs a{};
+    a.state = c->state;
+    a.marks = c->marks_dev;
+    a.m = c->marks.size();
+    a.iters = iters;
+    a.scale = scale;
+    a.flips = flips;
+    a.top = std::min(s.bits, c->n);
+    if (g > 0) {
+        const uint32_t rest = c->n - s.bits;
+        const uint32_t r = rest / s.highs + (g <= rest % s.highs ? 1u : 0u);
+        a.c = s.bits - r;
+        a.q0 = s.bits + (g - 1u) * (rest / s.highs) + std::min(g - 1u, rest % s.highs);
+    }
+    a.tiles = c->N >> a.top;
+    const void *fn = kernel<T, kKind>(s.bits, a.c);
+    if (!fn)
+        return hipErrorInvalidValue;
+    const uint64_t grid = s.bits == kMaxTileBits && Wht<T>::kStride == 1 ? std::min<uint64_t>(a.tiles, uint64_t(c->cu_count))
+                                                                         : a.tiles * Wht<T>::kStride;
+    void *args[] = {&a};
+    return hipLaunchKernel(fn, dim3(unsigned(grid)), dim3(1u << (s.bits - uint32_t(value_bits(int(s.bits))))), args, 0, c->stream);
 }
 
 template <class T>
@@ -231,37 +551,57 @@ hipError_t hadamard_all_blocked(grover_ctx *c)
 {
     // 2^(-n/2): exact for even n; for odd n 2^(-(n+1)/2) * sqrt(2) rounded once to binary64
     const int n = int(c->n);
-    const double s = (n % 2 == 0) ? std::ldexp(1.0, -n / 2) : std::ldexp(std::sqrt(2.0), -(n + 1) / 2);
-    return wht<T>(c, kScale, s);
+    const double scale = (n % 2 == 0) ? std::ldexp(1.0, -n / 2) : std::ldexp(std::sqrt(2.0), -(n + 1) / 2);
+    const Split s = split(c);
+    hipError_t e = pass<T, kLow>(c, s, 0, s.highs == 0u ? scale : 1.0);
+    for (uint32_t g = 1; g <= s.highs && e == hipSuccess; ++g)
+        e = pass<T, kHigh>(c, s, g, g == s.highs ? scale : 1.0);
+    return e;
 }
 
 template <class T>
-hipError_t diffusion_blocked(grover_ctx *c)
+hipError_t gate_iterate_blocked(grover_ctx *c, uint64_t k)
 {
-    hipError_t e = wht<T>(c, kNegExceptZero, 1.0);
-    if (e != hipSuccess)
-        return e;
-    return wht<T>(c, kScale, std::ldexp(1.0, -int(c->n)));
+    const Split s = split(c);
+    const double scale = -std::ldexp(1.0, -int(c->n));
+    if (k == 0)
+        return hipSuccess;
+    if (s.highs == 0)
+        return pass<T, kAll>(c, s, 0, scale, true, k);
+    hipError_t e = pass<T, kLow>(c, s, 0, 1.0, true);
+    for (uint64_t it = 0; it < k && e == hipSuccess; ++it) {
+        for (uint32_t g = 1; g < s.highs && e == hipSuccess; ++g)
+            e = pass<T, kHigh>(c, s, g);
+        if (e == hipSuccess)
+            e = pass<T, kHighBack>(c, s, s.highs);
+        for (uint32_t g = s.highs - 1u; g > 0u && e == hipSuccess; --g)
+            e = pass<T, kHigh>(c, s, g);
+        if (e == hipSuccess)
+            e = it + 1 < k ? pass<T, kLowBack>(c, s, 0, scale) : pass<T, kLow>(c, s, 0, scale);
+    }
+    return e;
 }
 
 }  // namespace
 
 hipError_t launch_hadamard_all_blocked(grover_ctx *c)
 {
+    const bool parts = by_parts(c);
     switch (c->dtype) {
     case GROVER_F64_REAL: return hadamard_all_blocked<F64Real>(c);
-    case GROVER_C64: return hadamard_all_blocked<C64>(c);
-    case GROVER_C128: return hadamard_all_blocked<C128>(c);
+    case GROVER_C64: return parts ? hadamard_all_blocked<PartOf<float>>(c) : hadamard_all_blocked<C64>(c);
+    case GROVER_C128: return parts ? hadamard_all_blocked<PartOf<double>>(c) : hadamard_all_blocked<C128>(c);
     default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_gate_diffusion_blocked(grover_ctx *c)
+hipError_t launch_gate_iterate_blocked(grover_ctx *c, uint64_t k)
 {
+    const bool parts = by_parts(c);
     switch (c->dtype) {
-    case GROVER_F64_REAL: return diffusion_blocked<F64Real>(c);
-    case GROVER_C64: return diffusion_blocked<C64>(c);
-    case GROVER_C128: return diffusion_blocked<C128>(c);
+    case GROVER_F64_REAL: return gate_iterate_blocked<F64Real>(c, k);
+    case GROVER_C64: return parts ? gate_iterate_blocked<PartOf<float>>(c, k) : gate_iterate_blocked<C64>(c, k);
+    case GROVER_C128: return parts ? gate_iterate_blocked<PartOf<double>>(c, k) : gate_iterate_blocked<C128>(c, k);
     default: return hipErrorInvalidValue;
     }
 }

@@ -5,10 +5,9 @@
 
 namespace grover {
 
-// H^n with the normalisation 2^(-n/2), in ceil((n - L) / H) + 1 LDS-blocked passes.
+// H^n with the normalisation 2^(-n/2), one pass over the state per group of qubits.
 hipError_t launch_hadamard_all_blocked(grover_ctx *c);
-// H^n (2|0><0| - I) H^n as two unnormalised transforms: the phase shift fused into the first one's last
-// pass, the exact scale 2^(-n) into the second one's.
-hipError_t launch_gate_diffusion_blocked(grover_ctx *c);
+// k iterations of H^n (2|0><0| - I) H^n after the oracle, the neighbouring passes of one group merged.
+hipError_t launch_gate_iterate_blocked(grover_ctx *c, uint64_t k);
 
 }  // namespace grover
