@@ -7,6 +7,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "grover.h"
@@ -238,6 +239,45 @@ struct AccF32Kahan {
 };
 
 // ------------------------------------------------------------------------------ update of one vector
+// The update of complex bfloat16.  Rounding binary64 once, in integers (double_to_bf16), is some ten instructions for
+// each part.  Rounding to binary32 and from there to bfloat16, one and a half, differs from it only where the binary32
+// lies halfway between two bfloat16: then the part's true value may be to either side.  Those vectors (one in 8192 of
+// unrelated values) are rounded again in integers.  (The conversion of all 2^32 binary32 was compared with rounding
+// in integers.)  On MI355X a search at n = 26 was bound by these instructions: 78.0 -> 73.8 us per iteration
+// (n = 24 23.9 -> 18.1).
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+template <class A>
+__device__ inline void update_vec_bf16(bf16x8 &v, double mr, double mi, unsigned marked, A &acc)
+{
+    double d[8];
+    uint32_t w[4];
+    bool halfway = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const double s = (marked >> e) & 1u ? -1.0 : 1.0;
+        d[2 * e] = mr - s * CBF16::re(v, e);
+        d[2 * e + 1] = mi - s * CBF16::im(v, e);
+        const f32x2 f{float(d[2 * e]), float(d[2 * e + 1])};
+        halfway |= uint16_t(__float_as_uint(f.x)) == 0x8000u;
+        halfway |= uint16_t(__float_as_uint(f.y)) == 0x8000u;
+        const bf16x2 b = __builtin_convertvector(f, bf16x2);
+        __builtin_memcpy(&w[e], &b, 4);
+    }
+    __builtin_memcpy(&v, w, 16);
+    if (__builtin_expect(halfway, false)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            v.h[i] = double_to_bf16(d[i]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const double s = (marked >> e) & 1u ? -1.0 : 1.0;
+        acc.add(s * CBF16::re(v, e), s * CBF16::im(v, e));
+    }
+}
+
 // Inversion about the mean on the oracle-flipped amplitudes: c' = 2S/N - s*c with s = -1 for marked
 // amplitudes (bit e of `marked`), +1 otherwise, computed in binary64 from (mr, mi) = 2S/N and rounded to
 // the storage type.  The stored value, times s, is added to the accumulator: that is the next iteration's
@@ -245,6 +285,10 @@ struct AccF32Kahan {
 template <class T, class A>
 __device__ inline void update_vec(typename T::vec &v, double mr, double mi, unsigned marked, A &acc)
 {
+    if constexpr (std::is_same<T, CBF16>::value) {
+        update_vec_bf16(v, mr, mi, marked, acc);
+        return;
+    }
 #pragma unroll
     for (int e = 0; e < T::EPV; ++e) {
         const double s = (marked >> e) & 1u ? -1.0 : 1.0;
