@@ -109,82 +109,114 @@ struct MarkBits {
     }
 };
 
+// First index of the sorted list marks[0, m) whose mark is >= x, m if none is.  Called by a whole wave: 64 probes a
+// step, as a list is far away and a step's loads travel together.
+__device__ inline uint64_t wave_lower_bound(const uint64_t *marks, uint64_t m, uint64_t x)
+{
+    const uint64_t lane = threadIdx.x % kWave;
+    uint64_t lo = 0, len = m;  // the answer lies in [lo, lo + len]
+    while (len > 0) {
+        const uint64_t step = (len + kWave - 1u) / kWave;
+        const uint64_t below = uint64_t(__popcll(__ballot(lane * step < len && marks[lo + lane * step] < x)));
+        if (below == 0)
+            break;
+        const uint64_t end = below * step < len ? below * step : len;
+        lo += (below - 1u) * step + 1u;
+        len = end - ((below - 1u) * step + 1u);
+    }
+    return lo;
+}
+
 // Where a wave of a B-thread member finds its marked amplitudes.  Position r of a thread holds vector e = r ^ swap,
-// swap the same in every lane of a wave and chosen so that the wave's first marked vector is at position 0: the
+// swap the same in every lane of a wave and chosen so that a wave whose marks lie in one row has them at position 0: the
 // few instructions for marks are then spent on position 0 alone, unless the wave holds marks in other rows too
 // (in_rest, a bit per position).
 template <int NE, int B, int EPV>
 struct WaveMarks {
+    // LDS words that `find` needs: a bit per amplitude of the member
+    static constexpr unsigned kWords = unsigned(NE) * B * EPV / 32u;
     MarkBits<NE> mk{};
     unsigned swap = 0u;
     unsigned any = 0u;  // this wave holds marked amplitudes (the same in every lane, as swap and rest)
     uint32_t rest_lo = 0u, rest_hi = 0u;
     __device__ inline bool in_rest(int r) const { return ((r < 32 ? rest_lo >> r : rest_hi >> (r - 32)) & 1u) != 0u; }
     __device__ inline bool has_rest() const { return (rest_lo | rest_hi) != 0u; }
-    // From the sorted list marks[0, m), for the vectors [base, base + per) of the member.  A short list (or a member's
-    // part of it) is read a wave at a time and gone through mark by mark; a long one is searched per vector.
-    __device__ inline void find(const uint64_t *marks, uint64_t m, uint64_t base, uint64_t per)
+    // From the sorted list marks[0, m), for the vectors [base, base + per) of the member; called by the whole workgroup.
+    // Up to 16 marks are held by the lanes of every wave, which goes through those of its own; more are scattered into the
+    // LDS words.  On MI355X, one iteration of a call on one workgroup (n = 10 binary64, 64 marks; n = 14 complex64, 300
+    // and 1024 marks): every mark gone through by every wave up to 128 of them, then a binary search of the list per
+    // vector 8.8, 28.8 and 32.9 us; a search per vector always 3.6, 19.5, 20.9; this 2.7, 7.2, 7.5.
+    __device__ inline void find(const uint64_t *marks, uint64_t m, uint64_t base, uint64_t per, uint32_t *words)
     {
-        constexpr uint64_t kList = 128;
-        const unsigned tid = threadIdx.x, wave = tid / kWave;
+        const unsigned tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
         uint64_t lo = 0, hi = m;
         if (m > uint64_t(kWave)) {
-            lo = lower_bound_u64(marks, 0, m, base * EPV);
-            hi = lower_bound_u64(marks, lo, m, (base + per) * EPV);
+            lo = wave_lower_bound(marks, m, base * EPV);
+            hi = lo + wave_lower_bound(marks + lo, m - lo, (base + per) * EPV);
         }
-        bool marked = false;
-        uint64_t rest = 0;
-        if (hi - lo <= kList) {
-            for (uint64_t c = lo; c < hi; c += kWave) {
-                const uint64_t mine = c + tid % kWave < hi ? marks[c + tid % kWave] : ~uint64_t(0);
-                const unsigned cnt = unsigned(hi - c < uint64_t(kWave) ? hi - c : uint64_t(kWave));
-                for (unsigned k = 0; k < cnt; ++k) {
-                    const uint64_t x = (uint64_t(unsigned(__builtin_amdgcn_readlane(int(mine >> 32), int(k)))) << 32) |
-                                       unsigned(__builtin_amdgcn_readlane(int(mine), int(k)));
-                    const uint64_t v = x / EPV - base;  // huge when x lies before the member
-                    if (v >= per || unsigned(v) % B / kWave != wave)
-                        continue;
-                    const unsigned e = unsigned(v) / B;
-                    if (!marked)
-                        swap = e;
-                    marked = true;
-                    const unsigned r = e ^ swap;
-                    if (unsigned(v) % B == tid)
-                        mk.set(r, 1u << unsigned(x % EPV));
-                    rest |= r > 0u ? uint64_t(1) << r : 0u;
-                }
+        const uint64_t mine = hi - lo <= uint64_t(kWave) && lane < hi - lo ? marks[lo + lane] : ~uint64_t(0);
+        const uint64_t v = mine / EPV - base;  // huge when the mark lies before the member, or there is none
+        uint64_t rows = 0;                     // positions that hold marks
+        if (__builtin_expect(hi - lo <= uint64_t(kWave) && __popcll(__ballot(v < per)) <= 16, 1)) {
+            uint64_t todo = __ballot(v < per && unsigned(v) % B / kWave == wave);
+            if (todo != 0)
+                swap = unsigned(__builtin_amdgcn_readlane(int(v), __builtin_ctzll(todo))) / B;
+            for (; todo != 0; todo &= todo - 1u) {
+                const int k = __builtin_ctzll(todo);
+                const unsigned at = unsigned(__builtin_amdgcn_readlane(int(v), k));
+                const unsigned amp = unsigned(__builtin_amdgcn_readlane(int(mine % EPV), k));
+                const unsigned r = (at / B) ^ swap;
+                if (at % kWave == lane)
+                    mk.set(r, 1u << amp);
+                rows |= uint64_t(1) << r;
             }
         } else {
-            const bool active = NE > 1 || tid < per;
-#pragma unroll 1
-            for (unsigned e = 0; e < unsigned(NE); ++e) {
-                const unsigned b = active ? marked_bits<EPV>(marks, lo, hi, (base + uint64_t(e) * B + tid) * EPV) : 0u;
-                if (__any(b != 0u)) {
-                    if (!marked)
-                        swap = e;
-                    marked = true;
-                    const unsigned r = e ^ swap;
-                    mk.set(r, b);
-                    rest |= r > 0u ? uint64_t(1) << r : 0u;
+            for (unsigned w = tid; w < kWords; w += B)
+                words[w] = 0u;
+            __syncthreads();
+#pragma unroll 4
+            for (uint64_t i = lo + tid; i < hi; i += B) {
+                const uint64_t d = marks[i] - base * EPV;
+                if (d < per * EPV)
+                    atomicOr(&words[d / 32u], 1u << (d % 32u));
+            }
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                const unsigned i = (unsigned(e) * B + tid) * EPV;
+                const unsigned b = (words[i / 32u] >> (i % 32u)) & ((1u << EPV) - 1u);
+                mk.w[e / 16] |= b << (2 * (e % 16));
+                rows |= __ballot(b != 0u) != 0u ? uint64_t(1) << e : 0u;
+            }
+            if (rows != 0u && (rows & (rows - 1u)) == 0u) {  // one row: to position 0
+                swap = unsigned(__builtin_ctzll(rows));
+                unsigned b = 0u;
+#pragma unroll
+                for (int i = 0; i < MarkBits<NE>::words; ++i) {
+                    b |= int(swap / 16u) == i ? (mk.w[i] >> (2u * (swap % 16u))) & 3u : 0u;
+                    mk.w[i] = 0u;
                 }
+                mk.w[0] = b;
+                rows = 1u;
             }
         }
         // the same in every lane of a wave: kept in scalar registers
         swap = __builtin_amdgcn_readfirstlane(swap);
-        any = __builtin_amdgcn_readfirstlane(marked ? 1u : 0u);
-        rest_lo = __builtin_amdgcn_readfirstlane(uint32_t(rest));
-        rest_hi = __builtin_amdgcn_readfirstlane(uint32_t(rest >> 32));
+        any = __builtin_amdgcn_readfirstlane(rows != 0u ? 1u : 0u);
+        rest_lo = __builtin_amdgcn_readfirstlane(uint32_t(rows) & ~1u);
+        rest_hi = __builtin_amdgcn_readfirstlane(uint32_t(rows >> 32));
     }
 };
 
 // All iterations of one member's share, and the store back.  The state is loaded (kLoad) or starts as `fill`;
 // its oracle-signed sum is formed in the order the iterations add theirs, so consecutive calls compose bit for
 // bit.  `begin` is asked once, by the whole workgroup, before the first sum; `reduce` is the team's (or the
-// workgroup's) sum.  Returns false, nothing stored, when either says so.  `mine`: the thread's LDS slots, B apart.
+// workgroup's) sum.  Returns false, nothing stored, when either says so.  `words`: LDS of WaveMarks::find; `mine`: the
+// thread's LDS slots, B apart.
 template <class T, bool U32, bool WIDE, int NE, int RE, int B, bool kLoad, class Begin, class Reduce>
 __device__ __forceinline__ bool held_run(typename T::vec *st, uint64_t base, uint64_t per, const uint64_t *marks,
                                          uint64_t m, uint64_t iters, double scale, const typename T::vec &fill,
-                                         typename T::vec *mine, Begin begin, Reduce reduce)
+                                         uint32_t *words, typename T::vec *mine, Begin begin, Reduce reduce)
 {
     using X = Held<T, U32, WIDE>;
     using V = typename T::vec;
@@ -193,7 +225,7 @@ __device__ __forceinline__ bool held_run(typename T::vec *st, uint64_t base, uin
     const unsigned tid = threadIdx.x;
     const bool active = NE > 1 || tid < per;
     WaveMarks<NE, B, T::EPV> wm;
-    wm.find(marks, m, base, per);
+    wm.find(marks, m, base, per, words);
     const bool has_rest = wm.has_rest();
 
     typename X::H x[RE][X::parts];

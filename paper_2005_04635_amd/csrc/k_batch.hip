@@ -87,25 +87,26 @@ __device__ bool run_streamed(const BatchArgs &a, const BatchInstance &I, unsigne
 // memory once, at the end.  Returns false when a barrier gave up.
 template <bool U32, int NE, class Reduce>
 __device__ __forceinline__ bool run_held_ne(const BatchArgs &a, const BatchInstance &I, uint64_t base, uint64_t per,
-                                            Reduce reduce)
+                                            uint32_t *words, Reduce reduce)
 {
+    static_assert(WaveMarks<NE, kBatchBlock, 2>::kWords <= unsigned(kMarkWords), "the table holds a bit per amplitude");
     // 2/N is a power of two, so S * (2/N) rounds to the same binary64 value as 2S / N
     return held_run<C64, U32, !U32 && NE <= 16, NE, NE, kBatchBlock, false>(
         a.state + I.state_off + base, base, per, a.marks + I.marks_off, I.m, I.iters, 2.0 / I.N, uniform_vec(I.amp),
-        static_cast<float4 *>(nullptr), []() { return true; }, reduce);
+        words, static_cast<float4 *>(nullptr), []() { return true; }, reduce);
 }
 
 template <bool U32, class Reduce>
 __device__ __forceinline__ bool run_held(const BatchArgs &a, const BatchInstance &I, uint64_t base, uint64_t per,
-                                         Reduce reduce)
+                                         uint32_t *words, Reduce reduce)
 {
     switch (per < uint64_t(kBatchBlock) ? 1u : unsigned(per / kBatchBlock)) {
-    case 1: return run_held_ne<U32, 1>(a, I, base, per, reduce);
-    case 2: return run_held_ne<U32, 2>(a, I, base, per, reduce);
-    case 4: return run_held_ne<U32, 4>(a, I, base, per, reduce);
-    case 8: return run_held_ne<U32, 8>(a, I, base, per, reduce);
-    case 16: return run_held_ne<U32, 16>(a, I, base, per, reduce);
-    case 32: return run_held_ne<U32, 32>(a, I, base, per, reduce);
+    case 1: return run_held_ne<U32, 1>(a, I, base, per, words, reduce);
+    case 2: return run_held_ne<U32, 2>(a, I, base, per, words, reduce);
+    case 4: return run_held_ne<U32, 4>(a, I, base, per, words, reduce);
+    case 8: return run_held_ne<U32, 8>(a, I, base, per, words, reduce);
+    case 16: return run_held_ne<U32, 16>(a, I, base, per, words, reduce);
+    case 32: return run_held_ne<U32, 32>(a, I, base, per, words, reduce);
     default: return false;
     }
 }
@@ -119,7 +120,7 @@ template <bool kStreams, bool U32>
 __global__ __launch_bounds__(kBatchBlock) void batch_kernel(BatchArgs a)
 {
     __shared__ TeamShared<kBatchBlock> sh;
-    __shared__ uint32_t table[kStreams ? kMarkWords : 1];
+    __shared__ uint32_t table[kMarkWords];  // of build_mark_table or WaveMarks::find
     const uint32_t grid = gridDim.x;
     if (a.probe) {
         const Team tm{a.sync, a.partials, grid, blockIdx.x, a.timeout_ticks};
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(kBatchBlock) void batch_kernel(BatchArgs a)
             bool ok;
             if (T == 1u ? I.nvec <= kBatchAloneVecs : a.resident[p] != 0u) {
                 const uint64_t per = I.nvec / T;
-                ok = run_held<U32>(a, I, uint64_t(tm.rank) * per, per, reduce);
+                ok = run_held<U32>(a, I, uint64_t(tm.rank) * per, per, table, reduce);
             } else if (kStreams) {
                 ok = run_streamed<U32>(a, I, tm.rank, T, table, reduce);
             } else {

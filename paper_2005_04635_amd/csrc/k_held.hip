@@ -52,6 +52,7 @@ __global__ __launch_bounds__(kChipBlock) void chip_iterate_kernel(ChipArgs a)
     using V = typename T::vec;
     __shared__ TeamShared<kChipBlock> sh;
     __shared__ V held[LE > 0 ? LE * kChipBlock : 1];
+    __shared__ uint32_t words[WaveMarks<NE, kChipBlock, T::EPV>::kWords];
     const unsigned q = blockIdx.x & 7u, rank = (blockIdx.x >> 3) * a.xcds + q;
     if (q >= a.xcds || rank >= a.team)
         return;
@@ -70,7 +71,8 @@ __global__ __launch_bounds__(kChipBlock) void chip_iterate_kernel(ChipArgs a)
         error = __hip_atomic_load(&a.sync->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint64_t base = uint64_t(rank) * a.per;
     (void)held_run<T, U32, kWide, NE, RE, kChipBlock, true>(
-        static_cast<V *>(a.state) + base, base, a.per, a.marks, a.m, a.iters, a.scale, V{}, held + threadIdx.x,
+        static_cast<V *>(a.state) + base, base, a.per, a.marks, a.m, a.iters, a.scale, V{}, words,
+        held + threadIdx.x,
         [&]() { return !__syncthreads_or(error != 0u); },
         [&](double &r, double &i) { return team_sum<kChipBlock>(r, i, tm, ++gen, sh); });
 }

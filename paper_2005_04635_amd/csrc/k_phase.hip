@@ -595,6 +595,7 @@ __global__ __launch_bounds__(kHeldBlock) void phase_forward_held_kernel(PhaseArg
 {
     __shared__ PhaseShared sh;
     __shared__ TrigTable trig;
+    __shared__ uint32_t words[WaveMarks<NE, kHeldBlock, 2>::kWords];
     const unsigned T = a.team_size, teams = gridDim.x / T, team_id = xcd_major_block() / T;
     if (team_id >= teams)
         return;
@@ -610,7 +611,7 @@ __global__ __launch_bounds__(kHeldBlock) void phase_forward_held_kernel(PhaseArg
     const uint64_t per = a.per, base = uint64_t(tm.rank) * per;
     const bool active = NE > 1 || tid < per;
     WaveMarks<NE, kHeldBlock, 2> wm;
-    wm.find(a.marks, a.m, base, per);
+    wm.find(a.marks, a.m, base, per, words);
     const double inv_n = 1.0 / a.N;  // N is a power of two: x * (1/N) rounds as x / N
     auto at = [&](unsigned r, unsigned t16) { return (r ^ wm.swap) * unsigned(kHeldBlock * 16) + t16; };
     auto store = [&](float4 *to, Vec4 (&x)[NE]) {
@@ -730,6 +731,7 @@ __global__ __launch_bounds__(kHeldBlock) void phase_adjoint_held_kernel(PhaseArg
 {
     __shared__ PhaseShared sh;
     __shared__ TrigTable trig;
+    __shared__ uint32_t words[WaveMarks<NE, kHeldBlock, 2>::kWords];
     const unsigned T = a.team_size, teams = gridDim.x / T, team_id = xcd_major_block() / T;
     if (team_id >= teams)
         return;
@@ -746,7 +748,7 @@ __global__ __launch_bounds__(kHeldBlock) void phase_adjoint_held_kernel(PhaseArg
     const uint64_t per = a.per, base = uint64_t(tm.rank) * per;
     const bool active = NE > 1 || tid < per;
     WaveMarks<NE, kHeldBlock, 2> wm;
-    wm.find(a.marks, a.m, base, per);
+    wm.find(a.marks, a.m, base, per, words);
     const double inv_n = 1.0 / a.N;
     auto at = [&](unsigned r, unsigned t16) { return (r ^ wm.swap) * unsigned(kHeldBlock * 16) + t16; };
     auto load = [&](const float4 *from, Vec4 (&x)[NE]) {

@@ -31,9 +31,11 @@ __global__ __launch_bounds__(B) void resident_iterate_kernel(ResidentArgs a)
     using V = typename T::vec;
     constexpr bool kWide = std::is_same<T, C64>::value && !U32 && NE <= 16;
     __shared__ TeamShared<B> sh;
+    __shared__ uint32_t words[WaveMarks<NE, B, T::EPV>::kWords];
     unsigned parity = 0;
     (void)held_run<T, U32, kWide, NE, NE, B, true>(
-        static_cast<V *>(a.state), 0, a.nvec, a.marks, a.m, a.iters, a.scale, V{}, static_cast<V *>(nullptr),
+        static_cast<V *>(a.state), 0, a.nvec, a.marks, a.m, a.iters, a.scale, V{}, words,
+        static_cast<V *>(nullptr),
         []() { return true; },
         [&](double &r, double &i) {
             block_allsum<B>(r, i, parity++, sh);
