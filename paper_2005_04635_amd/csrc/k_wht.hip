@@ -274,36 +274,80 @@ struct Tile {
         return (first(a, tile) + offset) * W::kStride + part;
     }
 
+    // A state of at most one tile (kPart): its bytes as a buffer, of which loads beyond the end give zero and stores there
+    // do nothing, so that no value needs a condition.
+    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t small_state(const WhtArgs &a)
+    {
+        return buffer_rsrc(a.state, (uint32_t(sizeof(E)) * uint32_t(W::kStride)) << a.top);
+    }
+    template <int S>
+    static __device__ __forceinline__ uint32_t small_place(uint32_t part, int k)
+    {
+        return ((spot<S>(threadIdx.x) | uint32_t(k) << S) * uint32_t(W::kStride) + part) * uint32_t(sizeof(E));
+    }
+    static __device__ __forceinline__ E load_bytes(__amdgpu_buffer_rsrc_t rs, uint32_t off)
+    {
+        E v;
+        if constexpr (sizeof(E) == 4) {
+            const auto w = __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
+            __builtin_memcpy(&v, &w, 4);
+        } else {
+            static_assert(sizeof(E) == 8, "a part of an amplitude, or a real one");
+            const auto w = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
+            __builtin_memcpy(&v, &w, 8);
+        }
+        return v;
+    }
+    static __device__ __forceinline__ void store_bytes(E v, __amdgpu_buffer_rsrc_t rs, uint32_t off)
+    {
+        if constexpr (sizeof(E) == 4) {
+            unsigned w;
+            __builtin_memcpy(&w, &v, 4);
+            __builtin_amdgcn_raw_buffer_store_b32(w, rs, off, 0, 0);
+        } else {
+            unsigned w __attribute__((ext_vector_type(2)));
+            __builtin_memcpy(&w, &v, 8);
+            __builtin_amdgcn_raw_buffer_store_b64(w, rs, off, 0, 0);
+        }
+    }
+
     template <int S>
     static __device__ __forceinline__ void load(const WhtArgs &a, uint64_t tile, uint32_t part, E (&raw)[kVals])
     {
+        if constexpr (kPart) {
+            const auto rs = small_state(a);
+#pragma unroll
+            for (int k = 0; k < kVals; ++k)
+                raw[k] = load_bytes(rs, small_place<S>(part, k));
+            return;
+        }
         const uint32_t e0 = spot<S>(fresh_tid());
         const Offsets offset(a);
         const E *const p = static_cast<const E *>(a.state) + place(a, tile, part, offset(e0));
-        if (!kPart || a.top == uint32_t(B)) {
 #pragma unroll
-            for (int k = 0; k < kVals; ++k) {
-                raw[k] = p[offset(uint32_t(k) << S) * W::kStride];
-                if (k % 4 == 3)
-                    __builtin_amdgcn_sched_barrier(0);  // keeps few of the addresses in registers at a time
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < kVals; ++k)
-                raw[k] = ((e0 | uint32_t(k) << S) >> a.top) == 0u ? p[offset(uint32_t(k) << S) * W::kStride] : E{};
+        for (int k = 0; k < kVals; ++k) {
+            raw[k] = p[offset(uint32_t(k) << S) * W::kStride];
+            if (k % 4 == 3)
+                __builtin_amdgcn_sched_barrier(0);  // keeps few of the addresses in registers at a time
         }
     }
 
     template <int S>
     __device__ __forceinline__ void store(const WhtArgs &a, uint64_t tile, uint32_t part) const
     {
+        if constexpr (kPart) {
+            const auto rs = small_state(a);
+#pragma unroll
+            for (int k = 0; k < kVals; ++k)
+                store_bytes(W::out(x[0][k], x[W::kParts - 1][k]), rs, small_place<S>(part, k));
+            return;
+        }
         const uint32_t e0 = spot<S>(fresh_tid());
         const Offsets offset(a);
         E *const p = static_cast<E *>(a.state) + place(a, tile, part, offset(e0));
 #pragma unroll
         for (int k = 0; k < kVals; ++k) {
-            if (!kPart || a.top == uint32_t(B) || ((e0 | uint32_t(k) << S) >> a.top) == 0u)
-                p[offset(uint32_t(k) << S) * W::kStride] = W::out(x[0][k], x[W::kParts - 1][k]);
+            p[offset(uint32_t(k) << S) * W::kStride] = W::out(x[0][k], x[W::kParts - 1][k]);
             if (k % 4 == 3)
                 __builtin_amdgcn_sched_barrier(0);
         }
@@ -373,7 +417,7 @@ template <class T, int B, Kind kKind, int C>
 __global__ __launch_bounds__(1 << (B - value_bits(B)), 2) void wht_kernel(WhtArgs a)
 {
     constexpr bool kRows = C != 0;
-    constexpr bool kPart = B == 11 && (kKind == kLow || kKind == kAll);
+    constexpr bool kPart = B == 10;
     using Tl = Tile<T, B, C, kPart>;
     // the largest tile leaves room for one workgroup per CU: it takes several tiles, and loads the next one early
     constexpr bool kSeveral = B == int(kMaxTileBits) && Wht<T>::kStride == 1, kPrefetch = kSeveral && Wht<T>::kPrefetch;
@@ -427,6 +471,14 @@ __global__ __launch_bounds__(1 << (B - value_bits(B)), 2) void wht_kernel(WhtArg
         } else {
             if (marked)
                 tl.template flip<4>(table);
+            if (kPart && top <= Tl::kMid) {  // no stage in the top layout: nor the exchange to it
+                tl.template stages<4>(c, top);
+                tl.template exchange<4, 0>(buf);
+                tl.template stages<0>(c, top < 4u ? top : 4u);
+                tl.scaled(a.scale);
+                tl.template store<0>(a, tile, part);
+                return;
+            }
             tl.forward(c, top, buf);
             if (a.scale != 1.0)
                 tl.scaled(a.scale);
@@ -445,13 +497,16 @@ struct Split {
 // 13.7 in two groups).  Above, as few groups as tiles of 2^14 and segments of 64 bytes allow (n = 25 complex64, two
 // groups 381 us per iteration; three, as n = 26 scaled, 420), and the smallest tile that does it: more and smaller
 // workgroups hide each other's loads (n = 23 complex64, 2^13 against 2^14: 87 and 98 us for the first iteration).  Three
-// groups keep 2^12, below which segments would be no longer.
-Split split(const grover_ctx *c)
+// groups keep 2^12, below which segments would be no longer.  H^n alone, for which one workgroup has no later passes to
+// save, goes to two groups from n = 14 on (`alone`; n = 14 complex64 6.6 us, 8.3 in one group).  States below 2^11 have a
+// kernel of one wave, whose loads and stores need no conditions, and no third layout up to n = 8 (n = 9 complex64, H^n 2.9
+// us; 4.1 in the padded tile of 2^11, 3.1 with the tile in LDS).
+Split split(const grover_ctx *c, bool alone)
 {
     Split s;
     const uint32_t n = c->n, elem = uint32_t(elem_bytes(c->dtype));
-    if (n <= kMaxTileBits) {
-        s.bits = std::max(n, 11u);
+    if (n <= (alone ? kMaxTileBits - 1u : kMaxTileBits)) {
+        s.bits = std::max(n, 10u);
         return s;
     }
     const uint32_t cols = elem == 16u ? 2u : 3u;  // columns of a 64-byte segment, log2
@@ -468,9 +523,8 @@ Split split(const grover_ctx *c)
 // Whether the real and the imaginary parts go to workgroups of their own: where the tiles are too few to fill the
 // chip, half the work of each takes less time than the lines read twice, which caches hold at these sizes (n = 18
 // complex64 10.5 us per iteration against 17.2; at n = 20 the two are equal).
-bool by_parts(const grover_ctx *c)
+bool by_parts(const Split &s)
 {
-    const Split s = split(c);
     return s.highs == 0u || (s.highs == 1u && s.bits <= 11u);
 }
 
@@ -479,6 +533,9 @@ bool by_parts(const grover_ctx *c)
 template <class T, Kind kKind, int C>
 const void *kernel_of(uint32_t bits)
 {
+    if constexpr (C == 0 && Wht<T>::kParts == 1 && (kKind == kLow || kKind == kAll))
+        if (bits == 10)
+            return reinterpret_cast<const void *>(&wht_kernel<T, 10, kKind, C>);
     if constexpr (C <= 0)
         if (bits == 11)
             return reinterpret_cast<const void *>(&wht_kernel<T, 11, kKind, C>);
@@ -547,12 +604,11 @@ hipError_t pass(grover_ctx *c, const Split &s, uint32_t g, double scale = 1.0, b
 }
 
 template <class T>
-hipError_t hadamard_all_blocked(grover_ctx *c)
+hipError_t hadamard_all_blocked(grover_ctx *c, const Split &s)
 {
     // 2^(-n/2): exact for even n; for odd n 2^(-(n+1)/2) * sqrt(2) rounded once to binary64
     const int n = int(c->n);
     const double scale = (n % 2 == 0) ? std::ldexp(1.0, -n / 2) : std::ldexp(std::sqrt(2.0), -(n + 1) / 2);
-    const Split s = split(c);
     hipError_t e = pass<T, kLow>(c, s, 0, s.highs == 0u ? scale : 1.0);
     for (uint32_t g = 1; g <= s.highs && e == hipSuccess; ++g)
         e = pass<T, kHigh>(c, s, g, g == s.highs ? scale : 1.0);
@@ -560,9 +616,8 @@ hipError_t hadamard_all_blocked(grover_ctx *c)
 }
 
 template <class T>
-hipError_t gate_iterate_blocked(grover_ctx *c, uint64_t k)
+hipError_t gate_iterate_blocked(grover_ctx *c, const Split &s, uint64_t k)
 {
-    const Split s = split(c);
     const double scale = -std::ldexp(1.0, -int(c->n));
     if (k == 0)
         return hipSuccess;
@@ -586,22 +641,24 @@ hipError_t gate_iterate_blocked(grover_ctx *c, uint64_t k)
 
 hipError_t launch_hadamard_all_blocked(grover_ctx *c)
 {
-    const bool parts = by_parts(c);
+    const Split s = split(c, true);
+    const bool parts = by_parts(s);
     switch (c->dtype) {
-    case GROVER_F64_REAL: return hadamard_all_blocked<F64Real>(c);
-    case GROVER_C64: return parts ? hadamard_all_blocked<PartOf<float>>(c) : hadamard_all_blocked<C64>(c);
-    case GROVER_C128: return parts ? hadamard_all_blocked<PartOf<double>>(c) : hadamard_all_blocked<C128>(c);
+    case GROVER_F64_REAL: return hadamard_all_blocked<F64Real>(c, s);
+    case GROVER_C64: return parts ? hadamard_all_blocked<PartOf<float>>(c, s) : hadamard_all_blocked<C64>(c, s);
+    case GROVER_C128: return parts ? hadamard_all_blocked<PartOf<double>>(c, s) : hadamard_all_blocked<C128>(c, s);
     default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t launch_gate_iterate_blocked(grover_ctx *c, uint64_t k)
 {
-    const bool parts = by_parts(c);
+    const Split s = split(c, false);
+    const bool parts = by_parts(s);
     switch (c->dtype) {
-    case GROVER_F64_REAL: return gate_iterate_blocked<F64Real>(c, k);
-    case GROVER_C64: return parts ? gate_iterate_blocked<PartOf<float>>(c, k) : gate_iterate_blocked<C64>(c, k);
-    case GROVER_C128: return parts ? gate_iterate_blocked<PartOf<double>>(c, k) : gate_iterate_blocked<C128>(c, k);
+    case GROVER_F64_REAL: return gate_iterate_blocked<F64Real>(c, s, k);
+    case GROVER_C64: return parts ? gate_iterate_blocked<PartOf<float>>(c, s, k) : gate_iterate_blocked<C64>(c, s, k);
+    case GROVER_C128: return parts ? gate_iterate_blocked<PartOf<double>>(c, s, k) : gate_iterate_blocked<C128>(c, s, k);
     default: return hipErrorInvalidValue;
     }
 }
