@@ -28,6 +28,7 @@
 // launch: 12.5 -> 2.8; n = 28, 13 passes of four iterations at 4.3 TB/s for 24: 6.1 -> 3.3 ms per iteration.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "stream.h"
 #include "wht.h"
@@ -71,7 +72,7 @@ struct Wht;
 template <>
 struct Wht<C64> {
     using E = float2;
-    static constexpr int kParts = 2, kStride = 1;
+    static constexpr int kParts = 2, kStride = 1, kBytes = 8;
     static constexpr bool kPrefetch = true;
     __device__ static void in(E x, double *re, double *im) { *re = x.x, *im = x.y; }
     __device__ static E out(double re, double im) { return make_float2(float(re), float(im)); }
@@ -79,7 +80,7 @@ struct Wht<C64> {
 template <>
 struct Wht<C128> {
     using E = double2;
-    static constexpr int kParts = 2, kStride = 1;
+    static constexpr int kParts = 2, kStride = 1, kBytes = 16;
     static constexpr bool kPrefetch = false;  // two tiles do not fit the registers
     __device__ static void in(E x, double *re, double *im) { *re = x.x, *im = x.y; }
     __device__ static E out(double re, double im) { return make_double2(re, im); }
@@ -87,7 +88,7 @@ struct Wht<C128> {
 template <>
 struct Wht<F64Real> {
     using E = double;
-    static constexpr int kParts = 1, kStride = 1;
+    static constexpr int kParts = 1, kStride = 1, kBytes = 8;
     static constexpr bool kPrefetch = true;
     __device__ static void in(E x, double *re, double *) { *re = x; }
     __device__ static E out(double re, double) { return re; }
@@ -98,7 +99,7 @@ struct PartOf {};
 template <class R>
 struct Wht<PartOf<R>> {
     using E = R;
-    static constexpr int kParts = 1, kStride = 2;
+    static constexpr int kParts = 1, kStride = 2, kBytes = 2 * int(sizeof(R));
     static constexpr bool kPrefetch = false;
     __device__ static void in(E x, double *re, double *) { *re = double(x); }
     __device__ static E out(double re, double) { return R(re); }
@@ -501,10 +502,9 @@ struct Split {
 // save, goes to two groups from n = 14 on (`alone`; n = 14 complex64 6.6 us, 8.3 in one group).  States below 2^11 have a
 // kernel of one wave, whose loads and stores need no conditions, and no third layout up to n = 8 (n = 9 complex64, H^n 2.9
 // us; 4.1 in the padded tile of 2^11, 3.1 with the tile in LDS).
-Split split(const grover_ctx *c, bool alone)
+constexpr Split split(uint32_t n, uint32_t elem, bool alone)
 {
     Split s;
-    const uint32_t n = c->n, elem = uint32_t(elem_bytes(c->dtype));
     if (n <= (alone ? kMaxTileBits - 1u : kMaxTileBits)) {
         s.bits = std::max(n, 10u);
         return s;
@@ -520,60 +520,102 @@ Split split(const grover_ctx *c, bool alone)
     }
 }
 
+// Qubits of high group g = 1 .. s.highs.
+constexpr uint32_t high_bits(const Split &s, uint32_t n, uint32_t g)
+{
+    const uint32_t rest = n - s.bits;
+    return rest / s.highs + (g <= rest % s.highs ? 1u : 0u);
+}
+
 // Whether the real and the imaginary parts go to workgroups of their own: where the tiles are too few to fill the
 // chip, half the work of each takes less time than the lines read twice, which caches hold at these sizes (n = 18
 // complex64 10.5 us per iteration against 17.2; at n = 20 the two are equal).
-bool by_parts(const Split &s)
+constexpr bool by_parts(const Split &s)
 {
     return s.highs == 0u || (s.highs == 1u && s.bits <= 11u);
 }
 
-// The kernel for tiles of 2^bits and segments of 2^c.  The columns are a constant of the kernel where a workgroup has
-// more than a wave: stages left out at run time cost registers and moves.
-template <class T, Kind kKind, int C>
-const void *kernel_of(uint32_t bits)
+// Whether some n has a pass of this kind in tiles of 2^bits and, in high groups, segments of 2^c (kAnyCols: any): only
+// those are compiled.
+template <class T>
+constexpr bool reached(Kind kind, uint32_t bits, int c)
 {
-    if constexpr (C == 0 && Wht<T>::kParts == 1 && (kKind == kLow || kKind == kAll))
-        if (bits == 10)
-            return reinterpret_cast<const void *>(&wht_kernel<T, 10, kKind, C>);
-    if constexpr (C <= 0)
-        if (bits == 11)
-            return reinterpret_cast<const void *>(&wht_kernel<T, 11, kKind, C>);
-    if constexpr (C >= 0)
-        if (bits == 12)
-            return reinterpret_cast<const void *>(&wht_kernel<T, 12, kKind, C>);
-    // parts of a state of more than one group come in tiles of up to 2^12 only
-    if constexpr (C >= 0 && (Wht<T>::kStride == 1 || kKind == kLow || kKind == kAll)) {
-        if (bits == 13)
-            return reinterpret_cast<const void *>(&wht_kernel<T, 13, kKind, C>);
-        if (bits == kMaxTileBits)
-            return reinterpret_cast<const void *>(&wht_kernel<T, int(kMaxTileBits), kKind, C>);
-    }
+    for (uint32_t n = 1; n <= kMaxQubits; ++n)
+        for (const bool alone : {false, true}) {
+            const Split s = split(n, uint32_t(Wht<T>::kBytes), alone);
+            if (s.bits != bits || (!std::is_same<T, F64Real>::value && by_parts(s) != (Wht<T>::kStride == 2)))
+                continue;
+            if ((kind == kLow && (alone || s.highs > 0u)) || (kind == kLowBack && !alone && s.highs > 0u) ||
+                (kind == kAll && !alone && s.highs == 0u))
+                return true;
+            for (uint32_t g = 1; g <= s.highs; ++g)
+                if (kind == (alone || g < s.highs ? kHigh : kHighBack) &&
+                    (c == kAnyCols || uint32_t(c) == s.bits - high_bits(s, n, g)))
+                    return true;
+        }
+    return false;
+}
+
+template <class T, Kind kKind, int B, int C>
+const void *kernel_if_reached()
+{
+    if constexpr (reached<T>(kKind, B, C))
+        return reinterpret_cast<const void *>(&wht_kernel<T, B, kKind, C>);
     return nullptr;
+}
+
+// The kernel for tiles of 2^B and segments of 2^c.  The columns are a constant of the kernel where a workgroup has more
+// than two waves: stages left out at run time cost registers and moves.
+template <class T, Kind kKind, int B>
+const void *kernel_of(uint32_t c)
+{
+    if constexpr (kKind != kHigh && kKind != kHighBack) {
+        return kernel_if_reached<T, kKind, B, 0>();
+    } else if constexpr (B <= 11) {
+        return kernel_if_reached<T, kKind, B, kAnyCols>();
+    } else {
+        switch (c) {
+        case 2: return kernel_if_reached<T, kKind, B, 2>();
+        case 3: return kernel_if_reached<T, kKind, B, 3>();
+        case 4: return kernel_if_reached<T, kKind, B, 4>();
+        case 5: return kernel_if_reached<T, kKind, B, 5>();
+        default: return nullptr;
+        }
+    }
 }
 
 template <class T, Kind kKind>
 const void *kernel(uint32_t bits, uint32_t c)
 {
-    if constexpr (kKind == kHigh || kKind == kHighBack) {
-        if (bits == 11)
-            return kernel_of<T, kKind, kAnyCols>(bits);
-        switch (c) {
-        case 2:
-            if constexpr (sizeof(typename Wht<T>::E) == 16)
-                return kernel_of<T, kKind, 2>(bits);
-            return nullptr;
-        case 3: return kernel_of<T, kKind, 3>(bits);
-        case 4: return kernel_of<T, kKind, 4>(bits);
-        case 5: return kernel_of<T, kKind, 5>(bits);
-        default: return nullptr;
-        }
-    } else if constexpr (kKind == kAll && Wht<T>::kParts == 2) {
-        return nullptr;  // by parts
-    } else {
-        return kernel_of<T, kKind, 0>(bits);
+    switch (bits) {
+    case 10: return kernel_of<T, kKind, 10>(c);
+    case 11: return kernel_of<T, kKind, 11>(c);
+    case 12: return kernel_of<T, kKind, 12>(c);
+    case 13: return kernel_of<T, kKind, 13>(c);
+    case 14: return kernel_of<T, kKind, 14>(c);
+    default: return nullptr;
     }
 }
+static_assert(kMaxTileBits == 14, "the largest of `kernel`");
+
+// Every split has its kernels: high groups in tiles of 2^12 and more have segments of 2^2 to 2^5.
+constexpr bool splits_covered()
+{
+    for (uint32_t n = 1; n <= kMaxQubits; ++n)
+        for (const uint32_t elem : {8u, 16u})
+            for (const bool alone : {false, true}) {
+                const Split s = split(n, elem, alone);
+                if (s.bits < 10u || s.bits > kMaxTileBits || (s.highs == 0u && n > s.bits))
+                    return false;
+                for (uint32_t g = 1; g <= s.highs; ++g) {
+                    const uint32_t r = high_bits(s, n, g), c = s.bits - r;
+                    if (r < 1u || r > s.bits || (s.bits > 11u && (c < 2u || c > 5u)))
+                        return false;
+                }
+            }
+    return true;
+}
+static_assert(splits_covered(), "a number of qubits without a kernel");
 
 // One pass of group g (0: the low one).
 template <class T, Kind kKind>
@@ -589,8 +631,7 @@ hipError_t pass(grover_ctx *c, const Split &s, uint32_t g, double scale = 1.0, b
     a.top = std::min(s.bits, c->n);
     if (g > 0) {
         const uint32_t rest = c->n - s.bits;
-        const uint32_t r = rest / s.highs + (g <= rest % s.highs ? 1u : 0u);
-        a.c = s.bits - r;
+        a.c = s.bits - high_bits(s, c->n, g);
         a.q0 = s.bits + (g - 1u) * (rest / s.highs) + std::min(g - 1u, rest % s.highs);
     }
     a.tiles = c->N >> a.top;
@@ -641,7 +682,7 @@ hipError_t gate_iterate_blocked(grover_ctx *c, const Split &s, uint64_t k)
 
 hipError_t launch_hadamard_all_blocked(grover_ctx *c)
 {
-    const Split s = split(c, true);
+    const Split s = split(c->n, uint32_t(elem_bytes(c->dtype)), true);
     const bool parts = by_parts(s);
     switch (c->dtype) {
     case GROVER_F64_REAL: return hadamard_all_blocked<F64Real>(c, s);
@@ -653,7 +694,7 @@ hipError_t launch_hadamard_all_blocked(grover_ctx *c)
 
 hipError_t launch_gate_iterate_blocked(grover_ctx *c, uint64_t k)
 {
-    const Split s = split(c, false);
+    const Split s = split(c->n, uint32_t(elem_bytes(c->dtype)), false);
     const bool parts = by_parts(s);
     switch (c->dtype) {
     case GROVER_F64_REAL: return gate_iterate_blocked<F64Real>(c, s, k);
