@@ -262,8 +262,8 @@ struct WaveMarks {
             __syncthreads();
 #pragma unroll
             for (int e = 0; e < NE; ++e) {
-                const unsigned i = (unsigned(e) * B + tid) * EPV;
-                const unsigned b = (words[i / 32u] >> (i % 32u)) & ((1u << EPV) - 1u);
+                const unsigned w = words[tid * EPV / 32u + unsigned(e) * (B * EPV / 32u)];
+                const unsigned b = (w >> (tid * EPV % 32u)) & ((1u << EPV) - 1u);
                 mk.w[e / 16] |= b << (2 * (e % 16));
                 rows |= __ballot(b != 0u) != 0u ? uint64_t(1) << e : 0u;
             }
