@@ -506,9 +506,10 @@ struct GridSync {
 static_assert(sizeof(GridSync) == 1024, "barrier words on separate lines");
 
 // ------------------------------------------------------------------------------- team barrier memory
-// Teams of more than kFlatTeam workgroups whose size is a multiple of 8 meet in two levels (see team_sum).
+// Teams of more than kFlatTeam workgroups, up to one per CU of the 256, meet in two levels if their size is a multiple of
+// 8 (see team_sum).
 constexpr unsigned kFlatTeam = 128;
-__host__ __device__ constexpr bool team_two_level(uint64_t size) { return size > kFlatTeam && size <= 512 && size % 8 == 0; }
+__host__ __device__ constexpr bool team_two_level(uint64_t size) { return size > kFlatTeam && size <= 256 && size % 8 == 0; }
 // Bytes between member slots: 64 (two members to a 128-byte line) up to kFlatTeam, else 32.
 __host__ __device__ constexpr unsigned team_stride(uint64_t size) { return size <= kFlatTeam ? 64u : 32u; }
 constexpr uint64_t kGroupWords = 16;  // a group's sum in a two-level team: a 128-byte line each

@@ -227,19 +227,10 @@ __device__ bool team_sum(double &xr, double &xi, const Team &tm, uint64_t gen, T
                                           groups * uint32_t(kGroupWords) * 8u);
             const unsigned m = lane & 31u;
             double x[1] = {0.0};
-            if (tm.rank < groups) {  // the group's first member; per_group <= 64
-                double g = 0.0;
-                if (per_group <= 32u) {
-                    if (m < per_group)
-                        ok = wait_values<1>(slots, (pos + m) * stride + part, 0u, tag, &tm.sync->error, tm.timeout_ticks, x);
-                    g = x[0];
-                } else {
-                    double y[2] = {0.0, 0.0};
-                    if (lane < per_group)
-                        ok = wait_values<2>(slots, (pos + lane) * stride, 16u, tag, &tm.sync->error, tm.timeout_ticks, y);
-                    g = fold_pair(y[0], y[1]);
-                }
-                g = half_totals(g);
+            if (tm.rank < groups) {  // the group's first member; per_group <= 32
+                if (m < per_group)
+                    ok = wait_values<1>(slots, (pos + m) * stride + part, 0u, tag, &tm.sync->error, tm.timeout_ticks, x);
+                const double g = half_totals(x[0]);
                 const bool all_ok = __all(ok);
                 if (m == 31u && all_ok)
                     put_value(sums, tm.rank * uint32_t(kGroupWords) * 8u + part, g, tag);
