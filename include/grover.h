@@ -205,7 +205,9 @@ int grover_sync(grover_ctx *ctx);
  * tiles of each workgroup's share up to 272 MiB in all, the rest with nontemporal accesses; 0 for the other
  * forms).  The environment variable GROVER_FUSED_TEMPORAL, read at grover_init, makes a state of any size
  * stream, with all accesses nontemporal (0) or all ordinary (1); the results of the two are identical, and equal
- * up to the order of the sums to those of a state kept on chip. */
+ * up to the order of the sums to those of a state kept on chip.  GROVER_TEAM_CHECK=fail, read at grover_init, makes the
+ * residency check of a team that would hold the state on chip fail: the fused form and AUTO then stream the state, the
+ * held form is refused with GROVER_E_COOP. */
 int grover_query(grover_ctx *ctx, int key, int64_t *value);
 
 /* grover_stream_probe — measurement helper, not a step of the method: the bandwidth ceiling that the fused

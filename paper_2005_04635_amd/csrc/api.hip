@@ -98,8 +98,9 @@ int quiesce_device(grover_ctx *c, const char *what)
     return GROVER_OK;
 }
 
-// The held form's team must be co-resident (its members wait on each other): its barrier slots are
+// The team that holds a state must be co-resident (its members wait on each other): its barrier slots are
 // allocated and one team barrier is run under a short wait limit, as the fused form's grid is checked.
+// GROVER_TEAM_CHECK=fail makes a check that passed report the opposite.
 int check_held_team(grover_ctx *c, int clock_khz)
 {
     const int64_t team = int64_t(c->held_team);
@@ -116,8 +117,24 @@ int check_held_team(grover_ctx *c, int clock_khz)
     GROVER_HIP(c, hipStreamSynchronize(c->stream), "held team check");
     GridSync gs;
     GROVER_HIP(c, hipMemcpy(&gs, c->sync, sizeof(gs), hipMemcpyDeviceToHost), "held team check");
-    if (gs.error)
-        return fail(c, GROVER_E_COOP, "the held form's team is not co-resident on this device");
+    const char *env = getenv("GROVER_TEAM_CHECK");
+    if (gs.error || (env && std::string(env) == "fail"))
+        return fail(c, GROVER_E_COOP, "the team that holds the state is not co-resident on this device");
+    return GROVER_OK;
+}
+
+// Undoes a failed check_held_team: the state streams instead.
+int drop_held_team(grover_ctx *c)
+{
+    if (c->sync)
+        if (int st = reset_barrier(c, "barrier reset after a failed team check"))
+            return st;
+    (void)hipFree(c->partials);
+    (void)hipFree(c->sync);
+    c->partials = nullptr;
+    c->sync = nullptr;
+    c->held_team = 0;
+    c->last_error.clear();
     return GROVER_OK;
 }
 
@@ -126,14 +143,17 @@ int check_held_team(grover_ctx *c, int clock_khz)
 // fewer workgroups per CU of this kernel than it reports), so the grid is confirmed on the device: the
 // fused kernel runs with zero iterations (a read-only sum pass and one barrier) under a short wait limit,
 // and on a time-out the grid shrinks by one workgroup per CU.  GROVER_FUSED_GRID forces a grid, which must
-// pass the same check.  Allocates the barrier state and the per-workgroup partials.
-int select_persistent_grid(grover_ctx *c, int clock_khz)
+// pass the same check.  Allocates the barrier state and the per-workgroup partials.  A state that fits on chip is held
+// by a team instead (`on_chip`), unless that is not co-resident.
+int select_persistent_grid(grover_ctx *c, int clock_khz, bool on_chip)
 {
     int per_cu = 0, block = 0;
     int64_t forced = 0;
     GROVER_HIP(c, fused_configure(c, &per_cu, &block, &forced), "persistent grid configuration");
     c->per_cu_reported = per_cu;
-    if (c->held_team > 0) {  // the state stays on chip: a team instead of the streaming grid
+    if (!on_chip)
+        c->held_team = 0;
+    if (c->held_team > 0) {
         const int st = check_held_team(c, clock_khz);
         if (st == GROVER_OK) {
             c->grid = int(c->held_team);
@@ -142,13 +162,8 @@ int select_persistent_grid(grover_ctx *c, int clock_khz)
         }
         if (st != GROVER_E_COOP)
             return st;
-        if (int rs = reset_barrier(c, "barrier reset after a failed team check"))
+        if (int rs = drop_held_team(c))
             return rs;
-        (void)hipFree(c->partials);
-        (void)hipFree(c->sync);
-        c->partials = nullptr;
-        c->sync = nullptr;
-        c->held_team = 0;
     }
     if (per_cu < 1)
         per_cu = 1;  // the runtime may report 0 workgroups per CU; the device check below decides
@@ -462,13 +477,20 @@ int grover_init(grover_ctx **out, const grover_config *cfg, void *hip_stream, vo
             status = hip_fail(c, e, "initial state");
             throw status;
         }
-        if (form == GROVER_FORM_FUSED) {
-            // needs the marked list on the device and a written state: it runs the fused kernel
-            status = select_persistent_grid(c, clock_khz);
+        bool on_chip = true;
+        if (form == GROVER_FORM_HELD) {
+            status = check_held_team(c, clock_khz);
+            if (status == GROVER_E_COOP && auto_form) {  // the caller asked for no form in particular
+                status = drop_held_team(c);
+                c->form = form = GROVER_FORM_FUSED;
+                on_chip = false;
+            }
             if (status != GROVER_OK)
                 throw status;
-        } else if (form == GROVER_FORM_HELD) {
-            status = check_held_team(c, clock_khz);
+        }
+        if (form == GROVER_FORM_FUSED) {
+            // needs the marked list on the device and a written state: it runs the fused kernel
+            status = select_persistent_grid(c, clock_khz, on_chip);
             if (status != GROVER_OK)
                 throw status;
         }
