@@ -162,7 +162,8 @@ int grover_apply_hadamard_all_blocked(grover_ctx *ctx);
  *   Q_i = q_0 + ... + q_i (exact integer prefix sum), and for shot j with 53-bit uniform U_j:
  *   t_j = floor(U_j * Q_{N-1} / 2^53), index_j = the smallest i with Q_i > t_j.
  * Because the CDF is an integer prefix sum, the result depends only on the state's bits, not on the order
- * of the device's scan.
+ * of the device's scan.  The sum of the p_i has to be below 4, so that Q_{N-1} fits; the indices are unspecified, but
+ * below N, where it is not (or where an amplitude is not finite).
  *   shots        number of shots (0 allowed).
  *   seed         U_j = SplitMix64_j(seed) >> 11, generated on the device.
  *   out          shots uint64 indices; a device pointer when out_is_device != 0, else host memory (the call
