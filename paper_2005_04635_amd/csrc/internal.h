@@ -242,8 +242,8 @@ struct AccF32Kahan {
 // The update of complex bfloat16.  Rounding binary64 once, in integers (double_to_bf16), is some ten instructions for
 // each part.  Rounding to binary32 and from there to bfloat16, one and a half, differs from it only where the binary32
 // lies halfway between two bfloat16: then the part's true value may be to either side.  Those vectors (one in 8192 of
-// unrelated values) are rounded again in integers.  (The conversion of all 2^32 binary32 was compared with rounding
-// in integers.)  On MI355X a search at n = 26 was bound by these instructions: 78.0 -> 73.8 us per iteration
+// unrelated values) are rounded again in integers.  The tests hold it to one rounding in integers for ties and what lies
+// next to them, subnormal parts, the overflow threshold and signed zeros; a NaN stays one.  On MI355X a search at n = 26 was bound by these instructions: 78.0 -> 73.8 us per iteration
 // (n = 24 23.9 -> 18.1).
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
