@@ -141,7 +141,7 @@ uint32_t next_pow2(uint64_t x)
     return p;
 }
 
-// Phases of a tiling.  With resident vectors r > 0, an instance whose state fits on chip in a team of
+// Phases of a tiling.  With resident = r > 0, an instance whose state fits on chip in a team of
 // T = the power of two >= nvec / (r * 1024) workgroups (T no larger than the largest power of two <= grid)
 // runs in the resident phase of that T; states of <= 16384 vectors (n <= 15) run alone on chip.
 // Every other instance streams: with n >= split_n and team > 1 in a streamed phase of teams of `team`
@@ -152,7 +152,7 @@ int apply_tiling(grover_batch *b, uint32_t split_n, uint32_t team_size, uint32_t
     if (team_size < 1 || team_size > uint32_t(b->grid))
         return bfail(b, GROVER_E_INVAL, "team size must lie in [1, grid size]");
     if (resident > uint32_t(kBatchHoldE) || (resident & (resident - 1u)) != 0u)
-        return bfail(b, GROVER_E_INVAL, "resident vectors per thread must be 0, 1, 2, 4, 8 or 16");
+        return bfail(b, GROVER_E_INVAL, "resident must be 0, 1, 2, 4, 8 or 16 (times 1024 vectors per workgroup)");
     const uint32_t max_team = next_pow2(uint64_t(b->grid) + 1) / 2;  // largest power of two <= grid
     std::vector<uint32_t> order(b->count);
     std::iota(order.begin(), order.end(), 0u);

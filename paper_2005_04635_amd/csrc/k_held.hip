@@ -16,8 +16,8 @@
 // thread are held widened to binary64 (values that a binary32 represents), which saves one of five
 // instructions per part.  One optimal search (or 801 iterations at n = 24), 1024-thread workgroups of at most 16
 // vectors and the earlier barrier (n = 24 and complex128: the streaming fused kernel) -> this kernel on MI355X:
-// complex64 n = 16 (binary32 update) 0.635 -> 0.311 ms, n = 20 3.49 -> 2.07, n = 24 14.1 -> 6.44 (8.0 us per
-// iteration); complex128 n = 21 4.61 -> 1.98 ms (2.5 us per iteration).
+// complex64 n = 16 (binary32 update) 0.635 -> 0.32 ms, n = 20 3.49 -> 2.04, n = 24 14.1 -> 5.87 (7.3 us per
+// iteration); complex128 n = 21 4.61 -> 1.91 ms (2.4 us per iteration).
 #include <algorithm>
 
 #include "held.h"

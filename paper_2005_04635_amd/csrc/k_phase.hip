@@ -168,7 +168,7 @@ struct PhaseArgs {
     const double *dloss;        // [B]
     double *dphi, *dtheta;      // [B][K]
     PhaseSync *sync;            // one per team
-    uint64_t *partials;         // [teams][2][T][8]
+    uint64_t *partials;         // [teams][2][T][16]
     uint32_t team_size;
     uint32_t probe;  // 1: only meet once at a barrier of the whole grid (residency check)
     uint64_t timeout_ticks;

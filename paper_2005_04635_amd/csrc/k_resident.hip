@@ -6,9 +6,9 @@
 // What bounds an iteration is the workgroup's sum (0.23 us with 256 threads, 0.30 with 512, two waves per SIMD) and
 // the update's instructions.  So the workgroup is as small as its registers allow without making the update the
 // larger part: one wave up to 256 vectors, whose sum needs no barrier at all, 256 threads up to 1024, then 512 with
-// up to 32 vectors per thread.  On MI355X, whole searches with reset, against 1024
-// threads for every size with a sign factor on every amplitude: n = 10 binary64, 25 iterations and 10^4 shots
-// 35 -> 16 us; n = 13 complex64, 41 iterations 82 -> 39 us.
+// up to 32 vectors per thread.  On MI355X, whole searches with reset, against 1024 threads for every size with a sign
+// factor on every amplitude: n = 10 binary64, 25 iterations and 10^4 shots 35 -> 15 us; n = 13 complex64, 41 iterations
+// 82 -> 37 us.
 #include "held.h"
 
 namespace grover {

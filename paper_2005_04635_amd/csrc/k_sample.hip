@@ -8,8 +8,8 @@
 // its group of 16 or 64 among the block's, and adds up the group's q_i itself.  What is kept is one prefix sum per
 // group, so the state is read once and little is written.  At n = 28 complex64 on MI355X, 10^6 shots of a searched
 // state: 1.21 ms (block totals 0.33, their scan 0.11, the CDF written 0.74, searches 0.04) -> 0.45 ms.  States of
-// up to kSmallN amplitudes are sampled by one launch, every workgroup building the whole CDF in its LDS (four
-// launches and their gaps before; 10^4 shots at n = 10: 11 -> 5.5 us).
+// up to kSmallN amplitudes (complex128: half) are sampled by one launch, every workgroup building the whole CDF in its
+// LDS (four launches and their gaps before; 10^4 shots at n = 10: 11 -> 5.5 us).
 #include "internal.h"
 
 namespace grover {
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(kGroupBlock, T::EPV == 1 ? 4 : 8) void group_sums_k
     uint64_t so_far = 0;     // wave 0: the block's sum before this tile
     uint64_t b = blockIdx.x, i = 0;  // block, and tile of the block
     for (unsigned n = 0, p = 0; b < nb; p ^= 1u) {  // n: tiles in `kept`
-        // the state has more than kSmallN amplitudes, so every tile is full
+        // the state has more than small_limit amplitudes, two tiles and more, so every tile is full
         const V *from = st + (b * tiles + i) * (kTile / T::EPV) + 2u * tid;
         V x[R][2];
 #pragma unroll
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(kSearchBlock) void search_kernel(const void *state,
     }
 }
 
-// States of up to kSmallN amplitudes: every workgroup builds the CDF in LDS (1024 threads, each the vectors of one
+// States of up to small_limit amplitudes: every workgroup builds the CDF in LDS (1024 threads, each the vectors of one
 // contiguous run of kSmallN / 1024 amplitudes or fewer) and serves its shots from there.  n = 10, 10^4 shots: one
 // launch of about 4 us instead of four kernels.
 template <class T>
