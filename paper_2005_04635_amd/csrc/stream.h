@@ -359,7 +359,7 @@ __device__ inline void stream_pass(const Share<T> &sh, const uint32_t *table, bo
         else
             update_vec<T>(v, mr, mi, bits, acc);
     };
-    const unsigned tid = threadIdx.x;
+    const unsigned tid = fresh_tid();
     const uint64_t cnt = sh.count();
     uint64_t mp = 0;  // marked entries before this position lie in tiles already visited
     auto plain = [&](uint64_t j) {  // a full tile without marked amplitudes
