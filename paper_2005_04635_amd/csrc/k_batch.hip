@@ -129,6 +129,12 @@ __global__ __launch_bounds__(kBatchBlock) void batch_kernel(BatchArgs a)
         (void)team_sum<kBatchBlock>(zr, zi, tm, 1u, sh);
         return;
     }
+    // A limit of zero gives up before the first team's barrier (team sizes do not increase): at the barriers, members that
+    // arrive together would not have to wait.
+    if (a.timeout_ticks == 0u && a.nphases > 0u && a.team[0] > 1u) {
+        flag_error(a.sync);
+        return;
+    }
     const unsigned major = xcd_major_block();
     for (uint32_t p = 0; p < a.nphases; ++p) {
         const uint64_t q0 = a.qoff[p], count = a.qoff[p + 1] - q0;

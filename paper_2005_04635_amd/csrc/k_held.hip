@@ -66,9 +66,13 @@ __global__ __launch_bounds__(kChipBlock) void chip_iterate_kernel(ChipArgs a)
     // A launch enqueued behind a failure (a wait that gave up, or input rejected on the device) leaves the
     // state as it is.  Thread 0 reads the error word (other threads might read it later and differ) and the
     // workgroup barrier before the first sum hands the answer on.
+    // A limit of zero gives up here: at the barriers, members that arrive together would not have to wait.
     uint32_t error = 0u;
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
+        if (a.timeout_ticks == 0u)
+            __hip_atomic_store(&a.sync->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         error = __hip_atomic_load(&a.sync->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     const uint64_t base = uint64_t(rank) * a.per;
     (void)held_run<T, U32, kWide, NE, RE, kChipBlock, true>(
         static_cast<V *>(a.state) + base, base, a.per, a.marks, a.m, a.iters, a.scale, V{}, words,

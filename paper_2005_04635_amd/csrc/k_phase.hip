@@ -174,6 +174,14 @@ struct PhaseArgs {
     uint64_t timeout_ticks;
 };
 
+// A limit of zero gives up before the first barrier: at the barriers, members that arrive together would not have to wait.
+__device__ inline bool gives_up(const PhaseArgs &a, const PhaseTeam &tm)
+{
+    if (a.timeout_ticks == 0u && threadIdx.x == 0)
+        __hip_atomic_store(&tm.sync->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return a.timeout_ticks == 0u;
+}
+
 // Marked entries of one tile: the slice [mp, mq) of the sorted list, held in registers when short.
 struct TileMarks {
     uint64_t mp, mq;
@@ -295,6 +303,8 @@ __global__ __launch_bounds__(kStreamBlock) void phase_forward_kernel(PhaseArgs a
         (void)team_sum_n<kStreamBlock, kPV>(v, tm, ++gen, sh);
         return;
     }
+    if (gives_up(a, tm))
+        return;
     const bool use_table = build_phase_table(a, tm, table);
     for (uint32_t b = team_id; b < a.B; b += teams) {
         float4 *st = a.state + uint64_t(b) * a.nvec;
@@ -449,6 +459,8 @@ __global__ __launch_bounds__(kStreamBlock) void phase_adjoint_kernel(PhaseArgs a
         (void)team_sum_n<kStreamBlock, kPV>(v, tm, ++gen, sh);
         return;
     }
+    if (gives_up(a, tm))
+        return;
     const bool leader = tm.rank == 0 && threadIdx.x == 0;
     const bool use_table = build_phase_table(a, tm, table);
     for (uint32_t b = team_id; b < a.B; b += teams) {
@@ -607,6 +619,8 @@ __global__ __launch_bounds__(kHeldBlock) void phase_forward_held_kernel(PhaseArg
         (void)team_sum_n<kHeldBlock, 4>(v, tm, ++gen, sh);
         return;
     }
+    if (gives_up(a, tm))
+        return;
     const unsigned tid = threadIdx.x;
     const uint64_t per = a.per, base = uint64_t(tm.rank) * per;
     const bool active = NE > 1 || tid < per;
@@ -743,6 +757,8 @@ __global__ __launch_bounds__(kHeldBlock) void phase_adjoint_held_kernel(PhaseArg
         (void)team_sum_n<kHeldBlock, 5>(v, tm, ++gen, sh);
         return;
     }
+    if (gives_up(a, tm))
+        return;
     const unsigned tid = threadIdx.x;
     const bool leader = tm.rank == 0 && tid == 0;
     const uint64_t per = a.per, base = uint64_t(tm.rank) * per;

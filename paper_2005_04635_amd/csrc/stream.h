@@ -55,7 +55,8 @@ __device__ inline void put_value(__amdgpu_buffer_rsrc_t slots, uint32_t off, dou
 // passes (then setting the error word); both are looked at in the first round and every 16th, the error word by a
 // load issued with that round's others (on its own it would add a memory round trip to nearly every barrier: the
 // first round mostly comes too early).  The clock is first read in the 16th round, for the same reason: the
-// limit counts from there, and a limit of zero gives up in the first round.
+// limit counts from there, and a limit of zero gives up in the first round unless all is there already (kernels that
+// are to give up at a limit of zero in any case look at it before their first barrier).
 template <int NV>
 __device__ inline bool wait_offsets(__amdgpu_buffer_rsrc_t slots, const uint32_t (&off)[NV], const bool (&use)[NV],
                                     uint32_t tag, uint32_t *error, uint64_t timeout_ticks, double (&x)[NV])
