@@ -227,7 +227,7 @@ struct WaveMarks {
     // vector 8.8, 28.8 and 32.9 us; a search per vector always 3.6, 19.5, 20.9; this 2.7, 7.2, 7.5.
     __device__ inline void find(const uint64_t *marks, uint64_t m, uint64_t base, uint64_t per, uint32_t *words)
     {
-        const unsigned tid = fresh_tid(), lane = tid % kWave, wave = tid / kWave;
+        const unsigned tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
         uint64_t lo = 0, hi = m;
         if (m > uint64_t(kWave)) {
             lo = wave_lower_bound(marks, m, base * EPV);
