@@ -433,7 +433,7 @@ int grover_batch_init(grover_batch **out, const grover_batch_config *cfg, void *
         status = select_grid(b, clock_khz);
         if (status != GROVER_OK)
             throw status;
-        // default tiling until tuned: states held on chip by teams sized for 16 vectors per thread; states too large for that stream with teams of 2
+        // default tiling until tuned: states held on chip by teams whose threads hold up to 32 vectors; states too large for that stream with teams of 2
         status = apply_tiling(b, 19, b->grid >= 2 ? 2u : 1u, uint32_t(kBatchHoldE));
         if (status != GROVER_OK)
             throw status;

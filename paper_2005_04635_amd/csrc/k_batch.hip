@@ -19,7 +19,7 @@
 // rather than 1024: all 32 vectors sit in registers (the other half of 16 went through LDS), and half the waves
 // pay the reduction.  Two workgroups of 16 vectors per CU, to update one instance while another waits, do not
 // overlap: a second workgroup on the CU lengthened the barrier from 1.4 to 2.9 us (T = 64), whatever the waves'
-// priorities and the pace of the polls, and an n = 20 iteration to 4.5 us.  1024 searches of n = 8 .. 20: 32.2 -> 23.2
+// priorities and the pace of the polls, and an n = 20 iteration to 4.5 us.  1024 searches of n = 8 .. 20: 32.2 -> 22.9
 // ms on MI355X.
 #include "batch.h"
 #include "held.h"
